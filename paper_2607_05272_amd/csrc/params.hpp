@@ -176,6 +176,14 @@ hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t of
                       float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
                       float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st);
 bool ppo_shape_supported(const MlpParams& m);
+// The same in four launches for the rollout policies' networks (ppo_fused.hip), in a scratch of
+// ppo_scratch_bytes: whether it takes this network and minibatch, and its launch.
+bool pg_fused_supported(const MlpParams& m, int M, size_t scratch_bytes);
+hipError_t launch_pg_fused(const MlpParams& m, const void* d_weights, const size_t off[6], int T,
+                           const float* obs, const uint8_t* act, const float* logp_old,
+                           const double* adv, const double* ret, int M, uint64_t seed, float clip,
+                           float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
+                           float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st);
 size_t ppo_scratch_bytes(const MlpParams& m, int M);
 // The fixed device scratch of ppo_minibatch_grad_noalloc: its size, and its address on the
 // current device (looked up once per device with hipGetSymbolAddress; allocates nothing).

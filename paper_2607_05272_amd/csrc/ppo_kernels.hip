@@ -10,6 +10,9 @@
 //   rho = exp(logp_new(a) - logp_old), H the entropy of the action distribution; REINFORCE
 //   replaces the first term by -mean(A log pi(a|s)) with A held constant.
 //
+// Networks of the rollout policies' widths run in the four launches of ppo_fused.hip; the form
+// here takes any hidden widths that are multiples of 64.
+//
 // The eight dense products run in one MFMA GEMM template (mb_gemm_k) with the elementwise
 // steps fused into its epilogues:
 //   forward    Z^T = W^T X^T per layer; epilogue: + bias, GELU, bf16 rounding, GELU'(z) kept,
@@ -26,8 +29,7 @@
 // v_mfma_f32_16x16x32_bf16. fp32 mode (fp32 policies): fp32 operands, v_mfma_f32_16x16x4_f32.
 #include <mutex>
 
-#include "devmath.hpp"
-#include "params.hpp"
+#include "ppo_dev.hpp"
 
 // Fixed device scratch of the minibatch gradient for callers that cannot allocate
 // (ppo_minibatch_grad_noalloc): one copy per GPU, held until the process ends. Host code must
@@ -38,56 +40,8 @@ static __device__ __align__(256) unsigned char scratch[bsim::kStaticScratchBytes
 namespace bsim {
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
 constexpr int kThr = 256;   // 4 waves
 constexpr int kTile = 64;   // output tile edge of a workgroup; every dimension is padded to it
-
-__device__ __forceinline__ float bf16_round(float f) { return bf16_to_f32(bf16_bits(f)); }
-__device__ __forceinline__ float gelu_exact(float z) {
-  return 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
-}
-__device__ __forceinline__ float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
-}
-
-// Operand modes. Both MFMA shapes take, per lane l, the row (A) or column (B) l % 16 and a run
-// of consecutive k (8 bf16 from k = 8 (l / 16), or one fp32 at k = l / 16): every operand
-// array is stored k-contiguous, [row][k]. Their 16 x 16 results share one layout: lane l holds
-// column l % 16, rows 4 (l / 16) .. + 3.
-struct Bf16Mode {
-  typedef uint16_t T;
-  typedef bf16x8 frag;
-  static constexpr int KS = 32, SPLIT = 2;
-  __device__ static int koff(int lane) { return (lane >> 4) * 8; }
-  __device__ static frag load(const T* p) { return *reinterpret_cast<const bf16x8*>(p); }
-  __device__ static f32x4 mfma(frag a, frag b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-  __device__ static T act(float v) { return bf16_bits(v); }     // activation (already rounded)
-  __device__ static float actf(float v) { return bf16_round(v); }
-  __device__ static void split(float v, T& hi, T& lo) {
-    hi = bf16_bits(v);
-    lo = bf16_bits(v - bf16_to_f32(hi));
-  }
-  __device__ static float value(T v) { return bf16_to_f32(v); }
-};
-
-struct F32Mode {
-  typedef float T;
-  typedef float frag;
-  static constexpr int KS = 4, SPLIT = 1;
-  __device__ static int koff(int lane) { return lane >> 4; }
-  __device__ static frag load(const T* p) { return *p; }
-  __device__ static f32x4 mfma(frag a, frag b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static T act(float v) { return v; }
-  __device__ static float actf(float v) { return v; }
-  __device__ static void split(float v, T& hi, T& lo) { hi = v; lo = 0.f; }
-  __device__ static float value(T v) { return v; }
-};
 
 // C [R][N] = sum_k A[r][k] (B0[n][k] + B1[n][k]) for one kTile x kTile output tile per
 // workgroup: wave w owns rows 32 (w & 1) .. + 31 and columns 32 (w >> 1) .. + 31 as 2 x 2 MFMA
@@ -469,19 +423,8 @@ __global__ __launch_bounds__(kThr) void mb_loss_k(LossArgs<Md> a) {
         const float v = a.A < 64 ? va0 : va1;
         const float invM = 1.0f / (float)a.M;
         float dlogp, pterm;
-        if (a.reinforce) {
-          // -A log pi(a|s), the advantage held constant
-          dlogp = -adv * invM;
-          pterm = -adv * logp;
-        } else {
-          const float rho = expf(logp - a.logp_old[ti]);
-          const float lo = 1.0f - a.clip, hi = 1.0f + a.clip;
-          const float rc = fminf(fmaxf(rho, lo), hi);
-          const float s1 = rho * adv, s2 = rc * adv;
-          const float g_rho = s1 <= s2 ? adv : ((rho > lo && rho < hi) ? adv : 0.0f);
-          dlogp = -g_rho * rho * invM;
-          pterm = -fminf(s1, s2);
-        }
+        policy_term(a.reinforce, a.clip, logp, a.reinforce ? 0.0f : a.logp_old[ti], adv, invM,
+                    dlogp, pterm);
         const float dv = 2.0f * a.c_v * (v - ret) * invM;
         if (i0 < a.Ap) {
           g0 = in0 ? -dlogp * p0 + a.c_h * invM * p0 * (lp0 + H) : dv;
@@ -893,6 +836,9 @@ hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t of
                       float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
                       float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st) {
   if (M < 1 || !ppo_shape_supported(m)) return hipErrorInvalidValue;
+  if (pg_fused_supported(m, M, ppo_scratch_bytes(m, M)))
+    return launch_pg_fused(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed, clip, c_v,
+                           c_h, reinforce, scratch, loss_out, grads, idx_out, err, st);
   if (m.bf16)
     return run_minibatch<Bf16Mode>(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed,
                                    clip, c_v, c_h, reinforce, scratch, loss_out, grads, idx_out,
