@@ -15,18 +15,14 @@
 // SIMT code: every weight is read at a wave-uniform address (scalar loads through the
 // scalar cache), the per-environment state stays in registers, and the observation columns
 // obs[f][E] are read coalesced.
-#include "devmath.hpp"
-#include "params.hpp"
+#include "ppo_dev.hpp"
+#include "train_dev.hpp"
 
 namespace bsim {
 namespace {
 
 constexpr int kD = 4;          // embedding width
 constexpr int kBlock = 256;
-
-__device__ __forceinline__ float gelu_exact(float x) {
-  return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
-}
 
 // Scores are kept in base-2 units: the queries carry the factor log2(e) / sqrt(D/NH), so each
 // softmax weight is one exp2 of (score - max).
@@ -215,12 +211,23 @@ hipError_t run_attn_h(const AttnParams& p, const float* obs, const uint64_t* see
 }
 
 // ---- gradient of one minibatch (Sec. 4.3 losses through the Sec. 4.2 network) --------------
-// One lane per sample m: the (t, env) index drawn like the MLP minibatch's, the forward in
-// fp32, the loss gradient with respect to the logits and V, then the chain rule backwards.
-// The pooled vector's gradient dp reaches every token's output equally (dy_g = dp / L), so
+// Eight lanes per sample m, lane g of them holding token g (idle where g >= L) and every eighth
+// unit of the heads: the (t, env) index drawn like the MLP minibatch's, the forward in fp32, the
+// loss gradient with respect to the logits and V, then the chain rule backwards. The pooled
+// vector's gradient dp reaches every token's output equally (dy_g = dp / L), so
 // dW_o = (sum_g o_g)^T dy, do_g = dy W_o^T is the same for every token and so is
-// da_{gj} = do . v_j per head; the softmax weights are recomputed per query token. Every
-// parameter's per-sample term goes to gs[param][m]; a second kernel sums over m in a fixed order.
+// da_{gj} = do . v_j per head. What a query's lane needs of the other tokens (keys and values, and
+// in the backward the softmax weights and score gradients of their queries) it reads from the
+// sample's slice of LDS; the eight lanes are part of one wave, so no barrier is needed for it.
+//
+// A workgroup takes kSamples samples. The heads run in chunks of kUnits units staged in LDS; in
+// the backward the chunk's activations and gradients dz go to LDS and each thread sums its
+// parameters' terms over the workgroup's samples, while the attention's parameters are summed
+// over the wave's lanes. Each workgroup writes one row of partial sums [P]; attn_finish_k adds
+// the rows in a fixed order. Bound by the chain of one sample's layers at one wave per SIMD:
+// 8192 samples of the 8-token, 2-head, 64-unit network take 20 us and the sums with Adam's step 4
+// (one lane per sample, on an eighth of the SIMDs, with every per-sample term through memory:
+// 159 us and, in four launches, 27).
 struct AttnGradArgs {
   AttnParams p;
   int T, M, reinforce;
@@ -231,106 +238,170 @@ struct AttnGradArgs {
   const double* ret;         // [T][E]
   uint64_t seed;
   float clip, c_v, c_h;
-  float* gs;                 // [P][M] per-sample gradient terms
-  double* terms;             // [M][3] policy, value, entropy per sample
+  float* part;               // [workgroups][P] partial sums of the gradient
+  double* terms;             // [workgroups][3] policy, value, entropy sums
   int64_t* idx_out;          // optional [M]
   uint32_t* err;
   int off[14];               // start of each parameter array in the gradient vector
   int P;
 };
 
-__device__ __forceinline__ float gelu_grad(float z) {
-  return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * expf(-0.5f * z * z) * 0.39894228040143268f;
+constexpr int kSamples = 32, kUnits = 64, kUStride = kUnits + 8;   // rows 8 banks apart
+constexpr int kGradThr = 8 * kSamples;
+// a sample's slice: keys and values of its tokens, and one head's [query][key] of weights and
+// score gradients with the queries they go with
+struct AttnSlice {
+  float kv[8][8];
+  float a[8][9], ds[8][9];
+  float q[8][4];
+};
+template <int A>
+struct HeadChunk {           // one chunk of a head's weights (the value head: A = 1)
+  float w1[kD][kUnits], b1[kUnits], w2[kUnits][A];
+};
+template <int A>
+struct AttnGradLds {
+  AttnSlice sl[kSamples];
+  HeadChunk<A> pol;
+  HeadChunk<1> val;
+  float h[kSamples][kUStride], dz[kSamples][kUStride];   // the backward's chunk
+  float dl[kSamples][A], dV[kSamples], pool[kSamples][kD];
+  double terms[kSamples][3];
+};
+
+__device__ __forceinline__ void wave_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Sums by DPP moves within rows of 16 lanes (two samples): over a sample's 8 lanes (quads, then
+// the other quad by a half-row mirror), and with the other sample's lane of the same part (a
+// rotation by 8); every lane that shares a sum gets the same bits.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float sum8(float v) {
+  v += dpp_f<0xB1>(v);
+  v += dpp_f<0x4E>(v);
+  return v + dpp_f<0x141>(v);
+}
+__device__ __forceinline__ float sum_pair(float v) { return v + dpp_f<0x128>(v); }
+
+// Units j0 .. j0 + kUnits - 1 of a head (zero past its n units) into LDS, by the workgroup.
+template <int A>
+__device__ __forceinline__ void stage_head(HeadChunk<A>& c, const float* w1, const float* b1,
+                                           const float* w2, int n, int j0) {
+  for (int q = threadIdx.x; q < kUnits * (kD + 1 + A); q += kGradThr) {
+    const int r = q / kUnits, u = q % kUnits;
+    if (r < kD) {
+      c.w1[r][u] = j0 + u < n ? w1[r * n + j0 + u] : 0.f;
+    } else if (r == kD) {
+      c.b1[u] = j0 + u < n ? b1[j0 + u] : 0.f;
+    } else {
+      const int e = (r - kD - 1) * kUnits + u;   // w2's rows of this chunk are contiguous
+      (&c.w2[0][0])[e] = j0 * A + e < n * A ? w2[j0 * A + e] : 0.f;
+    }
+  }
 }
 
 template <int L, int NH, int A>
-__global__ __launch_bounds__(64) void attn_grad_k(AttnGradArgs g) {
+__global__ __launch_bounds__(kGradThr) void attn_grad_k(AttnGradArgs g) {
   constexpr int D = kD, DH = D / NH;
   const float rs = DH == 1 ? 1.0f : DH == 2 ? 0.70710678118654752f : 0.5f;  // 1 / sqrt(DH)
-  const int m = blockIdx.x * 64 + threadIdx.x;
-  if (m >= g.M) return;
+  __shared__ AttnGradLds<A> S;
+  const int tid = threadIdx.x, lane = tid & 63, sl = tid >> 3, gg = tid & 7;
+  const int m = blockIdx.x * kSamples + sl;
   const AttnParams& p = g.p;
-  const size_t E = (size_t)p.E, M = (size_t)g.M;
+  const size_t E = (size_t)p.E;
   const int G = p.F / L;
-  auto put = [&](int k, int i, float v) { g.gs[(size_t)(g.off[k] + i) * M + m] = v; };
+  const bool tokn = gg < L;          // the lane holds a token
+  float* part = g.part + (size_t)blockIdx.x * g.P;
 
-  const u32x4 w = draw(g.seed, (uint32_t)m, 0xFFFFFFFDu, P_MINIBATCH, 0, 0);
-  long long ix = (long long)(unit(w.x, w.y) * ((double)g.T * (double)p.E));
-  if (ix > (long long)g.T * p.E - 1) ix = (long long)g.T * p.E - 1;
-  if (g.idx_out) g.idx_out[m] = ix;
-  const int t = (int)(ix / p.E), e = (int)(ix % p.E);
-  const size_t ti = (size_t)t * E + e;
+  // the heads' first chunks, while the sample is fetched
+  stage_head<A>(S.pol, p.wp1, p.bp1, p.wp2, p.Hp, 0);
+  stage_head<1>(S.val, p.wv1, p.bv1, p.wv2, p.Hv, 0);
+
+  // the sample: past M it is computed with a zero observation and contributes nothing, and so does
+  // one whose stored action is invalid (flagged)
+  long long ix = 0;
+  if (m < g.M) {
+    const u32x4 w = draw(g.seed, (uint32_t)m, 0xFFFFFFFDu, P_MINIBATCH, 0, 0);
+    ix = (long long)(unit(w.x, w.y) * ((double)g.T * (double)p.E));
+    if (ix > (long long)g.T * p.E - 1) ix = (long long)g.T * p.E - 1;
+    if (gg == 0 && g.idx_out) g.idx_out[m] = ix;
+  }
+  const int t = (int)ix / p.E, e = (int)ix - t * p.E;   // T E < 2^31 (checked by the host)
+  const size_t ti = (size_t)ix;
   const float* xo = g.obs + (size_t)t * p.F * E + e;
   const int a_act = g.act[ti];
-  if (a_act >= A) {  // invalid stored action: flag it, the sample contributes nothing
-    atomicOr(g.err, ERR_ACTION);
-    for (int i = 0; i < g.P; ++i) g.gs[(size_t)i * M + m] = 0.0f;
-    g.terms[m * 3] = g.terms[m * 3 + 1] = g.terms[m * 3 + 2] = 0.0;
-    return;
-  }
+  const float adv = (float)g.adv[ti], ret = (float)g.ret[ti];
+  const float lold = g.reinforce ? 0.f : g.logp_old[ti];
+  const bool bad = m < g.M && a_act >= A;
+  if (bad && gg == 0) atomicOr(g.err, ERR_ACTION);
+  const bool on = m < g.M && !bad;
 
-  // forward
-  float tok[L][D];
+  // forward: the lane's token, its query, key and value
+  float tok[D];
 #pragma unroll
-  for (int gg = 0; gg < L; ++gg) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) tok[gg][d] = p.b_in[d];
+  for (int d = 0; d < D; ++d) tok[d] = p.b_in[d];
+  if (tokn)
     for (int i = gg * G; i < (gg + 1) * G; ++i) {
-      const float x = xo[(size_t)i * E];
+      const float x = on ? xo[(size_t)i * E] : 0.f;
 #pragma unroll
-      for (int d = 0; d < D; ++d) tok[gg][d] = fmaf(x, p.w_in[i * D + d], tok[gg][d]);
+      for (int d = 0; d < D; ++d) tok[d] = fmaf(x, p.w_in[i * D + d], tok[d]);
     }
+  float q[D], k[D], v[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    float aq = p.b_qkv[d], ak = p.b_qkv[D + d], av = p.b_qkv[2 * D + d];
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      aq = fmaf(tok[i], p.w_qkv[i * 3 * D + d], aq);
+      ak = fmaf(tok[i], p.w_qkv[i * 3 * D + D + d], ak);
+      av = fmaf(tok[i], p.w_qkv[i * 3 * D + 2 * D + d], av);
+    }
+    q[d] = aq; k[d] = ak; v[d] = av;
   }
-  float q[L][D], k[L][D], v[L][D];
+  AttnSlice& X = S.sl[sl];
 #pragma unroll
-  for (int gg = 0; gg < L; ++gg)
+  for (int d = 0; d < D; ++d) {
+    X.kv[gg][d] = k[d];
+    X.kv[gg][D + d] = v[d];
+    X.q[gg][d] = q[d];
+  }
+  wave_lds();
+  float att[NH][L];   // softmax weights of the lane's query
+  float osum[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      float aq = p.b_qkv[d], ak = p.b_qkv[D + d], av = p.b_qkv[2 * D + d];
-#pragma unroll
-      for (int i = 0; i < D; ++i) {
-        aq = fmaf(tok[gg][i], p.w_qkv[i * 3 * D + d], aq);
-        ak = fmaf(tok[gg][i], p.w_qkv[i * 3 * D + D + d], ak);
-        av = fmaf(tok[gg][i], p.w_qkv[i * 3 * D + 2 * D + d], av);
-      }
-      q[gg][d] = aq; k[gg][d] = ak; v[gg][d] = av;
-    }
-  // softmax weights of query gg, head h
-  auto weights = [&](int gg, int h, float (&a)[L]) {
-    float mx = -INFINITY;
+  for (int h = 0; h < NH; ++h) {
+    float mx = -INFINITY, s = 0.f, o[DH];
 #pragma unroll
     for (int j = 0; j < L; ++j) {
       float dot = 0.f;
 #pragma unroll
-      for (int tt = h * DH; tt < (h + 1) * DH; ++tt) dot = fmaf(q[gg][tt], k[j][tt], dot);
-      a[j] = dot * rs;
-      mx = fmaxf(mx, a[j]);
+      for (int x = 0; x < DH; ++x) dot = fmaf(q[h * DH + x], X.kv[j][h * DH + x], dot);
+      att[h][j] = dot * rs;
+      mx = fmaxf(mx, att[h][j]);
     }
-    float S = 0.f;
 #pragma unroll
     for (int j = 0; j < L; ++j) {
-      a[j] = expf(a[j] - mx);
-      S += a[j];
+      att[h][j] = expf(att[h][j] - mx);
+      s += att[h][j];
     }
-    const float inv = 1.0f / S;
+    const float inv = tokn ? 1.0f / s : 0.f;
 #pragma unroll
-    for (int j = 0; j < L; ++j) a[j] *= inv;
-  };
-  float osum[D] = {0.f, 0.f, 0.f, 0.f};
+    for (int x = 0; x < DH; ++x) o[x] = 0.f;
 #pragma unroll
-  for (int gg = 0; gg < L; ++gg)
+    for (int j = 0; j < L; ++j) {
+      att[h][j] *= inv;   // zero in lanes without a token
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      float a[L];
-      weights(gg, h, a);
-#pragma unroll
-      for (int tt = h * DH; tt < (h + 1) * DH; ++tt) {
-        float acc = 0.f;
-#pragma unroll
-        for (int j = 0; j < L; ++j) acc = fmaf(a[j], v[j][tt], acc);
-        osum[tt] += acc;
-      }
+      for (int x = 0; x < DH; ++x) o[x] = fmaf(att[h][j], X.kv[j][D + h * DH + x], o[x]);
     }
+#pragma unroll
+    for (int x = 0; x < DH; ++x) osum[h * DH + x] = sum8(o[x]);
+  }
   float pool[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) {
@@ -339,228 +410,364 @@ __global__ __launch_bounds__(64) void attn_grad_k(AttnGradArgs g) {
     for (int i = 0; i < D; ++i) y = fmaf(osum[i], p.w_o[i * D + d], y);
     pool[d] = y * (1.0f / (float)L) + p.b_o[d];
   }
-  float lg[A];
+  // heads forward: the lane's units of every chunk, then the sample's sums
+  float lg[A], V = 0.f;
 #pragma unroll
-  for (int a = 0; a < A; ++a) lg[a] = p.bp2[a];
-  for (int j = 0; j < p.Hp; ++j) {
-    float z = p.bp1[j];
+  for (int a = 0; a < A; ++a) lg[a] = 0.f;
+  const int npol = (p.Hp + kUnits - 1) / kUnits, nval = (p.Hv + kUnits - 1) / kUnits;
+  for (int c = 0; c < npol; ++c) {
+    if (c > 0) {
+      __syncthreads();
+      stage_head<A>(S.pol, p.wp1, p.bp1, p.wp2, p.Hp, c * kUnits);
+    }
+    __syncthreads();
+#pragma unroll 2
+    for (int u = gg; u < kUnits; u += 8) {
+      float z = S.pol.b1[u], Phi, gr;
 #pragma unroll
-    for (int d = 0; d < D; ++d) z = fmaf(pool[d], p.wp1[d * p.Hp + j], z);
-    const float hj = gelu_exact(z);
+      for (int d = 0; d < D; ++d) z = fmaf(pool[d], S.pol.w1[d][u], z);
+      gelu_parts(z, Phi, gr);
+      const float hj = z * Phi;
 #pragma unroll
-    for (int a = 0; a < A; ++a) lg[a] = fmaf(hj, p.wp2[(size_t)j * A + a], lg[a]);
+      for (int a = 0; a < A; ++a) lg[a] = fmaf(hj, S.pol.w2[u][a], lg[a]);
+    }
   }
-  float V = p.bv2[0];
-  for (int j = 0; j < p.Hv; ++j) {
-    float z = p.bv1[j];
+  for (int c = 0; c < nval; ++c) {
+    if (c > 0) {
+      __syncthreads();
+      stage_head<1>(S.val, p.wv1, p.bv1, p.wv2, p.Hv, c * kUnits);
+      __syncthreads();
+    }
+#pragma unroll 2
+    for (int u = gg; u < kUnits; u += 8) {
+      float z = S.val.b1[u], Phi, gr;
 #pragma unroll
-    for (int d = 0; d < D; ++d) z = fmaf(pool[d], p.wv1[d * p.Hv + j], z);
-    V = fmaf(gelu_exact(z), p.wv2[j], V);
+      for (int d = 0; d < D; ++d) z = fmaf(pool[d], S.val.w1[d][u], z);
+      gelu_parts(z, Phi, gr);
+      V = fmaf(z * Phi, S.val.w2[u][0], V);
+    }
   }
+#pragma unroll
+  for (int a = 0; a < A; ++a) lg[a] = sum8(lg[a]) + p.bp2[a];
+  V = sum8(V) + p.bv2[0];
 
-  // loss terms and their gradient with respect to the logits and V
-  const float adv = (float)g.adv[ti], ret = (float)g.ret[ti];
+  // loss terms and their gradient with respect to the logits and V (every lane of the sample)
   float mx = lg[0];
 #pragma unroll
   for (int a = 1; a < A; ++a) mx = fmaxf(mx, lg[a]);
-  float S = 0.f;
+  float s = 0.f;
 #pragma unroll
-  for (int a = 0; a < A; ++a) S += expf(lg[a] - mx);
-  const float lS = logf(S);
-  float H = 0.f;
+  for (int a = 0; a < A; ++a) s += expf(lg[a] - mx);
+  const float lS = logf(s);
+  float pa[A], H = 0.f, l_act = lg[0];
 #pragma unroll
   for (int a = 0; a < A; ++a) {
     const float lp = (lg[a] - mx) - lS;
-    H -= expf(lp) * lp;
+    pa[a] = expf(lp);
+    H -= pa[a] * lp;
+    l_act = a == a_act ? lg[a] : l_act;
   }
-  float l_act = lg[0];
-#pragma unroll
-  for (int a = 1; a < A; ++a) l_act = a == a_act ? lg[a] : l_act;
   const float logp = (l_act - mx) - lS;
   const float invM = 1.0f / (float)g.M;
   float dlogp, pterm;
-  if (g.reinforce) {
-    dlogp = -adv * invM;
-    pterm = -adv * logp;
-  } else {
-    const float rho = expf(logp - g.logp_old[ti]);
-    const float lo = 1.0f - g.clip, hi = 1.0f + g.clip;
-    const float rc = fminf(fmaxf(rho, lo), hi);
-    const float s1 = rho * adv, s2 = rc * adv;
-    const float g_rho = s1 <= s2 ? adv : ((rho > lo && rho < hi) ? adv : 0.0f);
-    dlogp = -g_rho * rho * invM;
-    pterm = -fminf(s1, s2);
-  }
+  policy_term(g.reinforce, g.clip, logp, lold, adv, invM, dlogp, pterm);
   float dl[A];
 #pragma unroll
   for (int a = 0; a < A; ++a) {
     const float lp = (lg[a] - mx) - lS;
-    const float pa = expf(lp);
-    dl[a] = -dlogp * pa + g.c_h * invM * pa * (lp + H) + (a == a_act ? dlogp : 0.0f);
+    dl[a] = on ? -dlogp * pa[a] + g.c_h * invM * pa[a] * (lp + H) + (a == a_act ? dlogp : 0.0f)
+               : 0.f;
   }
-  const float dV = p.value_head ? 2.0f * g.c_v * (V - ret) * invM : 0.0f;
-  g.terms[m * 3] = (double)pterm;
-  g.terms[m * 3 + 1] = (double)(V - ret) * (double)(V - ret);
-  g.terms[m * 3 + 2] = (double)H;
+  const float dV = p.value_head && on ? 2.0f * g.c_v * (V - ret) * invM : 0.0f;
+  if (gg == 0) {
+#pragma unroll
+    for (int a = 0; a < A; ++a) S.dl[sl][a] = dl[a];
+    S.dV[sl] = dV;
+#pragma unroll
+    for (int d = 0; d < D; ++d) S.pool[sl][d] = pool[d];
+    S.terms[sl][0] = on ? (double)pterm : 0.0;
+    S.terms[sl][1] = on ? (double)(V - ret) * (double)(V - ret) : 0.0;
+    S.terms[sl][2] = on ? (double)H : 0.0;
+  }
 
-  // heads backward
+  // heads backward, a chunk at a time
   float dp[D] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int a = 0; a < A; ++a) put(9, a, dl[a]);
-  for (int j = 0; j < p.Hp; ++j) {
-    float z = p.bp1[j];
-#pragma unroll
-    for (int d = 0; d < D; ++d) z = fmaf(pool[d], p.wp1[d * p.Hp + j], z);
-    const float hj = gelu_exact(z);
-    float dh = 0.f;
-#pragma unroll
-    for (int a = 0; a < A; ++a) {
-      dh = fmaf(dl[a], p.wp2[(size_t)j * A + a], dh);
-      put(8, j * A + a, hj * dl[a]);
+  const int pu = tid & 63, pr = tid >> 6;   // the thread's unit and row in the parameter sums
+  for (int c = 0; c < npol; ++c) {
+    if (npol > 1) {
+      __syncthreads();
+      stage_head<A>(S.pol, p.wp1, p.bp1, p.wp2, p.Hp, c * kUnits);
+      __syncthreads();
     }
-    const float dz = dh * gelu_grad(z);
-    put(7, j, dz);
+#pragma unroll 2
+    for (int u = gg; u < kUnits; u += 8) {
+      float z = S.pol.b1[u], Phi, gr, dh = 0.f;
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      put(6, d * p.Hp + j, pool[d] * dz);
-      dp[d] = fmaf(dz, p.wp1[d * p.Hp + j], dp[d]);
+      for (int d = 0; d < D; ++d) z = fmaf(pool[d], S.pol.w1[d][u], z);
+      gelu_parts(z, Phi, gr);
+#pragma unroll
+      for (int a = 0; a < A; ++a) dh = fmaf(dl[a], S.pol.w2[u][a], dh);
+      const float dz = dh * gr;
+      S.h[sl][u] = z * Phi;
+      S.dz[sl][u] = dz;
+#pragma unroll
+      for (int d = 0; d < D; ++d) dp[d] = fmaf(dz, S.pol.w1[d][u], dp[d]);
     }
+    __syncthreads();
+    const int j = c * kUnits + pu;
+    float s1 = 0.f, sb = 0.f, s2[(A + 3) / 4];
+#pragma unroll
+    for (int i = 0; i < (A + 3) / 4; ++i) s2[i] = 0.f;
+#pragma unroll 4
+    for (int x = 0; x < kSamples; ++x) {
+      const float dz = S.dz[x][pu], hj = S.h[x][pu];
+      s1 = fmaf(S.pool[x][pr], dz, s1);
+      sb += dz;
+#pragma unroll
+      for (int i = 0; i < (A + 3) / 4; ++i)
+        if (pr + 4 * i < A) s2[i] = fmaf(hj, S.dl[x][pr + 4 * i], s2[i]);
+    }
+    if (j < p.Hp) {
+      part[g.off[6] + pr * p.Hp + j] = s1;
+      if (pr == 0) part[g.off[7] + j] = sb;
+#pragma unroll
+      for (int i = 0; i < (A + 3) / 4; ++i)
+        if (pr + 4 * i < A) part[g.off[8] + j * A + pr + 4 * i] = s2[i];
+    }
+    __syncthreads();
   }
-  put(13, 0, dV);
-  for (int j = 0; j < p.Hv; ++j) {
-    float z = p.bv1[j];
-#pragma unroll
-    for (int d = 0; d < D; ++d) z = fmaf(pool[d], p.wv1[d * p.Hv + j], z);
-    put(12, j, gelu_exact(z) * dV);
-    const float dz = dV * p.wv2[j] * gelu_grad(z);
-    put(11, j, dz);
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      put(10, d * p.Hv + j, pool[d] * dz);
-      dp[d] = fmaf(dz, p.wv1[d * p.Hv + j], dp[d]);
+  for (int c = 0; c < nval; ++c) {
+    if (nval > 1) {
+      stage_head<1>(S.val, p.wv1, p.bv1, p.wv2, p.Hv, c * kUnits);
+      __syncthreads();
     }
+#pragma unroll 2
+    for (int u = gg; u < kUnits; u += 8) {
+      float z = S.val.b1[u], Phi, gr;
+#pragma unroll
+      for (int d = 0; d < D; ++d) z = fmaf(pool[d], S.val.w1[d][u], z);
+      gelu_parts(z, Phi, gr);
+      const float dz = dV * S.val.w2[u][0] * gr;
+      S.h[sl][u] = z * Phi;
+      S.dz[sl][u] = dz;
+#pragma unroll
+      for (int d = 0; d < D; ++d) dp[d] = fmaf(dz, S.val.w1[d][u], dp[d]);
+    }
+    __syncthreads();
+    const int j = c * kUnits + pu;
+    float s1 = 0.f, sb = 0.f, s2 = 0.f;
+#pragma unroll 4
+    for (int x = 0; x < kSamples; ++x) {
+      const float dz = S.dz[x][pu];
+      s1 = fmaf(S.pool[x][pr], dz, s1);
+      sb += dz;
+      s2 = fmaf(S.h[x][pu], S.dV[x], s2);
+    }
+    if (j < p.Hv) {
+      part[g.off[10] + pr * p.Hv + j] = s1;
+      if (pr == 0) part[g.off[11] + j] = sb;
+      if (pr == 1) part[g.off[12] + j] = s2;
+    }
+    __syncthreads();
   }
+  // biases of the heads' outputs and the loss terms: sums over the samples in order
+  if (tid < A) {
+    float x = 0.f;
+    for (int i = 0; i < kSamples; ++i) x += S.dl[i][tid];
+    part[g.off[9] + tid] = x;
+  } else if (tid == 64) {
+    float x = 0.f;
+    for (int i = 0; i < kSamples; ++i) x += S.dV[i];
+    part[g.off[13]] = x;
+  } else if (tid >= 128 && tid < 131) {
+    double x = 0.0;
+    for (int i = 0; i < kSamples; ++i) x += S.terms[i][tid - 128];
+    g.terms[(size_t)blockIdx.x * 3 + tid - 128] = x;
+  }
+
   // output projection: dy = dp / L for every token
-  float dy[D], dO[D];
+  float dO[D];
 #pragma unroll
-  for (int d = 0; d < D; ++d) dy[d] = dp[d] * (1.0f / (float)L);
+  for (int d = 0; d < D; ++d) dp[d] = sum8(dp[d]);
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     float acc = 0.f;
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-      put(4, i * D + d, osum[i] * dy[d]);
-      acc = fmaf(dy[d], p.w_o[i * D + d], acc);
-    }
+    for (int d = 0; d < D; ++d) acc = fmaf(dp[d] * (1.0f / (float)L), p.w_o[i * D + d], acc);
     dO[i] = acc;
   }
-#pragma unroll
-  for (int d = 0; d < D; ++d) put(5, d, dp[d]);
-  // attention backward, head by head
-  float dq[L][D], dk[L][D], dv[L][D];
-#pragma unroll
-  for (int gg = 0; gg < L; ++gg)
-#pragma unroll
-    for (int d = 0; d < D; ++d) { dq[gg][d] = 0.f; dk[gg][d] = 0.f; dv[gg][d] = 0.f; }
+  // attention backward, head by head: the query's score gradients, then each key's and value's
+  // share of all queries'
+  float dq[D], dk[D], dv[D];
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
-    float da[L], colsum[L];
+    float sd = 0.f, da[L];
 #pragma unroll
     for (int j = 0; j < L; ++j) {
       float acc = 0.f;
 #pragma unroll
-      for (int tt = h * DH; tt < (h + 1) * DH; ++tt) acc = fmaf(dO[tt], v[j][tt], acc);
+      for (int x = 0; x < DH; ++x) acc = fmaf(dO[h * DH + x], X.kv[j][D + h * DH + x], acc);
       da[j] = acc;
-      colsum[j] = 0.f;
+      sd = fmaf(att[h][j], acc, sd);
+    }
+    float aq[DH];
+#pragma unroll
+    for (int x = 0; x < DH; ++x) aq[x] = 0.f;
+    wave_lds();   // the previous head's reads are done
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const float ds = att[h][j] * (da[j] - sd) * rs;   // zero in lanes without a token
+      X.a[gg][j] = att[h][j];
+      X.ds[gg][j] = ds;
+#pragma unroll
+      for (int x = 0; x < DH; ++x) aq[x] = fmaf(ds, X.kv[j][h * DH + x], aq[x]);
+    }
+    wave_lds();
+    float cs = 0.f, ak[DH];
+#pragma unroll
+    for (int x = 0; x < DH; ++x) ak[x] = 0.f;
+    const int me = tokn ? gg : 0;   // lanes without a token read column 0 and drop it
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const float ds = X.ds[j][me];
+      cs += X.a[j][me];
+#pragma unroll
+      for (int x = 0; x < DH; ++x) ak[x] = fmaf(ds, X.q[j][h * DH + x], ak[x]);
     }
 #pragma unroll
-    for (int gg = 0; gg < L; ++gg) {
-      float a[L];
-      weights(gg, h, a);
-      float sd = 0.f;
-#pragma unroll
-      for (int j = 0; j < L; ++j) {
-        sd = fmaf(a[j], da[j], sd);
-        colsum[j] += a[j];
-      }
-#pragma unroll
-      for (int j = 0; j < L; ++j) {
-        const float ds = a[j] * (da[j] - sd) * rs;
-#pragma unroll
-        for (int tt = h * DH; tt < (h + 1) * DH; ++tt) {
-          dq[gg][tt] = fmaf(ds, k[j][tt], dq[gg][tt]);
-          dk[j][tt] = fmaf(ds, q[gg][tt], dk[j][tt]);
-        }
-      }
+    for (int x = 0; x < DH; ++x) {
+      dq[h * DH + x] = aq[x];
+      dk[h * DH + x] = tokn ? ak[x] : 0.f;
+      dv[h * DH + x] = tokn ? cs * dO[h * DH + x] : 0.f;
     }
-#pragma unroll
-    for (int j = 0; j < L; ++j)
-#pragma unroll
-      for (int tt = h * DH; tt < (h + 1) * DH; ++tt) dv[j][tt] = colsum[j] * dO[tt];
   }
-  // q/k/v projection and the tokens
-  float de[L][D];
+  // q/k/v projection and the token. The attention's parameters (W_qkv [D][3D], b_qkv, W_o [D][D],
+  // b_o, b_in: entries 0 .. kEnt - 1) are summed over rows of 16 lanes, entry n kept by the
+  // row's lane n % 16, then over the workgroup's rows through LDS.
+  constexpr int kEnt = 84, kRows = kGradThr / 16;
+  float* ws = &S.h[0][0];   // [kRows][kEnt], free after the heads
+  static_assert(kRows * kEnt <= kSamples * kUStride, "room for the rows' sums");
+  float de[D];
 #pragma unroll
-  for (int gg = 0; gg < L; ++gg)
+  for (int i = 0; i < D; ++i) de[i] = 0.f;
+  float keep[(kEnt + 15) / 16];
 #pragma unroll
-    for (int i = 0; i < D; ++i) de[gg][i] = 0.f;
+  for (int i = 0; i < (kEnt + 15) / 16; ++i) keep[i] = 0.f;
+  auto entry = [&](int n, float v) {   // v: the lane's term of entry n
+    const float x = sum_pair(sum8(v));
+    keep[n >> 4] = (n & 15) == (lane & 15) ? x : keep[n >> 4];
+  };
 #pragma unroll
   for (int c = 0; c < 3 * D; ++c) {
-    float bsum = 0.f;
-    float col[L];
-#pragma unroll
-    for (int gg = 0; gg < L; ++gg) {
-      col[gg] = c < D ? dq[gg][c] : (c < 2 * D ? dk[gg][c - D] : dv[gg][c - 2 * D]);
-      bsum += col[gg];
-    }
-    put(3, c, bsum);
+    const float col = c < D ? dq[c % D] : c < 2 * D ? dk[c % D] : dv[c % D];
+    entry(4 * 3 * D + c, col);
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      float wsum = 0.f;
-#pragma unroll
-      for (int gg = 0; gg < L; ++gg) {
-        wsum = fmaf(tok[gg][i], col[gg], wsum);
-        de[gg][i] = fmaf(col[gg], p.w_qkv[i * 3 * D + c], de[gg][i]);
-      }
-      put(2, i * 3 * D + c, wsum);
+      entry(i * 3 * D + c, tok[i] * col);
+      de[i] = fmaf(col, p.w_qkv[i * 3 * D + c], de[i]);
     }
   }
+  const float own = gg == 0 ? 1.f : 0.f;   // per-sample terms, counted once
+#pragma unroll
+  for (int i = 0; i < D; ++i)
+#pragma unroll
+    for (int d = 0; d < D; ++d) entry(60 + i * D + d, own * (osum[i] * (dp[d] * (1.0f / (float)L))));
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    float bsum = 0.f;
-#pragma unroll
-    for (int gg = 0; gg < L; ++gg) bsum += de[gg][d];
-    put(1, d, bsum);
+    entry(76 + d, own * dp[d]);
+    entry(80 + d, tokn ? de[d] : 0.f);
   }
+  const int row = tid >> 4;
 #pragma unroll
-  for (int gg = 0; gg < L; ++gg)
-    for (int i = gg * G; i < (gg + 1) * G; ++i) {
-      const float x = xo[(size_t)i * E];
+  for (int i = 0; i < (kEnt + 15) / 16; ++i) {
+    const int n = i * 16 + (lane & 15);
+    if (n < kEnt) ws[row * kEnt + n] = keep[i];
+  }
+  __syncthreads();
+  if (tid < kEnt) {
+    float x = ws[tid];
 #pragma unroll
-      for (int d = 0; d < D; ++d) put(0, i * D + d, x * de[gg][d]);
+    for (int r = 1; r < kRows; ++r) x += ws[r * kEnt + tid];
+    const int n = tid;
+    const int o = n < 48 ? g.off[2] + n : n < 60 ? g.off[3] + n - 48 : n < 76 ? g.off[4] + n - 60
+                : n < 80 ? g.off[5] + n - 76 : g.off[1] + n - 80;
+    part[o] = x;
+  }
+  // W_in: feature gg G + r of the lane's token, summed over the samples the same way
+  for (int r = 0; r < G; ++r) {
+    const float x = tokn && on ? xo[(size_t)(gg * G + r) * E] : 0.f;
+    __syncthreads();   // the previous sums are read
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const float y = sum_pair(x * de[d]);
+      if ((lane & 8) == 0) ws[(row * 8 + gg) * D + d] = y;
     }
+    __syncthreads();
+    if (tid < 8 * D && tid / D < L) {
+      float y = ws[tid];
+#pragma unroll
+      for (int w = 1; w < kRows; ++w) y += ws[w * 8 * D + tid];
+      part[g.off[0] + ((tid / D) * G + r) * D + tid % D] = y;
+    }
+  }
 }
 
-// grads[i] = sum over m of gs[i][m]: each of 256 threads sums a strided slice in order, then
-// a fixed tree
-__global__ __launch_bounds__(256) void attn_gsum_k(const float* __restrict__ gs, int M,
-                                                   float* __restrict__ grads) {
-  __shared__ float part[256];
-  const float* row = gs + (size_t)blockIdx.x * M;
-  float s = 0.f;
-  for (int m = threadIdx.x; m < M; m += 256) s += row[m];
-  part[threadIdx.x] = s;
+// The workgroups' partial sums and loss terms added in a fixed order: kFinCols parameters per
+// workgroup, part t of them adding rows t, t + kFinParts, ... in order, then the parts in order; the last
+// workgroup the loss terms.
+struct AttnFinArgs {
+  const float* part;
+  const double* terms;
+  int nwg, P, M;
+  float c_v, c_h;
+  float* grads;
+  double* loss;
+  AdamStep adam;   // p NULL: the gradient is written
+};
+constexpr int kFinThr = 256, kFinCols = 16, kFinParts = kFinThr / kFinCols;
+__global__ __launch_bounds__(kFinThr) void attn_finish_k(AttnFinArgs a) {
+  const int tid = threadIdx.x;
+  if (blockIdx.x < gridDim.x - 1) {
+    __shared__ float part[kFinParts][kFinCols + 1];
+    const int i = blockIdx.x * kFinCols + tid % kFinCols, t = tid / kFinCols;
+    float s = 0.f;
+    if (i < a.P) {
+#pragma unroll 8
+      for (int w = t; w < a.nwg; w += kFinParts) s += a.part[(size_t)w * a.P + i];
+    }
+    part[t][tid % kFinCols] = s;
+    __syncthreads();
+    if (t == 0 && i < a.P) {
+#pragma unroll
+      for (int w = 1; w < kFinParts; ++w) s += part[w][tid];
+      finish_param(a.adam, a.grads, (size_t)i, s);
+    }
+    return;
+  }
+  __shared__ double dp[3][kFinThr];
+  for (int c = 0; c < 3; ++c) {
+    double s = 0.0;
+    for (int w = tid; w < a.nwg; w += kFinThr) s += a.terms[(size_t)w * 3 + c];
+    dp[c][tid] = s;
+  }
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+  for (int w = kFinThr / 2; w > 0; w >>= 1) {
+    if (tid < w)
+      for (int c = 0; c < 3; ++c) dp[c][tid] += dp[c][tid + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) grads[blockIdx.x] = part[0];
+  if (tid == 0) {
+    const double pi = dp[0][0] / a.M, v = a.c_v * dp[1][0] / a.M, h = -a.c_h * dp[2][0] / a.M;
+    a.loss[0] = pi + v + h;
+    a.loss[1] = pi;
+    a.loss[2] = v;
+    a.loss[3] = h;
+  }
 }
 
 template <int L, int NH, int A>
 hipError_t run_grad(const AttnGradArgs& g, hipStream_t st) {
-  hipLaunchKernelGGL((attn_grad_k<L, NH, A>), dim3((unsigned)((g.M + 63) / 64)), dim3(64), 0, st, g);
+  hipLaunchKernelGGL((attn_grad_k<L, NH, A>), dim3((unsigned)((g.M + kSamples - 1) / kSamples)), dim3(kGradThr), 0, st, g);
   return hipGetLastError();
 }
 template <int L, int NH>
@@ -602,16 +809,18 @@ size_t attn_grad_scratch_bytes(const AttnParams& p, int M) {
 hipError_t launch_attn_grad(const AttnParams& p, int T, const float* obs, const uint8_t* act,
                             const float* logp_old, const double* adv, const double* ret, int M,
                             uint64_t seed, float clip, float c_v, float c_h, int reinforce,
-                            void* scratch, double* loss_out, float* grads, int64_t* idx_out,
-                            uint32_t* err, hipStream_t st) {
+                            void* scratch, double* loss_out, float* grads, const AdamStep* adam,
+                            int64_t* idx_out, uint32_t* err, hipStream_t st) {
   if (!attn_shape_supported(p) || M < 1) return hipErrorInvalidValue;
   AttnGradArgs g;
   g.p = p; g.T = T; g.M = M; g.reinforce = reinforce;
   g.obs = obs; g.act = act; g.logp_old = logp_old; g.adv = adv; g.ret = ret;
   g.seed = seed; g.clip = clip; g.c_v = c_v; g.c_h = c_h;
   g.P = attn_param_count(p, g.off);
-  g.gs = static_cast<float*>(scratch);
-  g.terms = reinterpret_cast<double*>(g.gs + (size_t)g.P * M);
+  // the loss terms (8-byte aligned at the start), then the partial sums
+  const int nwg = (M + kSamples - 1) / kSamples;
+  g.terms = static_cast<double*>(scratch);
+  g.part = reinterpret_cast<float*>(g.terms + (size_t)nwg * 3);
   g.idx_out = idx_out; g.err = err;
   hipError_t e;
   switch (p.L) {
@@ -622,10 +831,11 @@ hipError_t launch_attn_grad(const AttnParams& p, int T, const float* obs, const 
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(attn_gsum_k, dim3((unsigned)g.P), dim3(256), 0, st, g.gs, M, grads);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_pg_loss(g.terms, M, c_v, c_h, loss_out, st);
+  AttnFinArgs f{g.part, g.terms, nwg, g.P, M, c_v, c_h, grads, loss_out,
+                adam ? *adam : AdamStep{}};
+  hipLaunchKernelGGL(attn_finish_k, dim3((unsigned)((g.P + kFinCols - 1) / kFinCols + 1)),
+                     dim3(kFinThr), 0, st, f);
+  return hipGetLastError();
 }
 
 bool attn_shape_supported(const AttnParams& p) {

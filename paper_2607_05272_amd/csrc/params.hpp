@@ -129,6 +129,25 @@ hipError_t launch_rollout_fused(const SimParams& p, const EnvState& s, const Mlp
                                 uint32_t k0, int T, const RolloutOut& o, hipStream_t st);
 bool policy_shape_supported(const MlpParams& m);
 
+// One Adam step taken by the launch that finishes a gradient, instead of writing it: the fp32
+// parameters and moments in gradient order, and the policy's weights rewritten from them
+// (segment k of len parameters from poff at byte woff of w, matrices rounded to bf16 if bf16).
+constexpr int kMaxSegs = 14;
+struct Segs {
+  int n;                   // segments in use (6 for the MLP, 14 for the attention policy)
+  size_t poff[kMaxSegs];   // offset in the parameter vector
+  size_t woff[kMaxSegs];   // byte offset in the weight buffer
+  size_t len[kMaxSegs];
+  int matrix[kMaxSegs];
+};
+struct AdamStep {
+  float *p, *m, *v;
+  unsigned char* w;
+  float lr, b1, b2, eps, bc1, bc2;   // bc: the bias corrections 1 - b^t
+  int bf16;
+  Segs seg;
+};
+
 // The attention policy (attn_kernels.hip): fp32 weights [in][out] inside the caller's
 // buffer; D = 4 embedding, NH heads, L tokens over F features, heads of Hp and Hv units.
 struct AttnParams {
@@ -136,6 +155,8 @@ struct AttnParams {
   const float *w_in, *b_in, *w_qkv, *b_qkv, *w_o, *b_o;
   const float *wp1, *bp1, *wp2, *bp2, *wv1, *bv1, *wv2, *bv2;
 };
+Segs mlp_segments(const MlpParams& m, const size_t off[6]);
+Segs attn_segments(const AttnParams& p, const size_t off[14]);
 bool attn_shape_supported(const AttnParams& p);
 hipError_t launch_attn_policy(const AttnParams& p, const float* obs, const uint64_t* seed,
                               uint32_t step,
@@ -150,8 +171,8 @@ size_t attn_grad_scratch_bytes(const AttnParams& p, int M);
 hipError_t launch_attn_grad(const AttnParams& p, int T, const float* obs, const uint8_t* act,
                             const float* logp_old, const double* adv, const double* ret, int M,
                             uint64_t seed, float clip, float c_v, float c_h, int reinforce,
-                            void* scratch, double* loss_out, float* grads, int64_t* idx_out,
-                            uint32_t* err, hipStream_t st);
+                            void* scratch, double* loss_out, float* grads, const AdamStep* adam,
+                            int64_t* idx_out, uint32_t* err, hipStream_t st);
 // the attention policy's weights from / to fp32 parameters in gradient order (plain copies)
 hipError_t launch_export_attn(const AttnParams& p, const float* params, void* d_weights,
                               const size_t off[14], hipStream_t st);
@@ -161,20 +182,19 @@ hipError_t launch_import_attn(const AttnParams& p, const void* d_weights, const 
 enum { PRIM_PHILOX = 0, PRIM_LOG = 1, PRIM_EXP = 2, PRIM_COS = 3, PRIM_SQRT = 4, PRIM_DIV = 5 };
 hipError_t launch_primitive(int kind, int64_t n, uint64_t key, const void* in, void* out,
                             hipStream_t st);
-// the four loss terms from per-sample [M][3] fp64 terms, summed in a fixed order
-hipError_t launch_pg_loss(const double* terms, int M, float c_v, float c_h, double* out,
-                          hipStream_t st);
 // Xavier init of the attention policy's seven matrices (layers 0..6) and zero biases;
 // off[14] are the byte offsets of w_in, b_in, ..., wv2, bv2; fin/fout the matrix shapes
 hipError_t launch_init_attn(uint64_t seed, void* d_weights, const size_t off[14], const int fin[7],
                             const int fout[7], hipStream_t st);
 // MLP policy-gradient minibatch (ppo_kernels.hip), value head required: the library's own MFMA
-// products with fused epilogues; scratch holds ppo_scratch_bytes(m, M) bytes.
+// products with fused epilogues; scratch holds ppo_scratch_bytes(m, M) bytes. adam != NULL (here
+// and for the attention policy) takes an Adam step with the gradient; grads is then scratch.
 hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t off[6], int T,
                       const float* obs, const uint8_t* act, const float* logp_old,
                       const double* adv, const double* ret, int M, uint64_t seed, float clip,
                       float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
-                      float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st);
+                      float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
+                      hipStream_t st);
 bool ppo_shape_supported(const MlpParams& m);
 // The same in four launches for the rollout policies' networks (ppo_fused.hip), in a scratch of
 // ppo_scratch_bytes: whether it takes this network and minibatch, and its launch.
@@ -183,7 +203,8 @@ hipError_t launch_pg_fused(const MlpParams& m, const void* d_weights, const size
                            const float* obs, const uint8_t* act, const float* logp_old,
                            const double* adv, const double* ret, int M, uint64_t seed, float clip,
                            float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
-                           float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st);
+                           float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
+                           hipStream_t st);
 size_t ppo_scratch_bytes(const MlpParams& m, int M);
 // The fixed device scratch of ppo_minibatch_grad_noalloc: its size, and its address on the
 // current device (looked up once per device with hipGetSymbolAddress; allocates nothing).

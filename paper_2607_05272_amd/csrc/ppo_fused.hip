@@ -5,12 +5,15 @@
 //   mlp      per workgroup of 16 RT samples: forward, loss and backward through every layer
 //            with the activations in LDS and GELU'(z) in registers
 //   wgrad    G_l = A_{l-1}^T dZ_l over chunks of the samples
-//   finish   the chunks', the bias gradients' and the loss terms' sums in a fixed order
+//   finish   the chunks', the bias gradients' and the loss terms' sums in a fixed order, and in
+//            an update Adam's step with the weights' rewrite (302 us per 8 minibatches of 4096 of
+//            the 32-256-256-25 network with launches of their own, 269 us so)
 // Nothing but the operands of the weight products passes between the launches through memory;
 // with a launch per layer and elementwise step (ppo_kernels.hip) a minibatch of 8192 samples of
 // the 64-256-256-49 network took 124 us, here 45; 16384 of the 96-512-512-97 one 475 and 156 us.
 // Per sample both forms compute the same bits up to GELU'; the sums over samples differ in order.
 #include "ppo_dev.hpp"
+#include "train_dev.hpp"
 
 namespace bsim {
 namespace {
@@ -651,6 +654,7 @@ struct FinArgs {
   float c_v, c_h;
   double* loss;         // total, policy, value, entropy
   float* grads;
+  AdamStep adam;        // p NULL: the gradient is written
 };
 constexpr int kFinThr = 256, kColUnits = 16, kColParts = kFinThr / kColUnits;
 __global__ __launch_bounds__(kFinThr) void pg_finish_k(FinArgs a) {
@@ -665,7 +669,7 @@ __global__ __launch_bounds__(kFinThr) void pg_finish_k(FinArgs a) {
     float s = 0.f;
 #pragma unroll 8
     for (int z = 0; z < a.S; ++z) s += p[z * st];
-    a.grads[d.goff + e] = s;
+    finish_param(a.adam, a.grads, (size_t)(d.goff + e), s);
     return;
   }
   if (b < (int)gridDim.x - 1) {
@@ -683,13 +687,9 @@ __global__ __launch_bounds__(kFinThr) void pg_finish_k(FinArgs a) {
     if (t == 0 && u < a.width) {
 #pragma unroll
       for (int i = 1; i < kColParts; ++i) s += part[i][tid];
-      if (u < a.AK) {
-        if (u < a.Ap) a.grads[a.boff[0] + u] = s;
-      } else if (u < a.AK + a.H2) {
-        a.grads[a.boff[1] + u - a.AK] = s;
-      } else {
-        a.grads[a.boff[2] + u - a.AK - a.H2] = s;
-      }
+      const int k = u < a.AK ? 0 : u < a.AK + a.H2 ? 1 : 2;
+      const int i = k == 0 ? u : k == 1 ? u - a.AK : u - a.AK - a.H2;
+      if (k > 0 || i < a.Ap) finish_param(a.adam, a.grads, (size_t)(a.boff[k] + i), s);
     }
     return;
   }
@@ -823,8 +823,8 @@ template <class N>
 hipError_t run(const MlpParams& m, const void* d_weights, const size_t off[6], int T,
                const float* obs, const uint8_t* act, const float* logp_old, const double* adv,
                const double* ret, int M, uint64_t seed, float clip, float c_v, float c_h,
-               int reinforce, void* scratch, double* loss_out, float* grads, int64_t* idx_out,
-               uint32_t* err, hipStream_t st) {
+               int reinforce, void* scratch, double* loss_out, float* grads, const AdamStep* adam,
+               int64_t* idx_out, uint32_t* err, hipStream_t st) {
   typedef typename N::Mode Md;
   typedef typename Md::T TT;
   const Plan p = plan_of(m, M);
@@ -901,6 +901,7 @@ hipError_t run(const MlpParams& m, const void* d_weights, const size_t off[6], i
   f.col = a.col; f.nwg = p.nwg; f.width = p.AK + p.H2 + p.H1; f.AK = p.AK; f.H2 = p.H2; f.Ap = m.Ap;
   f.boff[0] = gb3; f.boff[1] = gb2; f.boff[2] = gb1;
   f.terms = a.terms; f.M = M; f.c_v = c_v; f.c_h = c_h; f.loss = loss_out; f.grads = grads;
+  f.adam = adam ? *adam : AdamStep{};
   const int ncol = (f.width + kColUnits - 1) / kColUnits;
   hipLaunchKernelGGL(pg_finish_k, dim3(f.nred + ncol + 1), dim3(kFinThr), 0, st, f);
   return hipGetLastError();
@@ -917,10 +918,11 @@ hipError_t launch_pg_fused(const MlpParams& m, const void* d_weights, const size
                            const float* obs, const uint8_t* act, const float* logp_old,
                            const double* adv, const double* ret, int M, uint64_t seed, float clip,
                            float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
-                           float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st) {
+                           float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
+                           hipStream_t st) {
   return with_net(m, [&](auto n) -> hipError_t {
     return run<decltype(n)>(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed, clip, c_v,
-                            c_h, reinforce, scratch, loss_out, grads, idx_out, err, st);
+                            c_h, reinforce, scratch, loss_out, grads, adam, idx_out, err, st);
   });
 }
 

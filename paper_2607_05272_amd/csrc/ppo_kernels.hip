@@ -561,40 +561,6 @@ __global__ __launch_bounds__(kThr) void mb_finish_k(RedDesc<Md> r0, RedDesc<Md> 
   if (threadIdx.x == 0) c.out[r] = part[0];
 }
 
-// loss terms summed in a fixed order by one workgroup: each thread adds a contiguous run of
-// samples in order, then a pairwise tree combines the threads' partial sums
-constexpr int kSumThr = 1024;
-__global__ __launch_bounds__(kSumThr) void ppo_loss_k(const double* terms, int M, float c_v,
-                                                      float c_h, double* out) {
-  __shared__ double part[3][kSumThr];
-  const int per = (M + kSumThr - 1) / kSumThr;
-  const int m0 = threadIdx.x * per;
-  const int m1 = m0 + per < M ? m0 + per : M;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-#pragma unroll 4
-  for (int m = m0; m < m1; ++m) {
-    s0 += terms[(size_t)m * 3];
-    s1 += terms[(size_t)m * 3 + 1];
-    s2 += terms[(size_t)m * 3 + 2];
-  }
-  part[0][threadIdx.x] = s0;
-  part[1][threadIdx.x] = s1;
-  part[2][threadIdx.x] = s2;
-  __syncthreads();
-  for (int w = kSumThr / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int c = 0; c < 3; ++c) part[c][threadIdx.x] += part[c][threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double pi = part[0][0] / M, v = c_v * part[1][0] / M, h = -c_h * part[2][0] / M;
-    out[0] = pi + v + h;
-    out[1] = pi;
-    out[2] = v;
-    out[3] = h;
-  }
-}
-
 int pad64(int x) { return (x + 63) & ~63; }
 
 // split of a sample reduction of length Mp into chunks (multiples of 32) for about `target`
@@ -834,23 +800,24 @@ hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t of
                       const float* obs, const uint8_t* act, const float* logp_old,
                       const double* adv, const double* ret, int M, uint64_t seed, float clip,
                       float c_v, float c_h, int reinforce, void* scratch, double* loss_out,
-                      float* grads, int64_t* idx_out, uint32_t* err, hipStream_t st) {
+                      float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
+                      hipStream_t st) {
   if (M < 1 || !ppo_shape_supported(m)) return hipErrorInvalidValue;
   if (pg_fused_supported(m, M, ppo_scratch_bytes(m, M)))
     return launch_pg_fused(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed, clip, c_v,
-                           c_h, reinforce, scratch, loss_out, grads, idx_out, err, st);
-  if (m.bf16)
-    return run_minibatch<Bf16Mode>(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed,
-                                   clip, c_v, c_h, reinforce, scratch, loss_out, grads, idx_out,
-                                   err, st);
-  return run_minibatch<F32Mode>(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed, clip,
-                                c_v, c_h, reinforce, scratch, loss_out, grads, idx_out, err, st);
-}
-
-hipError_t launch_pg_loss(const double* terms, int M, float c_v, float c_h, double* out,
-                          hipStream_t st) {
-  hipLaunchKernelGGL(ppo_loss_k, dim3(1), dim3(kSumThr), 0, st, terms, M, c_v, c_h, out);
-  return hipGetLastError();
+                           c_h, reinforce, scratch, loss_out, grads, adam, idx_out, err, st);
+  const hipError_t e =
+      m.bf16 ? run_minibatch<Bf16Mode>(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed,
+                                       clip, c_v, c_h, reinforce, scratch, loss_out, grads, idx_out,
+                                       err, st)
+             : run_minibatch<F32Mode>(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed,
+                                      clip, c_v, c_h, reinforce, scratch, loss_out, grads, idx_out,
+                                      err, st);
+  if (e != hipSuccess || !adam) return e;
+  const hipError_t e2 =
+      launch_adam(adam->p, grads, adam->m, adam->v, adam->seg.poff[5] + adam->seg.len[5], adam->lr,
+                  adam->b1, adam->b2, adam->eps, adam->bc1, adam->bc2, st);
+  return e2 != hipSuccess ? e2 : launch_export_weights(m, adam->p, adam->w, off, st);
 }
 
 }  // namespace bsim

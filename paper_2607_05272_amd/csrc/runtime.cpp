@@ -882,7 +882,7 @@ static int pg_grad(sim_ctx* x, int reinforce, const void* d_weights, int32_t T, 
                    const uint8_t* d_actions, const float* d_logp_old, const double* d_adv,
                    const double* d_ret, int32_t M, uint64_t seed, float clip, float c_value,
                    float c_entropy, float* d_grads, double* d_loss, int64_t* d_index,
-                   bool no_alloc = false) {
+                   bool no_alloc = false, const AdamStep* adam = nullptr) {
   const char* who = reinforce ? "reinforce_minibatch_grad"
                               : (no_alloc ? "ppo_minibatch_grad_noalloc" : "ppo_minibatch_grad");
   if (!x || !d_weights || !d_obs || !d_actions || (!reinforce && !d_logp_old) || !d_adv ||
@@ -903,7 +903,7 @@ static int pg_grad(sim_ctx* x, int reinforce, const void* d_weights, int32_t T, 
     if (rc) return rc;
     auto launch = [&] {
       return launch_attn_grad(x->a, T, d_obs, d_actions, d_logp_old, d_adv, d_ret, M, seed, clip,
-                              c_value, c_entropy, reinforce, scr, d_loss, d_grads, d_index,
+                              c_value, c_entropy, reinforce, scr, d_loss, d_grads, adam, d_index,
                               x->s.err, x->stream);
     };
     HIPCHK(no_alloc ? launch() : x->timed(SIM_KC_PPO, launch),
@@ -923,8 +923,8 @@ static int pg_grad(sim_ctx* x, int reinforce, const void* d_weights, int32_t T, 
   offsets(x->cfg, off);
   auto launch = [&] {
     return launch_ppo(x->m, d_weights, off, T, d_obs, d_actions, d_logp_old, d_adv, d_ret, M, seed,
-                      clip, c_value, c_entropy, reinforce, scr, d_loss, d_grads, d_index, x->s.err,
-                      x->stream);
+                      clip, c_value, c_entropy, reinforce, scr, d_loss, d_grads, adam, d_index,
+                      x->s.err, x->stream);
   };
   HIPCHK(no_alloc ? launch() : x->timed(SIM_KC_PPO, launch), "minibatch gradient kernel launch");
   return SIM_OK;
@@ -973,16 +973,25 @@ int sim_params_from_weights(sim_ctx* x, const void* d_weights, float* d_params) 
   return SIM_OK;
 }
 
-int adam_update(sim_ctx* x, float* d_params, const float* d_grads, float* d_m, float* d_v,
-                int32_t step, float lr, float beta1, float beta2, float eps, void* d_weights) {
-  if (!x || !d_params || !d_grads || !d_m || !d_v) return fail(SIM_EINVAL, "NULL argument");
+static int adam_args(int32_t step, float beta1, float beta2, float eps) {
   if (step < 1) return fail(SIM_EINVAL, "step = %d must be >= 1", step);
   if (!(beta1 >= 0.0f && beta1 < 1.0f && beta2 >= 0.0f && beta2 < 1.0f && eps > 0.0f))
     return fail(SIM_EINVAL, "need 0 <= beta1, beta2 < 1 and eps > 0");
+  return SIM_OK;
+}
+
+static float bias_correction(float beta, int32_t step) {
+  return (float)(1.0 - std::pow((double)beta, (double)step));
+}
+
+int adam_update(sim_ctx* x, float* d_params, const float* d_grads, float* d_m, float* d_v,
+                int32_t step, float lr, float beta1, float beta2, float eps, void* d_weights) {
+  if (!x || !d_params || !d_grads || !d_m || !d_v) return fail(SIM_EINVAL, "NULL argument");
+  int rc = adam_args(step, beta1, beta2, eps);
+  if (rc) return rc;
   int64_t n = 0;
   sim_ppo_grad_count(&x->cfg, &n);
-  const float bc1 = (float)(1.0 - std::pow((double)beta1, (double)step));
-  const float bc2 = (float)(1.0 - std::pow((double)beta2, (double)step));
+  const float bc1 = bias_correction(beta1, step), bc2 = bias_correction(beta2, step);
   HIPCHK(x->timed(SIM_KC_PPO, [&] {
            return launch_adam(d_params, d_grads, d_m, d_v, (size_t)n, lr, beta1, beta2, eps, bc1,
                               bc2, x->stream);
@@ -1020,19 +1029,34 @@ int sim_update(sim_ctx* x, const sim_update_cfg* u, void* d_weights, float* d_pa
   }
   float* g = static_cast<float*>(x->grads);
   double* scratch_loss = reinterpret_cast<double*>(g + n + (n & 1));
+  // the Adam step runs in the launch that finishes each gradient
+  AdamStep ad{d_params, d_m, d_v, static_cast<unsigned char*>(d_weights), u->lr, u->beta1,
+              u->beta2, u->eps, 0.0f, 0.0f, x->m.bf16, {}};
+  if (x->cfg.policy_kind == SIM_POLICY_ATTN) {
+    size_t off[14];
+    attn_offsets(x->cfg, off);
+    ad.seg = attn_segments(x->a, off);
+    ad.bf16 = 0;
+  } else {
+    size_t off[6];
+    offsets(x->cfg, off);
+    ad.seg = mlp_segments(x->m, off);
+  }
   for (int e = 0; e < u->epochs; ++e) {
     for (int b = 0; b < u->minibatches; ++b) {
       const uint64_t k = (uint64_t)e * (uint64_t)u->minibatches + (uint64_t)b;
       const uint64_t seed = u->seed + k * 0x9E3779B97F4A7C15ull;
       double* loss = d_losses ? d_losses + 4 * k : scratch_loss;
-      int rc = pg_grad(x, u->algo == SIM_ALGO_REINFORCE, d_weights, T, d_obs, d_actions,
-                       d_logp_old, d_adv, d_ret, u->M, seed, u->clip, u->c_value, u->c_entropy,
-                       g, loss, nullptr);
+      const int32_t step = *h_step + 1;
+      int rc = adam_args(step, u->beta1, u->beta2, u->eps);
       if (rc) return rc;
-      rc = adam_update(x, d_params, g, d_m, d_v, *h_step + 1, u->lr, u->beta1, u->beta2, u->eps,
-                       d_weights);
+      ad.bc1 = bias_correction(u->beta1, step);
+      ad.bc2 = bias_correction(u->beta2, step);
+      rc = pg_grad(x, u->algo == SIM_ALGO_REINFORCE, d_weights, T, d_obs, d_actions, d_logp_old,
+                   d_adv, d_ret, u->M, seed, u->clip, u->c_value, u->c_entropy, g, loss, nullptr,
+                   false, &ad);
       if (rc) return rc;
-      *h_step += 1;
+      *h_step = step;
     }
   }
   return SIM_OK;

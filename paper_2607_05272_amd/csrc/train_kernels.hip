@@ -6,8 +6,7 @@
 // W3 [H2][A'], b3 [A'] back to back (fp32). The policy's weights are the ABI buffer (matrices
 // in the element type, bf16 by round-to-nearest-even or fp32; biases fp32; each block at its
 // layout offset).
-#include "devmath.hpp"
-#include "params.hpp"
+#include "train_dev.hpp"
 
 namespace bsim {
 namespace {
@@ -18,43 +17,20 @@ __global__ __launch_bounds__(256) void adam_k(float* __restrict__ p, const float
                                               float bc2) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (size_t)gridDim.x * blockDim.x) {
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * (gi * gi);
+    float mi = m[i], vi = v[i];
+    p[i] = adam_param(p[i], g[i], mi, vi, lr, b1, b2, eps, bc1, bc2);
     m[i] = mi;
     v[i] = vi;
-    const float mhat = mi / bc1, vhat = vi / bc2;
-    p[i] = p[i] - lr * mhat / (sqrtf(vhat) + eps);
   }
 }
 
-constexpr int kMaxSegs = 14;
-struct Segs {
-  int n;                   // segments in use (6 for the MLP, 14 for the attention policy)
-  size_t poff[kMaxSegs];   // offset in the parameter vector
-  size_t woff[kMaxSegs];   // byte offset in the weight buffer
-  size_t len[kMaxSegs];
-  int matrix[kMaxSegs];
-};
-
-// one thread per parameter; seg found by a short scan of the segment starts
-__device__ __forceinline__ int seg_of(const Segs& s, size_t i) {
-  int k = 0;
-#pragma unroll
-  for (int j = 1; j < kMaxSegs; ++j)
-    if (j < s.n && i >= s.poff[j]) k = j;
-  return k;
-}
-
+// one thread per parameter
 __global__ __launch_bounds__(256) void export_k(Segs s, size_t n, int bf16,
                                                 const float* __restrict__ p,
                                                 unsigned char* __restrict__ w) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const int k = seg_of(s, i);
-  const size_t j = i - s.poff[k];
-  if (s.matrix[k] && bf16) reinterpret_cast<uint16_t*>(w + s.woff[k])[j] = bf16_bits(p[i]);
-  else reinterpret_cast<float*>(w + s.woff[k])[j] = p[i];
+  export_param(s, bf16, w, i, p[i]);
 }
 
 __global__ __launch_bounds__(256) void import_k(Segs s, size_t n, int bf16,
@@ -68,7 +44,11 @@ __global__ __launch_bounds__(256) void import_k(Segs s, size_t n, int bf16,
   else p[i] = reinterpret_cast<const float*>(w + s.woff[k])[j];
 }
 
-Segs segments(const MlpParams& m, const size_t off[6]) {
+size_t total(const Segs& s) { return s.poff[s.n - 1] + s.len[s.n - 1]; }
+
+}  // namespace
+
+Segs mlp_segments(const MlpParams& m, const size_t off[6]) {
   Segs s;
   s.n = 6;
   const size_t len[6] = {(size_t)m.F * m.H1, (size_t)m.H1, (size_t)m.H1 * m.H2, (size_t)m.H2,
@@ -99,10 +79,6 @@ Segs attn_segments(const AttnParams& p, const size_t off[14]) {
   return s;
 }
 
-size_t total(const Segs& s) { return s.poff[s.n - 1] + s.len[s.n - 1]; }
-
-}  // namespace
-
 hipError_t launch_adam(float* params, const float* grads, float* m, float* v, size_t n, float lr,
                        float b1, float b2, float eps, float bc1, float bc2, hipStream_t st) {
   const unsigned blocks = (unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
@@ -113,7 +89,7 @@ hipError_t launch_adam(float* params, const float* grads, float* m, float* v, si
 
 hipError_t launch_export_weights(const MlpParams& m, const float* params, void* d_weights,
                                  const size_t off[6], hipStream_t st) {
-  const Segs s = segments(m, off);
+  const Segs s = mlp_segments(m, off);
   const size_t n = total(s);
   hipLaunchKernelGGL(export_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, s, n, m.bf16,
                      params, static_cast<unsigned char*>(d_weights));
@@ -140,7 +116,7 @@ hipError_t launch_import_attn(const AttnParams& p, const void* d_weights, const 
 
 hipError_t launch_import_weights(const MlpParams& m, const void* d_weights, const size_t off[6],
                                  float* params, hipStream_t st) {
-  const Segs s = segments(m, off);
+  const Segs s = mlp_segments(m, off);
   const size_t n = total(s);
   hipLaunchKernelGGL(import_k, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, s, n, m.bf16,
                      static_cast<const unsigned char*>(d_weights), params);
