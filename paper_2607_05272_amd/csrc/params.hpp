@@ -119,14 +119,22 @@ struct RolloutOut {
   uint64_t* rchk;
   float* obs;
 };
-// the number of environments whose workgroups of the fused rollout kernel are all resident on
-// the current device at once (0 with hipErrorNotSupported: no fused kernel for the network)
-hipError_t fused_rollout_capacity(const SimParams& p, const MlpParams& m, int* max_envs);
+// The fused rollout's form for a configuration: which kernel, and the number of environments
+// whose workgroups of it are resident on the current device at once (0: the network has none).
+struct FusedPlan {
+  int form, cap;
+};
+constexpr int kWideForms = 100;   // forms from here on are rollout_wide.hip's
+hipError_t fused_rollout_plan(const SimParams& p, const MlpParams& m, FusedPlan* plan);
+hipError_t fused_rollout_plan_wide(const SimParams& p, const MlpParams& m, FusedPlan* plan);
 // T ticks from k0 of the learned system with its MLP policy in one launch (the static shadow
-// system is not part of it); a bf16 policy needs s.obs_bf packed from s.obs beforehand.
-// hipErrorNotSupported for other policy shapes.
+// system is not part of it).
 hipError_t launch_rollout_fused(const SimParams& p, const EnvState& s, const MlpParams& m,
-                                uint32_t k0, int T, const RolloutOut& o, hipStream_t st);
+                                const FusedPlan& plan, uint32_t k0, int T, const RolloutOut& o,
+                                hipStream_t st);
+hipError_t launch_rollout_wide(const SimParams& p, const EnvState& s, const MlpParams& m,
+                               const FusedPlan& plan, uint32_t k0, int T, const RolloutOut& o,
+                               hipStream_t st);
 bool policy_shape_supported(const MlpParams& m);
 
 // One Adam step taken by the launch that finishes a gradient, instead of writing it: the fp32

@@ -189,19 +189,21 @@ __device__ __forceinline__ float action_uniform(uint64_t seed, uint32_t env, uin
 // us: the rows' uniforms, drawn beforehand (one lane per row), or NULL to draw them here (every
 // lane of a row's group then computes the same block).
 // AC: the action count when the padded width fixes it (0: m.A at run time); with it the
-// slices' bounds are compile-time and the per-logit guards vanish.
+// slices' bounds are compile-time and the per-logit guards vanish. nrows: the rows that hold an
+// environment of this workgroup; act_rows, if not NULL, also receives their actions by row.
 template <int AP, int ROWS, int NTHR, int AC = 0>
 __device__ __forceinline__ void sample_rows(const float* lg, int sl, const MlpParams& m, int e0,
                                             uint64_t seed, uint32_t step, uint8_t* act,
                                             float* logp, float* value, float* logits,
-                                            const float* us = nullptr) {
+                                            const float* us = nullptr, int nrows = ROWS,
+                                            uint8_t* act_rows = nullptr) {
   constexpr int G = 8, KMAX = AC > 0 ? (AC + G - 1) / G : (AP + G - 1) / G;
   static_assert(NTHR % G == 0 && G == 8, "sampler groups of 8 lanes (group8_*)");
   const int tid = threadIdx.x;
   for (int row0 = 0; row0 < ROWS; row0 += NTHR / G) {
     const int row = row0 + tid / G, part = tid % G;
     const int e = e0 + row;
-    const bool live = row < ROWS && e < m.E;
+    const bool live = row < nrows && e < m.E;
     const float* l = lg + (row < ROWS ? row : 0) * sl;
     const int A = AC > 0 ? AC : m.A;
     const int chunk = (A + G - 1) / G;
@@ -234,6 +236,7 @@ __device__ __forceinline__ void sample_rows(const float* lg, int sl, const MlpPa
     if (live && part == 0) {
       const int a = found < A ? found : A - 1;
       if (act) act[e] = (uint8_t)a;
+      if (act_rows) act_rows[row] = (uint8_t)a;
       if (logp) logp[e] = (l[a] - mx) - __logf(S);
       if (value && m.value_head) value[e] = l[A];
     }

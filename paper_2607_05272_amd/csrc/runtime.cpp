@@ -91,7 +91,7 @@ struct sim_ctx {
   RolloutKey rkey{}, seen{};
   bool rkey_valid = false, seen_valid = false;
   int fuse = SIM_FUSE_AUTO;   // fused small-batch rollouts (sim_set_fused_rollout)
-  int fuse_cap = -1;          // environments the fused kernel holds at once (0: none; -1: not asked)
+  FusedPlan fuse_plan{0, -1}; // its kernel and capacity (0: none; -1: not asked)
   int64_t graph_captures = 0, graph_replays = 0;
   // tracing: event pairs around kernel launches, per kernel class
   struct Pending { int cls; hipEvent_t a, b; };
@@ -639,12 +639,12 @@ int sim_policy_hidden(sim_ctx* x, const void* d_weights, const float* d_obs, uin
 // are resident at once (a second round would run every tick again for its workgroups alone)
 static bool use_fused(sim_ctx* x) {
   if (x->fuse == SIM_FUSE_OFF || x->cfg.policy_kind != SIM_POLICY_MLP) return false;
-  if (x->fuse_cap < 0) {
-    int cap = 0;
-    x->fuse_cap = fused_rollout_capacity(x->p, x->m, &cap) == hipSuccess && cap > 0 ? cap : 0;
+  if (x->fuse_plan.cap < 0) {
+    FusedPlan plan{0, 0};
+    x->fuse_plan = fused_rollout_plan(x->p, x->m, &plan) == hipSuccess ? plan : FusedPlan{0, 0};
   }
-  if (x->fuse_cap == 0) return false;
-  return x->fuse == SIM_FUSE_ON || x->cfg.n_envs <= x->fuse_cap;
+  if (x->fuse_plan.cap == 0) return false;
+  return x->fuse == SIM_FUSE_ON || x->cfg.n_envs <= x->fuse_plan.cap;
 }
 
 // Every launch of a rollout of T ticks from tick k0 on x->stream: the policy's weight repack,
@@ -684,17 +684,17 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
   // fp32 observation (half its bytes, both for the tick that writes it and the policy that
   // reads it); the fp32 observation is written again by the last tick
   const uint32_t* obs_bf = x->s.obs_bf;
-  if (obs_bf)
-    HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
-           "observation packing launch");
   if (use_fused(x)) {
     const RolloutOut o{tr->actions, tr->logp, tr->value, tr->reward, tr->rchk, tr->obs};
     HIPCHK(x->timed(SIM_KC_ROLLOUT, [&] {
-             return launch_rollout_fused(x->p, x->s, x->m, k0, T, o, x->stream);
+             return launch_rollout_fused(x->p, x->s, x->m, x->fuse_plan, k0, T, o, x->stream);
            }), "fused rollout launch");
     if (side) HIPCHK(hipStreamWaitEvent(x->stream, x->sev_join, 0), "hipStreamWaitEvent");
     return SIM_OK;
   }
+  if (obs_bf)
+    HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
+           "observation packing launch");
   for (int32_t i = 0; i < T; ++i) {
     const size_t row = (size_t)i * E;
     const uint32_t k = k0 + (uint32_t)i;

@@ -56,6 +56,9 @@ __device__ __forceinline__ void put(T (&a)[L], int i, T v) {
   for (int c = 0; c < M; ++c) a[c] = i == c ? v : a[c];
 }
 
+// The state arrays (SysState) are indexed [field][i] with a row length S: the whole batch in
+// memory (S = E and i the environment), or a workgroup's environments in LDS.
+
 // ---- per-class FIFO queues of one system ---------------------------------------------------
 template <int CM>
 struct Queue {
@@ -86,8 +89,7 @@ __device__ __forceinline__ int hol(const Queue<CM>& Q, const SimParams& p, doubl
 
 template <int CM>
 __device__ __forceinline__ void load_queue(Queue<CM>& Q, const SysState& g, const SimParams& p,
-                                           int e) {
-  const size_t E = (size_t)p.E;
+                                           size_t E, int e) {
   Q.qp = g.qpack[e];
   Q.hp = g.hpack[e];
   Q.qsum = 0;
@@ -96,14 +98,12 @@ __device__ __forceinline__ void load_queue(Queue<CM>& Q, const SysState& g, cons
     Q.hts[c] = c < p.C ? g.hts[(size_t)c * E + e] : 0.0;
     Q.qsum += Q.q(c);
   }
-  Q.ring = g.ring + (size_t)e * p.C * p.N;
   Q.hh = hol(Q, p, Q.hts_h);
 }
 
 template <int CM>
 __device__ __forceinline__ void store_queue(const Queue<CM>& Q, const SysState& g,
-                                            const SimParams& p, int e) {
-  const size_t E = (size_t)p.E;
+                                            const SimParams& p, size_t E, int e) {
   g.qpack[e] = Q.qp;
   g.hpack[e] = Q.hp;
 #pragma unroll
@@ -122,8 +122,7 @@ struct Count {
   uint32_t jsvc;  // service draws this tick
 };
 
-__device__ __forceinline__ void load_count(Count& C, const SysState& g, const SimParams& p, int e) {
-  const size_t E = (size_t)p.E;
+__device__ __forceinline__ void load_count(Count& C, const SysState& g, size_t E, int e) {
 #pragma unroll
   for (int i = 0; i < kNcnt; ++i) C.c[i] = g.cnt[(size_t)i * E + e];
   C.lat = g.sums[e];
@@ -134,9 +133,7 @@ __device__ __forceinline__ void load_count(Count& C, const SysState& g, const Si
   C.jsvc = 0;
 }
 
-__device__ __forceinline__ void store_count(const Count& C, const SysState& g, const SimParams& p,
-                                            int e) {
-  const size_t E = (size_t)p.E;
+__device__ __forceinline__ void store_count(const Count& C, const SysState& g, size_t E, int e) {
 #pragma unroll
   for (int i = 0; i < kNcnt; ++i) g.cnt[(size_t)i * E + e] = C.c[i];
   g.sums[e] = C.lat;
@@ -155,8 +152,9 @@ struct Arrivals {
   uint32_t jarr, jproc;
 };
 
+// (e_tr: the environment's index in the trace arrays)
 __device__ __forceinline__ void load_arrivals(Arrivals& A, const SysState& g, const SimParams& p,
-                                              int e) {
+                                              int e, int e_tr) {
   A.proc = g.proc[e];
   A.next_sw = g.next_sw[e];
   A.next_arr = g.next_arr[e];
@@ -165,7 +163,7 @@ __device__ __forceinline__ void load_arrivals(Arrivals& A, const SysState& g, co
   A.tr_cnt = 0;
   if (p.arrival_kind == 1) {
     A.tr_idx = g.tr_idx[e];
-    const int c = p.tr_cnt[e];
+    const int c = p.tr_cnt[e_tr];
     A.tr_cnt = c < 0 ? 0 : (c < p.tr_len ? c : p.tr_len);  // reset flags invalid counts
   }
   A.jarr = 0;
@@ -203,12 +201,13 @@ __device__ __forceinline__ double dwell(const SimParams& p, int st, double u) {
 // nothing else, stages 16 slots (fewer refills in bursts: -2.5% per C5 launch against 8); the
 // static system shares the CU's LDS with its servers' busy times and stages 8.
 constexpr int kStageLearned = 16, kStageStatic = 8;
-template <int KS>
+// LN: the lanes that can need draws (the wave's first LN)
+template <int KS, int LN = 64>
 struct Stage {
-  double E[KS][64];
-  uint8_t cls[KS][64];
-  uint32_t owner_j0[64];  // needing lane | first block << 6
-  uint32_t tick[64];
+  double E[KS][LN];
+  uint8_t cls[KS][LN];
+  uint32_t owner_j0[LN];  // needing lane | first block << 6
+  uint32_t tick[LN];
 };
 // A tick takes at most kMaxEventsPerTick events and each consumes at most two ARRIVAL blocks,
 // so a first block index fits the 26 bits above the lane.
@@ -226,8 +225,8 @@ __device__ __forceinline__ void wave_sync_lds() {
 // else KS / 2: at low arrival rates most lanes need one or two blocks per tick, and the work
 // of a pass is n times the number of lanes served. The lanes may be at different ticks.
 // fill(owner lane, tick, j) computes one block into the stage.
-template <int KS, class Fill>
-__device__ __forceinline__ void wave_refill(Stage<KS>& st, bool need, bool burst, uint32_t jneed,
+template <int KS, int LN, class Fill>
+__device__ __forceinline__ void wave_refill(Stage<KS, LN>& st, bool need, bool burst, uint32_t jneed,
                                             uint32_t k, uint32_t& staged_hi, int lane,
                                             Fill&& fill) {
   const uint64_t mask = __ballot(need);
@@ -251,25 +250,32 @@ __device__ __forceinline__ void wave_refill(Stage<KS>& st, bool need, bool burst
   if (need) staged_hi = jneed + (uint32_t)n;
 }
 
-// INL: the logarithm inline (kernels with registers to spare) rather than called
-template <int CM, int KS, bool INL = false>
-__device__ __forceinline__ void refill_arrivals(Stage<KS>& st, const SimParams& p, bool need,
+// Block j of (env, tick k) into lane own's slot of the stage. INL: the logarithm inline (kernels
+// with registers to spare) rather than called.
+template <int CM, int KS, bool INL, int LN>
+__device__ __forceinline__ void stage_block(Stage<KS, LN>& st, const SimParams& p, uint64_t seed,
+                                            uint32_t env, uint32_t k, uint32_t j, int own) {
+  const u32x4 d = draw(seed, env, k, P_ARRIVAL, j, 0);
+  st.E[j % KS][own] = -(INL ? dlog_inl(unit(d.x, d.y)) : dlog(unit(d.x, d.y)));
+  const double uc = unit(d.z, d.w);
+  int cls = CM - 1;
+#pragma unroll
+  for (int c = CM - 2; c >= 0; --c)
+    if (uc < p.class_cum[c]) cls = c;
+  st.cls[j % KS][own] = (uint8_t)cls;
+}
+
+template <int CM, int KS, bool INL = false, int LN = 64>
+__device__ __forceinline__ void refill_arrivals(Stage<KS, LN>& st, const SimParams& p, bool need,
                                                 uint32_t jneed, uint32_t& staged_hi,
                                                 uint64_t seed, int e_lane0, uint32_t k, int lane) {
   bool burst = false;
 #pragma unroll
   for (int s = 0; s < kMaxS; ++s)
     if (s < p.S && p.rate[s] * p.dt * 4.0 > (double)KS) burst = true;
-  wave_refill<KS>(st, need, burst, jneed, k, staged_hi, lane, [&](uint32_t own, uint32_t kk,
+  wave_refill<KS, LN>(st, need, burst, jneed, k, staged_hi, lane, [&](uint32_t own, uint32_t kk,
                                                                    uint32_t j) {
-    const u32x4 d = draw(seed, (uint32_t)(e_lane0 + (int)own), kk, P_ARRIVAL, j, 0);
-    st.E[j % KS][own] = -(INL ? dlog_inl(unit(d.x, d.y)) : dlog(unit(d.x, d.y)));
-    const double uc = unit(d.z, d.w);
-    int cls = CM - 1;
-#pragma unroll
-    for (int c = CM - 2; c >= 0; --c)
-      if (uc < p.class_cum[c]) cls = c;
-    st.cls[j % KS][own] = (uint8_t)cls;
+    stage_block<CM, KS, INL, LN>(st, p, seed, (uint32_t)(e_lane0 + (int)own), kk, j, (int)own);
   });
 }
 
@@ -277,8 +283,8 @@ __device__ __forceinline__ void refill_arrivals(Stage<KS>& st, const SimParams& 
 // arrival from the switch instant). Returns the class of an arrival at `now`, or -1. ARRIVAL
 // blocks are read from the stage (the caller guarantees that the two blocks an instant can
 // consume, a switch redraw and an arrival, are staged).
-template <int CM, int KS, bool INL = false>
-__device__ __forceinline__ int advance_staged(Arrivals& A, const SimParams& p, const Stage<KS>& st,
+template <int CM, int KS, bool INL = false, int LN = 64>
+__device__ __forceinline__ int advance_staged(Arrivals& A, const SimParams& p, const Stage<KS, LN>& st,
                                               int lane, uint64_t seed, int e, uint32_t k,
                                               double now) {
   if (A.next_sw == now) {
@@ -345,26 +351,25 @@ __device__ __forceinline__ void enqueue(Queue<CM>& Q, Count& C, const SimParams&
 
 // The same arrival as enqueue, written as selects (the ring store aside) for the arrival runs
 // of the learned tick: a loop over branchy code keeps copies of the whole queue state in
-// flight, while this straight-line form updates it in place.
+// flight, while this straight-line form updates it in place. Returns whether the request was
+// accepted; the run counts its arrivals once, at its end.
 template <int CM>
-__device__ __forceinline__ void enqueue_sel(Queue<CM>& Q, Count& C, const SimParams& p, int cls,
+__device__ __forceinline__ bool enqueue_sel(Queue<CM>& Q, const SimParams& p, int cls,
                                             double now) {
   const bool acc = Q.qsum != p.N;
   const int qc = Q.q(cls);
   int pos = Q.hd(cls) + qc;
   pos = pos >= p.N ? pos - p.N : pos;
-  if (acc) Q.ring[(size_t)cls * p.N + pos] = now;
-  const bool first = acc && qc == 0;
-  const bool lead = first && (Q.qsum == 0 || (now == Q.hts_h && cls < Q.hh));
+  if (acc) Q.ring[__umul24((uint32_t)cls, (uint32_t)p.N) + (uint32_t)pos] = now;
+  const bool first = acc & (qc == 0);
+  const bool lead = first & ((Q.qsum == 0) | ((now == Q.hts_h) & (cls < Q.hh)));
 #pragma unroll
   for (int c = 0; c < CM; ++c) Q.hts[c] = first && cls == c ? now : Q.hts[c];
   Q.hh = lead ? cls : Q.hh;
   Q.hts_h = lead ? now : Q.hts_h;
   Q.qp += acc ? 1u << (8 * cls) : 0u;
   Q.qsum += acc ? 1 : 0;
-  C.c[C_ARR] += 1u;
-  C.c[C_DROP] += acc ? 0u : 1u;
-  C.c[C_ACC] += acc ? 1u : 0u;
+  return acc;
 }
 
 // Service time of a batch of n requests of class h. kind 0: alpha + beta n; kind 1:
@@ -404,14 +409,14 @@ __device__ __forceinline__ double pop_batch(Queue<CM>& Q, Count& C, const SimPar
   const double cdone = now + sv;
   const double wh = pick<CM>(p.w_class, h);
   const int N = p.N;
-  const double* rb = Q.ring + (size_t)h * N;
+  const uint32_t rb = __umul24((uint32_t)h, (uint32_t)N);   // the class's ring in Q.ring
   const int head = Q.hd(h);
   int pos = head + n;
   pos = pos >= N ? pos - N : pos;
   const int qh = Q.q(h) - n;
   // the new head's timestamp (read even when the class empties: pos is inside the ring) and
   // the popped timestamps, eight at a time, are loaded before any of them is used
-  const double next_head = rb[pos];
+  const double next_head = Q.ring[rb + (uint32_t)pos];
   double Lw = C.Lw, lat = C.lat, wlat = C.wlat;
   for (int i0 = 0; i0 < n; i0 += 8) {
     double a[8];
@@ -419,7 +424,7 @@ __device__ __forceinline__ double pop_batch(Queue<CM>& Q, Count& C, const SimPar
     for (int i = 0; i < 8; ++i) {
       int q = head + i0 + i;
       q = q >= N ? q - N : q;
-      a[i] = i0 + i < n ? rb[q] : 0.0;
+      a[i] = i0 + i < n ? Q.ring[rb + (uint32_t)q] : 0.0;
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -484,76 +489,46 @@ struct ObsPairs {
     }
     if (bf) bf[(size_t)(i >> 1) * E + e] = pack_bf16_pair(a, b);
   }
+  // features from i on, past the state's: zero in the current observation (and its bf16 pairs)
+  // since the reset or the pairs' packing (nothing else writes them), so only a trajectory row
+  // needs them
+  __device__ __forceinline__ void pad(int i, int F) const {
+    if (traj)
+      for (; i < F; ++i) traj[(size_t)i * E + e] = 0.0f;
+  }
 };
 
 // ---- learned system: one tick ---------------------------------------------------------------
 // share of the wave's lanes still in the tick that triggers a dispatch pass (1 / share)
 constexpr int kLearnedDispatchShare = 4;
 constexpr int kEndChunk = 8;   // server rows read per round trip at the end of the tick
-// PF: the end-of-tick reads of the server rows (K <= kEndChunk) and of the arrival-rate
-// averages are issued at the start of the tick instead, so that their latency passes under
-// the event loop; they cost registers, which waves that have a SIMD to themselves can spare.
-// Only this kernel writes those arrays, at the end of a tick, so the early reads see the same
-// values. Without PF the kernel is held to four waves per SIMD (128 VGPRs): the largest grid
-// fills the chip exactly at that occupancy.
-// One tick k of the learned system for environments e_lane0 .. e_lane0 + lpw - 1, held by the
-// first lpw lanes of the calling wave (all 64 lanes call it, and lanes past E idle); st is
-// the wave's arrival stage. Reads the actions act[E], writes the observation of tick k + 1
-// (obs_mode), the reward and checksum rows (if not NULL) and the environments' state.
-template <int CM, bool PF>
-__device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState& g, uint64_t seed,
-                                             uint32_t k, int e_lane0, int lpw,
-                                             Stage<kStageLearned>& st,
-                                             const uint8_t* __restrict__ act,
-                                             float* __restrict__ obs_out, int obs_mode,
-                                             double* __restrict__ rew,
-                                             uint64_t* __restrict__ rchk) {
-  // the fp64 logarithm, exponential and cosine of the arrival, switch and service draws
-  // inline rather than called: a call waits for every outstanding memory access first and
-  // saves registers, which waves that have a SIMD to themselves can spare (measured with four
-  // request classes: the 8-server tick -4.9%; with fewer classes even or slower)
-  constexpr bool kInl = PF && CM >= 4;
+// The events of tick k for the calling wave's lanes (all 64 call it; those that are not `live`
+// take none): arrivals, switches, the chosen server's completion and the dispatches of b requests
+// to server s. e_lane0 + lane is the lane's environment in the draws, ee its own; the first
+// `staged` ARRIVAL blocks of every live lane are in the stage. load() and end() fetch the lane's
+// state and take what the events left (the state is a local of this function, between them, rather
+// than the caller's: by reference it costs the per-tick kernels 10 waits on memory and 3%).
+// Bound by the instructions of the lane with most events, about 80 per arrival in a run and a few
+// hundred per pass; with the runs' counters added once and 32-bit ring indices the tick of 65536
+// environments with 8 servers went from 40.8 to 39.5 us, of 32768 with 16 from 72 to 68.
+template <int CM, bool INL, int LN, class Load, class End>
+__device__ __forceinline__ void tick_events(const SimParams& p, uint32_t* err, uint64_t seed,
+                                            uint32_t k, int e_lane0, bool live, int ee,
+                                            Stage<kStageLearned, LN>& st, uint32_t staged,
+                                            Load&& load, End&& end) {
   const int lane = threadIdx.x & 63;
-  const int e = e_lane0 + lane;
-  // lanes without an environment stay in the loop (the wave refills together) but idle
-  const bool live = lane < lpw && e < p.E;
-  if (__ballot(live) == 0ull) return;
-  const int ee = live ? e : 0;
-  const size_t E = (size_t)p.E;
-  const SysState& G = g.sys[0];
-  // the state loads are issued before the action is examined: a branch on the action (and
-  // the error flag's atomic, which may alias any state array) ahead of them would make every
-  // environment wait out the action load first
-  const int a_in = live ? act[ee] : 0;
   Queue<CM> Q;
-  load_queue(Q, G, p, ee);
   Count C;
-  load_count(C, G, p, ee);
   Arrivals A;
-  load_arrivals(A, G, p, ee);
-  const bool bad_action = a_in >= 6 * p.K;
-  const int a = bad_action ? 0 : a_in;
-  const int s = a / 6, b = 1 << (a % 6);
-  double busy_s = G.busy[(size_t)s * E + ee];
-  uint32_t meta_s = G.meta[(size_t)s * E + ee];
-  if (bad_action) atomicOr(g.err, ERR_ACTION);
+  int s, b;   // the action: server, batch
+  double busy_s;
+  uint32_t meta_s;
   bool dirty_s = false;
-  double brow_pf[PF ? kEndChunk : 1], ew_pf[PF ? 4 : 1];
-  uint32_t mrow_pf[PF ? kEndChunk : 1];
-  if constexpr (PF) {
-#pragma unroll
-    for (int i = 0; i < kEndChunk; ++i) {
-      brow_pf[i] = i < p.K ? G.busy[(size_t)i * E + ee] : 0.0;
-      mrow_pf[i] = i < p.K ? G.meta[(size_t)i * E + ee] : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ew_pf[i] = g.ewma[(size_t)i * E + ee];
-  }
-
+  load(Q, C, A, s, b, busy_s, meta_s);
   const double t0 = (double)k * p.dt, t1 = (double)(k + 1) * p.dt;
   int A_k = 0;
   double now = t0;
-  uint32_t staged_hi = 0;
+  uint32_t staged_hi = staged;
   uint32_t it = 0;
   // the action's rule at `now`: exactly b requests of the head-of-line class whenever
   // server s is idle
@@ -575,7 +550,7 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
       if (!(te < t1)) {
         done = true;
       } else if (it > kMaxEventsPerTick) {
-        atomicOr(g.err, ERR_EVENTS);
+        atomicOr(err, ERR_EVENTS);
         done = true;
       } else {
         need = p.arrival_kind != 1 && (A.next_sw == te || A.next_arr == te) &&
@@ -584,12 +559,12 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
       }
     }
     if (__ballot(need) != 0ull)
-      refill_arrivals<CM, kStageLearned, kInl>(st, p, need, A.jarr, staged_hi, seed, e_lane0,
+      refill_arrivals<CM, kStageLearned, INL>(st, p, need, A.jarr, staged_hi, seed, e_lane0,
                                                k, lane);
     if (go) {
       ++it;
       now = te;
-      const int cls = advance_staged<CM, kStageLearned, kInl>(A, p, st, lane, seed, ee, k, now);
+      const int cls = advance_staged<CM, kStageLearned, INL>(A, p, st, lane, seed, ee, k, now);
       if (cls >= 0) {
         ++A_k;
         enqueue(Q, C, p, cls, now);
@@ -601,19 +576,31 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
       // until one makes a batch due, without the pass's wave-wide bookkeeping
       if (!pend && p.arrival_kind != 1) {
         const double wend = fmin(fmin(A.next_sw, busy_s > now ? busy_s : kInf), t1);
-        bool more = A.next_arr < wend && A.jarr + 2u <= staged_hi && it <= kMaxEventsPerTick;
+        // the run's r-th arrival is taken while r <= lim: with blocks staged for an instant
+        // (A.jarr + 2 <= staged_hi) and within the event bound
+        const uint32_t j0 = A.jarr;
+        const int lim = min((int)(staged_hi - j0) - 2, (int)kMaxEventsPerTick - (int)it);
+        // server s stays idle, or busy, through the run (a completion ends it): waiting requests
+        // of the head-of-line class that make a batch due
+        const int due_q = busy_s <= now ? b : 256;
+        int r = 0, drops = 0;
+        bool more = A.next_arr < wend && r <= lim;
         while (more) {
-          ++it;
           now = A.next_arr;
-          const uint32_t j = A.jarr++;
-          const int c = st.cls[j % kStageLearned][lane];
-          A.next_arr = now + st.E[j % kStageLearned][lane] * A.gap;
-          ++A_k;
-          enqueue_sel(Q, C, p, c, now);
-          pend = due();
-          more = !pend && A.next_arr < wend && A.jarr + 2u <= staged_hi &&
-                 it <= kMaxEventsPerTick;
+          const uint32_t j = (j0 + (uint32_t)r) % kStageLearned;
+          const int c = st.cls[j][lane];
+          A.next_arr = now + st.E[j][lane] * A.gap;
+          ++r;
+          drops += enqueue_sel(Q, p, c, now) ? 0 : 1;
+          pend = Q.q(Q.hh) >= due_q;
+          more = !pend && A.next_arr < wend && r <= lim;
         }
+        A.jarr += (uint32_t)r;
+        it += (uint32_t)r;
+        A_k += r;
+        C.c[C_ARR] += (uint32_t)r;
+        C.c[C_DROP] += (uint32_t)drops;
+        C.c[C_ACC] += (uint32_t)(r - drops);
       }
     }
     const int n_act = __popcll(__ballot(!done)), n_pend = __popcll(__ballot(pend));
@@ -622,7 +609,7 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
         pend) {
       const int h = Q.hh;
       C.c[C_DONE] += meta_s & 0xffu;  // the previous batch on s finished at busy_s <= now
-      const double sv = service<CM, kInl>(C, p, seed, ee, k, 0, h, b);
+      const double sv = service<CM, INL>(C, p, seed, ee, k, 0, h, b);
       busy_s = pop_batch(Q, C, p, k, s, h, b, now, sv);
       meta_s = (uint32_t)b | ((uint32_t)b << 8) | ((uint32_t)h << 16);
       dirty_s = true;
@@ -630,106 +617,170 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
     }
     if (__ballot(!done) == 0ull) break;
   }
-  if (!live) return;
+  end(Q, C, A, s, b, busy_s, meta_s, dirty_s, A_k);
+}
 
-  // end of tick: completions before t1 and the per-server part of obs_{k+1}. The server rows
-  // are read kEndChunk at a time, all loads of a chunk issued before any of its stores (the
-  // compiler cannot reorder them across the stores, which it must assume may alias), so a
-  // chunk costs one memory round trip instead of two per server.
-  const ObsPairs ob{(obs_mode & kObsF32) ? g.obs : nullptr, obs_out,
-                    (obs_mode & kObsBf16) ? g.obs_bf : nullptr, E, e};
-  const int per = p.K > 1 ? 4 : 2;
-  for (int j0 = 0; j0 < p.K; j0 += kEndChunk) {
-    double brow[kEndChunk];
-    uint32_t mrow[kEndChunk];
+// PF: the end-of-tick reads of the server rows (K <= kEndChunk) and of the arrival-rate
+// averages are issued at the start of the tick instead, so that their latency passes under
+// the event loop; they cost registers, which one or two waves per SIMD can spare.
+// Only this kernel writes those arrays, at the end of a tick, so the early reads see the same
+// values. Without PF the kernel is held to four waves per SIMD (128 VGPRs): the largest grid
+// fills the chip exactly at that occupancy.
+// One tick k of the learned system for environments e_lane0 .. e_lane0 + lpw - 1, held by the
+// first lpw lanes of the calling wave (all 64 lanes call it, and lanes past E idle); st is
+// the wave's arrival stage. Reads the actions act[E], writes the observation of tick k + 1
+// (obs_mode), the reward and checksum rows (if not NULL) and the environments' state.
+template <int CM, bool PF>
+__device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState& g, uint64_t seed,
+                                             uint32_t k, int e_lane0, int lpw,
+                                             Stage<kStageLearned>& st,
+                                             const uint8_t* __restrict__ act,
+                                             float* __restrict__ obs_out, int obs_mode,
+                                             double* __restrict__ rew,
+                                             uint64_t* __restrict__ rchk) {
+  // the fp64 logarithm, exponential and cosine of the arrival, switch and service draws
+  // inline rather than called: a call waits for every outstanding memory access first and
+  // saves registers, which one or two waves per SIMD can spare (measured with four
+  // request classes: the 8-server tick -4.9%; with fewer classes even or slower)
+  constexpr bool kInl = PF && CM >= 4;
+  const int lane = threadIdx.x & 63;
+  const int e = e_lane0 + lane;
+  // lanes without an environment stay in the loop (the wave refills together) but idle
+  const bool live = lane < lpw && e < p.E;
+  if (__ballot(live) == 0ull) return;
+  const int ee = live ? e : 0;
+  const size_t E = (size_t)p.E;
+  const SysState& G = g.sys[0];
+  double brow_pf[PF ? kEndChunk : 1], ew_pf[PF ? 4 : 1];
+  uint32_t mrow_pf[PF ? kEndChunk : 1];
+  const double t1 = (double)(k + 1) * p.dt;
+  auto load = [&](Queue<CM>& Q, Count& C, Arrivals& A, int& s, int& b, double& busy_s,
+                  uint32_t& meta_s) {
+    // the state loads are issued before the action is examined: a branch on the action (and
+    // the error flag's atomic, which may alias any state array) ahead of them would make every
+    // environment wait out the action load first
+    const int a_in = live ? act[ee] : 0;
+    load_queue(Q, G, p, E, ee);
+    Q.ring = G.ring + (size_t)ee * p.C * p.N;
+    load_count(C, G, E, ee);
+    load_arrivals(A, G, p, ee, ee);
+    const bool bad_action = a_in >= 6 * p.K;
+    const int a = bad_action ? 0 : a_in;
+    s = a / 6;
+    b = 1 << (a % 6);
+    busy_s = G.busy[(size_t)s * E + ee];
+    meta_s = G.meta[(size_t)s * E + ee];
+    if (bad_action) atomicOr(g.err, ERR_ACTION);
+    if constexpr (PF) {
 #pragma unroll
-    for (int i = 0; i < kEndChunk; ++i) {
-      if constexpr (PF) {
-        brow[i] = brow_pf[i];
-        mrow[i] = mrow_pf[i];
-      } else {
-        brow[i] = 0.0;
-        mrow[i] = 0u;
-        if (j0 + i < p.K) {
-          brow[i] = G.busy[(size_t)(j0 + i) * E + e];
-          mrow[i] = G.meta[(size_t)(j0 + i) * E + e];
+      for (int i = 0; i < kEndChunk; ++i) {
+        brow_pf[i] = i < p.K ? G.busy[(size_t)i * E + ee] : 0.0;
+        mrow_pf[i] = i < p.K ? G.meta[(size_t)i * E + ee] : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ew_pf[i] = g.ewma[(size_t)i * E + ee];
+    }
+  };
+  auto end = [&](Queue<CM>& Q, Count& C, Arrivals& A, int s, int b, double busy_s, uint32_t meta_s,
+                 bool dirty_s, int A_k) {
+    if (!live) return;
+
+    // end of tick: completions before t1 and the per-server part of obs_{k+1}. The server rows
+    // are read kEndChunk at a time, all loads of a chunk issued before any of its stores (the
+    // compiler cannot reorder them across the stores, which it must assume may alias), so a
+    // chunk costs one memory round trip instead of two per server.
+    const ObsPairs ob{(obs_mode & kObsF32) ? g.obs : nullptr, obs_out,
+                      (obs_mode & kObsBf16) ? g.obs_bf : nullptr, E, e};
+    const int per = p.K > 1 ? 4 : 2;
+    for (int j0 = 0; j0 < p.K; j0 += kEndChunk) {
+      double brow[kEndChunk];
+      uint32_t mrow[kEndChunk];
+#pragma unroll
+      for (int i = 0; i < kEndChunk; ++i) {
+        if constexpr (PF) {
+          brow[i] = brow_pf[i];
+          mrow[i] = mrow_pf[i];
+        } else {
+          brow[i] = 0.0;
+          mrow[i] = 0u;
+          if (j0 + i < p.K) {
+            brow[i] = G.busy[(size_t)(j0 + i) * E + e];
+            mrow[i] = G.meta[(size_t)(j0 + i) * E + e];
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kEndChunk; ++i) {
+        const int j = j0 + i;
+        if (j >= p.K) break;
+        const bool mine = j == s;
+        const double bu = mine ? busy_s : brow[i];
+        uint32_t m = mine ? meta_s : mrow[i];
+        bool dirty = mine && dirty_s;
+        const uint32_t infl = m & 0xffu;
+        if (infl > 0 && bu < t1) {
+          C.c[C_DONE] += infl;
+          m &= ~0xffu;
+          dirty = true;
+        }
+        if (dirty) {
+          if (mine) G.busy[(size_t)j * E + e] = bu;
+          G.meta[(size_t)j * E + e] = m;
+        }
+        const int base = 2 + per * j;
+        const double bflag = bu > t1 ? 1.0 : 0.0;
+        const double lb = (double)((m >> 8) & 0xffu) * 0.03125;
+        ob.put(base, bflag, lb);
+        if (p.K > 1) {
+          const double rem = (bu > t1 ? bu - t1 : 0.0) * p.inv_tw;
+          const uint32_t lc = (m >> 16) & 0xffu;
+          const double lcv = (double)((lc == 0xffu ? -1 : (int)lc) + 1) * p.inv_c;
+          ob.put(base + 2, rem, lcv);
         }
       }
     }
+    const double r = close_tick(Q, C, p, A.proc, A_k);
+    if (rew) rew[e] = r;
+    if (rchk) rchk[e] = C.chk;
+
+    // rates: exponentially weighted arrival counts with weights 1, 1/4, 1/16, 1/64
+    // (all four read before the first store, for the same reason as the server rows)
+    double ew[4];
+    const double ewc[4] = {1.0, 0.25, 0.0625, 0.015625};
 #pragma unroll
-    for (int i = 0; i < kEndChunk; ++i) {
-      const int j = j0 + i;
-      if (j >= p.K) break;
-      const bool mine = j == s;
-      const double bu = mine ? busy_s : brow[i];
-      uint32_t m = mine ? meta_s : mrow[i];
-      bool dirty = mine && dirty_s;
-      const uint32_t infl = m & 0xffu;
-      if (infl > 0 && bu < t1) {
-        C.c[C_DONE] += infl;
-        m &= ~0xffu;
-        dirty = true;
-      }
-      if (dirty) {
-        if (mine) G.busy[(size_t)j * E + e] = bu;
-        G.meta[(size_t)j * E + e] = m;
-      }
-      const int base = 2 + per * j;
-      const double bflag = bu > t1 ? 1.0 : 0.0;
-      const double lb = (double)((m >> 8) & 0xffu) * 0.03125;
-      ob.put(base, bflag, lb);
-      if (p.K > 1) {
-        const double rem = (bu > t1 ? bu - t1 : 0.0) * p.inv_tw;
-        const uint32_t lc = (m >> 16) & 0xffu;
-        const double lcv = (double)((lc == 0xffu ? -1 : (int)lc) + 1) * p.inv_c;
-        ob.put(base + 2, rem, lcv);
+    for (int i = 0; i < 4; ++i) ew[i] = PF ? ew_pf[PF ? i : 0] : g.ewma[(size_t)i * E + e];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ew[i] = ew[i] + ewc[i] * ((double)A_k - ew[i]);
+      g.ewma[(size_t)i * E + e] = ew[i];
+    }
+    // queue part of obs_{k+1}
+    const int h = Q.hh;
+    const double f0 = (double)Q.qsum * p.inv_n, f1 = (h >= 0 ? t1 - Q.hts_h : 0.0) * p.inv_tw;
+    ob.put(0, f0, f1);
+    int i = 2 + per * p.K;
+    if (p.C > 1) {
+#pragma unroll
+      for (int c = 0; c < CM; ++c) {
+        if (c < p.C) {
+          const int qc = Q.q(c);
+          const double fq = (double)qc * p.inv_n;
+          const double fa = (qc > 0 ? t1 - Q.hts[c] : 0.0) * p.inv_tw;
+          ob.put(i, fq, fa);
+          i += 2;
+        }
       }
     }
-  }
-  const double r = close_tick(Q, C, p, A.proc, A_k);
-  if (rew) rew[e] = r;
-  if (rchk) rchk[e] = C.chk;
+    ob.put(i, ew[0] * p.inv_rs, ew[1] * p.inv_rs);
+    ob.put(i + 2, ew[2] * p.inv_rs, ew[3] * p.inv_rs);
+    i += 4;
+    ob.pad(i, p.F);
 
-  // rates: exponentially weighted arrival counts with weights 1, 1/4, 1/16, 1/64
-  // (all four read before the first store, for the same reason as the server rows)
-  double ew[4];
-  const double ewc[4] = {1.0, 0.25, 0.0625, 0.015625};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) ew[i] = PF ? ew_pf[PF ? i : 0] : g.ewma[(size_t)i * E + e];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    ew[i] = ew[i] + ewc[i] * ((double)A_k - ew[i]);
-    g.ewma[(size_t)i * E + e] = ew[i];
-  }
-  // queue part of obs_{k+1}
-  const int h = Q.hh;
-  const double f0 = (double)Q.qsum * p.inv_n, f1 = (h >= 0 ? t1 - Q.hts_h : 0.0) * p.inv_tw;
-  ob.put(0, f0, f1);
-  int i = 2 + per * p.K;
-  if (p.C > 1) {
-#pragma unroll
-    for (int c = 0; c < CM; ++c) {
-      if (c < p.C) {
-        const int qc = Q.q(c);
-        const double fq = (double)qc * p.inv_n;
-        const double fa = (qc > 0 ? t1 - Q.hts[c] : 0.0) * p.inv_tw;
-        ob.put(i, fq, fa);
-        i += 2;
-      }
-    }
-  }
-  ob.put(i, ew[0] * p.inv_rs, ew[1] * p.inv_rs);
-  ob.put(i + 2, ew[2] * p.inv_rs, ew[3] * p.inv_rs);
-  i += 4;
-  // the padding rows past the observation's width: zero in the current observation (and its
-  // bf16 pairs) since the reset or the pairs' packing (nothing else writes them), so only a
-  // trajectory row needs them
-  if (obs_out)
-    for (; i < p.F; ++i) obs_out[(size_t)i * E + e] = 0.0f;
-
-  store_queue(Q, G, p, e);
-  store_count(C, G, p, e);
-  store_arrivals(A, G, p, e);
+    store_queue(Q, G, p, E, e);
+    store_count(C, G, E, e);
+    store_arrivals(A, G, p, e);
+  };
+  tick_events<CM, kInl, 64>(p, g.err, seed, k, e_lane0, live, ee, st, 0u, load, end);
 }
 
 }  // namespace

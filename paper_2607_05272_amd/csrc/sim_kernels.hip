@@ -363,11 +363,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   const size_t E = (size_t)p.E;
   const SysState& G = g.sys[1];
   Queue<CM> Q;
-  load_queue(Q, G, p, ee);
+  load_queue(Q, G, p, E, ee);
+  Q.ring = G.ring + (size_t)ee * p.C * p.N;
   Count C;
-  load_count(C, G, p, ee);
+  load_count(C, G, E, ee);
   Arrivals A;
-  load_arrivals(A, G, p, ee);
+  load_arrivals(A, G, p, ee, ee);
   // busy-until times in registers; of each server's meta word only the in-flight count
   // (low byte) is kept, eight servers to a 64-bit register (the word is stored at dispatch)
   BusyTimes<KM> busy;
@@ -403,8 +404,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         G.meta[(size_t)j * E + e] = infl.get(j) | (sq.n2.get(j) << 24);
       }
     }
-    store_queue(Q, G, p, e);
-    store_count(C, G, p, e);
+    store_queue(Q, G, p, E, e);
+    store_count(C, G, E, e);
     store_arrivals(A, G, p, e);
     return;
   }
@@ -420,8 +421,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   for (int j = 0; j < KM; ++j)
     if (dirty & (1u << j)) G.busy[(size_t)j * E + e] = busy.get(j);
   if (p.route == 2) G.rr[e] = rr;
-  store_queue(Q, G, p, e);
-  store_count(C, G, p, e);
+  store_queue(Q, G, p, E, e);
+  store_count(C, G, E, e);
   store_arrivals(A, G, p, e);
 }
 
@@ -615,8 +616,10 @@ hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
   const int lpw = lanes_per_wave(p.E);
   const int waves = (p.E + lpw - 1) / lpw;
   const dim3 grid((waves + 3) / 4);
-  // early end-of-tick reads when every wave has a SIMD to itself
-  if (waves <= kFillWaves && p.K <= kEndChunk)
+  // early end-of-tick reads (and no register limit) while a SIMD has at most two waves: 20000
+  // environments with 8 servers, 1250 waves, 36.5 us per tick against 37.0; two waves of the
+  // unlimited kernel are all that fit a SIMD
+  if (waves <= 2 * kFillWaves && p.K <= kEndChunk)
     launch_learned<true>(p, s, k, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
   else
     launch_learned<false>(p, s, k, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
