@@ -27,7 +27,7 @@ constexpr int kBlock = 256;
 // Scores are kept in base-2 units: the queries carry the factor log2(e) / sqrt(D/NH), so each
 // softmax weight is one exp2 of (score - max).
 template <int L, int NH, int A>
-__global__ __launch_bounds__(kBlock) void attn_policy_k(AttnParams p, const float* __restrict__ obs,
+__global__ __launch_bounds__(kBlock) void attn_policy_k(AttnParams p, int b0, const float* __restrict__ obs,
                                                         const uint64_t* __restrict__ seedp, uint32_t step,
                                                         uint8_t* __restrict__ act,
                                                         float* __restrict__ logp,
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kBlock) void attn_policy_k(AttnParams p, const floa
   constexpr int DH = kD / NH;
   constexpr float kLog2e = 1.4426950408889634f;
   const float qscale = (DH == 1 ? 1.0f : DH == 2 ? 0.70710678118654752f : 0.5f) * kLog2e;
-  const int e = blockIdx.x * kBlock + threadIdx.x;
+  const int e = (b0 + blockIdx.x) * kBlock + threadIdx.x;
   if (e >= p.E) return;
   const size_t E = (size_t)p.E;
   const int G = p.F / L;
@@ -181,31 +181,32 @@ __global__ __launch_bounds__(kBlock) void attn_policy_k(AttnParams p, const floa
 
 template <int L, int NH, int A>
 hipError_t run_attn(const AttnParams& p, const float* obs, const uint64_t* seed, uint32_t step,
-                    uint8_t* act, float* logp, float* value, float* logits, hipStream_t st) {
-  const dim3 grid((unsigned)((p.E + kBlock - 1) / kBlock)), block(kBlock);
-  hipLaunchKernelGGL((attn_policy_k<L, NH, A>), grid, block, 0, st, p, obs, seed, step, act, logp,
+                    uint8_t* act, float* logp, float* value, float* logits, EnvPart part, hipStream_t st) {
+  if (part.e0 % kBlock != 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((part.n + kBlock - 1) / kBlock)), block(kBlock);
+  hipLaunchKernelGGL((attn_policy_k<L, NH, A>), grid, block, 0, st, p, part.e0 / kBlock, obs, seed, step, act, logp,
                      value, logits);
   return hipGetLastError();
 }
 
 template <int L, int NH>
 hipError_t run_attn_a(const AttnParams& p, const float* obs, const uint64_t* seed, uint32_t step,
-                      uint8_t* act, float* logp, float* value, float* logits, hipStream_t st) {
+                      uint8_t* act, float* logp, float* value, float* logits, EnvPart part, hipStream_t st) {
   switch (p.A) {
-    case 6: return run_attn<L, NH, 6>(p, obs, seed, step, act, logp, value, logits, st);
-    case 12: return run_attn<L, NH, 12>(p, obs, seed, step, act, logp, value, logits, st);
-    case 24: return run_attn<L, NH, 24>(p, obs, seed, step, act, logp, value, logits, st);
+    case 6: return run_attn<L, NH, 6>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 12: return run_attn<L, NH, 12>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 24: return run_attn<L, NH, 24>(p, obs, seed, step, act, logp, value, logits, part, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int L>
 hipError_t run_attn_h(const AttnParams& p, const float* obs, const uint64_t* seed, uint32_t step,
-                      uint8_t* act, float* logp, float* value, float* logits, hipStream_t st) {
+                      uint8_t* act, float* logp, float* value, float* logits, EnvPart part, hipStream_t st) {
   switch (p.NH) {
-    case 1: return run_attn_a<L, 1>(p, obs, seed, step, act, logp, value, logits, st);
-    case 2: return run_attn_a<L, 2>(p, obs, seed, step, act, logp, value, logits, st);
-    case 4: return run_attn_a<L, 4>(p, obs, seed, step, act, logp, value, logits, st);
+    case 1: return run_attn_a<L, 1>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 2: return run_attn_a<L, 2>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 4: return run_attn_a<L, 4>(p, obs, seed, step, act, logp, value, logits, part, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -847,13 +848,13 @@ bool attn_shape_supported(const AttnParams& p) {
 
 hipError_t launch_attn_policy(const AttnParams& p, const float* obs, const uint64_t* seed, uint32_t step,
                               uint8_t* act, float* logp, float* value, float* logits,
-                              hipStream_t st) {
+                              EnvPart part, hipStream_t st) {
   if (!attn_shape_supported(p)) return hipErrorInvalidValue;
   switch (p.L) {
-    case 1: return run_attn_h<1>(p, obs, seed, step, act, logp, value, logits, st);
-    case 2: return run_attn_h<2>(p, obs, seed, step, act, logp, value, logits, st);
-    case 4: return run_attn_h<4>(p, obs, seed, step, act, logp, value, logits, st);
-    case 8: return run_attn_h<8>(p, obs, seed, step, act, logp, value, logits, st);
+    case 1: return run_attn_h<1>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 2: return run_attn_h<2>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 4: return run_attn_h<4>(p, obs, seed, step, act, logp, value, logits, part, st);
+    case 8: return run_attn_h<8>(p, obs, seed, step, act, logp, value, logits, part, st);
     default: return hipErrorInvalidValue;
   }
 }

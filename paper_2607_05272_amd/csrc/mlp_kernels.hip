@@ -9,7 +9,7 @@ namespace bsim {
 namespace {
 
 template <class M, int FP, int H1, int H2, int AP, int RT, bool DBG>
-__global__ __launch_bounds__(kThreads) void policy_k(MlpParams m, const float* __restrict__ obs,
+__global__ __launch_bounds__(kThreads) void policy_k(MlpParams m, int b0, const float* __restrict__ obs,
                                                      const uint64_t* __restrict__ seedp, uint32_t step,
                                                      uint8_t* __restrict__ act,
                                                      float* __restrict__ logp,
@@ -18,7 +18,7 @@ __global__ __launch_bounds__(kThreads) void policy_k(MlpParams m, const float* _
                                                      float* __restrict__ hid) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   policy_tile_f32<M, FP, H1, H2, AP, RT, DBG>(m, obs, *seedp, step, act, logp, value, logits, hid,
-                                              smem, blockIdx.x * Shape<M, FP, H1, H2, AP, RT>::ROWS);
+                                              smem, (b0 + blockIdx.x) * Shape<M, FP, H1, H2, AP, RT>::ROWS);
 }
 
 // packed bf16 weights in MFMA fragment order: for output tile t (16 units) and k-step ks (32
@@ -83,7 +83,7 @@ __global__ void zero_f32_k(float* p, int n) {
 
 // AC: the action count compiled into the sampler (0: m.A at run time)
 template <int FP, int H1, int H2, int AP, int RT, int NW, int MINB, int TPW, bool DBG, int AC>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW * MINB / 4 > 0 ? NW * MINB / 4 : 1))) void policy_bf16_k(MlpParams m, const float* __restrict__ obs,
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW * MINB / 4 > 0 ? NW * MINB / 4 : 1))) void policy_bf16_k(MlpParams m, int b0, const float* __restrict__ obs,
                                                                const uint32_t* __restrict__ obs_bf,
                                                                const uint64_t* __restrict__ seedp, uint32_t step,
                                                                uint8_t* __restrict__ act,
@@ -93,14 +93,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW * MI
                                                                float* __restrict__ hid) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   policy_tile_bf16<FP, H1, H2, AP, RT, NW, TPW, DBG, AC>(m, obs, obs_bf, *seedp, step, act, logp, value,
-                                                       logits, hid, smem, blockIdx.x * (16 * RT));
+                                                       logits, hid, smem, (b0 + blockIdx.x) * (16 * RT));
 }
 
 template <bool DBG, int FP, int H1, int H2, int AP, int RT, int NW, int MINB, int TPW, int AC>
 hipError_t run_policy_bf16(const MlpParams& m, const float* obs, const uint32_t* obs_bf,
                            const uint64_t* seed, uint32_t step,
                            uint8_t* act, float* logp, float* value, float* logits, float* hid,
-                           hipStream_t st) {
+                           EnvPart part, hipStream_t st) {
   typedef BigShape<FP, H1, H2, AP, RT, NW> Sh;
   static_assert(Sh::LDS <= 160 * 1024, "LDS budget");
   if (AC > 0 && m.A != AC) return hipErrorInvalidValue;
@@ -112,8 +112,9 @@ hipError_t run_policy_bf16(const MlpParams& m, const float* obs, const uint32_t*
     if (e != hipSuccess) return e;
     attr = true;
   }
-  const dim3 grid((m.E + Sh::ROWS - 1) / Sh::ROWS), block(NW * 64);
-  hipLaunchKernelGGL(kern, grid, block, Sh::LDS, st, m, obs, obs_bf, seed, step, act, logp, value,
+  if (part.e0 % Sh::ROWS != 0) return hipErrorInvalidValue;
+  const dim3 grid((part.n + Sh::ROWS - 1) / Sh::ROWS), block(NW * 64);
+  hipLaunchKernelGGL(kern, grid, block, Sh::LDS, st, m, part.e0 / Sh::ROWS, obs, obs_bf, seed, step, act, logp, value,
                      logits, hid);
   return hipGetLastError();
 }
@@ -121,7 +122,7 @@ hipError_t run_policy_bf16(const MlpParams& m, const float* obs, const uint32_t*
 template <bool DBG, class M, int FP, int H1, int H2, int AP, int RT>
 hipError_t run_policy(const MlpParams& m, const float* obs, const uint64_t* seed, uint32_t step,
                       uint8_t* act, float* logp, float* value, float* logits, float* hid,
-                      hipStream_t st) {
+                      EnvPart part, hipStream_t st) {
   typedef Shape<M, FP, H1, H2, AP, RT> Sh;
   auto kern = policy_k<M, FP, H1, H2, AP, RT, DBG>;
   static bool attr = false;
@@ -131,8 +132,9 @@ hipError_t run_policy(const MlpParams& m, const float* obs, const uint64_t* seed
     if (e != hipSuccess) return e;
     attr = true;
   }
-  const dim3 grid((m.E + Sh::ROWS - 1) / Sh::ROWS), block(kThreads);
-  hipLaunchKernelGGL(kern, grid, block, Sh::LDS, st, m, obs, seed, step, act, logp, value, logits,
+  if (part.e0 % Sh::ROWS != 0) return hipErrorInvalidValue;
+  const dim3 grid((part.n + Sh::ROWS - 1) / Sh::ROWS), block(kThreads);
+  hipLaunchKernelGGL(kern, grid, block, Sh::LDS, st, m, part.e0 / Sh::ROWS, obs, seed, step, act, logp, value, logits,
                      hid);
   return hipGetLastError();
 }
@@ -178,15 +180,15 @@ template <bool DBG>
 static hipError_t launch_policy_t(const MlpParams& m, const float* obs, const uint32_t* obs_bf,
                                   const uint64_t* seed,
                                   uint32_t step, uint8_t* act, float* logp, float* value,
-                                  float* logits, float* hid, hipStream_t st) {
+                                  float* logits, float* hid, EnvPart part, hipStream_t st) {
   if (!m.bf16 && m.FP == 8 && m.H1 == 64 && m.H2 == 64 && m.AP == 16)
     return m.E <= kF32SmallE
-               ? run_policy<DBG, F32Mode, 8, 64, 64, 16, kF32SmallRT>(m, obs, seed, step, act, logp, value, logits, hid, st)
-               : run_policy<DBG, F32Mode, 8, 64, 64, 16, kF32RT>(m, obs, seed, step, act, logp, value, logits, hid, st);
+               ? run_policy<DBG, F32Mode, 8, 64, 64, 16, kF32SmallRT>(m, obs, seed, step, act, logp, value, logits, hid, part, st)
+               : run_policy<DBG, F32Mode, 8, 64, 64, 16, kF32RT>(m, obs, seed, step, act, logp, value, logits, hid, part, st);
   // bf16 shapes: 64-row tiles with 4 waves, two workgroups per CU, when there are enough
   // rows to fill the chip; 32-row tiles otherwise
   const bool big = m.E >= 64 * 512;
-#define BSIM_BF16_ARGS (m, obs, obs_bf, seed, step, act, logp, value, logits, hid, st)
+#define BSIM_BF16_ARGS (m, obs, obs_bf, seed, step, act, logp, value, logits, hid, part, st)
   if (m.bf16 && m.FP == 32 && m.H1 == 128 && m.H2 == 128 && m.AP == 16)
     return run_shape_bf16<DBG, 0>(m, big, [&](auto big_v, auto ac_v) {   // 6 measured slower
       constexpr bool B = decltype(big_v)::value;
@@ -221,11 +223,11 @@ static hipError_t launch_policy_t(const MlpParams& m, const float* obs, const ui
 
 hipError_t launch_policy(const MlpParams& m, const float* obs, const uint32_t* obs_bf,
                          const uint64_t* seed, uint32_t step, uint8_t* act, float* logp,
-                         float* value, float* logits, float* hidden, hipStream_t st) {
+                         float* value, float* logits, float* hidden, EnvPart part, hipStream_t st) {
   if (obs_bf && !m.bf16) return hipErrorInvalidValue;
   if (hidden)
-    return launch_policy_t<true>(m, obs, obs_bf, seed, step, act, logp, value, logits, hidden, st);
-  return launch_policy_t<false>(m, obs, obs_bf, seed, step, act, logp, value, logits, nullptr, st);
+    return launch_policy_t<true>(m, obs, obs_bf, seed, step, act, logp, value, logits, hidden, part, st);
+  return launch_policy_t<false>(m, obs, obs_bf, seed, step, act, logp, value, logits, nullptr, part, st);
 }
 
 hipError_t launch_repack(const MlpParams& m, const void* d_weights, const size_t off[6],

@@ -66,13 +66,20 @@ struct EnvState {
   uint64_t* seed;    // [1] the episode seed (written by reset_k, read by every kernel that draws)
 };
 
+// The environments e0 .. e0 + n - 1 that a launch covers: all of them, or one of a rollout's two
+// halves (e0 a multiple of kPartAlign, n too unless the part is the batch's last).
+struct EnvPart {
+  int e0, n;
+};
+constexpr int kPartAlign = 256;
+
 // Kernel launchers (asynchronous on `st`); each returns the launch's hipError_t.
 hipError_t launch_reset(const SimParams& p, const EnvState& s, uint64_t seed, hipStream_t st);
 // obs_mode: kObsF32 writes the current observation s.obs, kObsBf16 its bf16 pairs s.obs_bf
 constexpr int kObsF32 = 1, kObsBf16 = 2;
 hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
                        const uint8_t* act, float* obs_out, int obs_mode, double* rew,
-                       uint64_t* rchk, hipStream_t st);
+                       uint64_t* rchk, EnvPart part, hipStream_t st);
 // s.obs_bf from s.obs (feature pairs (2m, 2m + 1), a missing last feature as zero)
 hipError_t launch_obs_pack(const SimParams& p, const EnvState& s, hipStream_t st);
 // ticks k .. k + nt - 1 of the static shadow system; rew_sh [nt][E] or NULL
@@ -105,7 +112,7 @@ hipError_t launch_repack(const MlpParams& m, const void* d_weights, const size_t
 // of obs
 hipError_t launch_policy(const MlpParams& m, const float* obs, const uint32_t* obs_bf,
                          const uint64_t* seed, uint32_t step, uint8_t* act, float* logp,
-                         float* value, float* logits, float* hidden, hipStream_t st);
+                         float* value, float* logits, float* hidden, EnvPart part, hipStream_t st);
 hipError_t launch_init_weights(int F, int H1, int H2, int Ap, int bf16, uint64_t seed,
                                void* d_weights, const size_t off[6], hipStream_t st);
 
@@ -169,7 +176,7 @@ bool attn_shape_supported(const AttnParams& p);
 hipError_t launch_attn_policy(const AttnParams& p, const float* obs, const uint64_t* seed,
                               uint32_t step,
                               uint8_t* act, float* logp, float* value, float* logits,
-                              hipStream_t st);
+                              EnvPart part, hipStream_t st);
 // Minibatch gradient of the attention policy (REINFORCE with baseline or PPO): indices drawn
 // as for the MLP; grads in the order w_in, b_in, w_qkv, b_qkv, w_o, b_o, wp1, bp1, wp2, bp2,
 // wv1, bv1, wv2, bv2 (fp32); loss_out[4] total, policy, value, entropy (fp64); scratch of

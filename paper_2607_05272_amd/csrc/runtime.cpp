@@ -88,6 +88,9 @@ struct sim_ctx {
   // from and joined back to the rollout's stream by events
   hipStream_t sstream = nullptr;
   hipEvent_t sev_fork = nullptr, sev_join = nullptr;
+  // the second half's chain of a rollout in two halves
+  hipStream_t hstream = nullptr;
+  hipEvent_t hev_fork = nullptr, hev_join = nullptr;
   RolloutKey rkey{}, seen{};
   bool rkey_valid = false, seen_valid = false;
   int fuse = SIM_FUSE_AUTO;   // fused small-batch rollouts (sim_set_fused_rollout)
@@ -279,6 +282,34 @@ static void derive(sim_ctx* x) {
   a.Hp = c.mlp_h1; a.Hv = c.mlp_h2; a.A = 6 * c.n_servers; a.value_head = c.value_head;
 }
 
+// whether a per-tick rollout runs as two chains of launches, one per half of the batch. A tick waits
+// on its slowest wave with the rest of the chip idle, and its waves load, compute and store in
+// step; with two chains one half's policy runs beside the other's tick. It pays once the tick fills
+// the chip (more than one 64-lane wave per SIMD: 12-128-128-6 network, 100000 environments 36.3 ->
+// 33.2 us per tick; 32-256-256-24, 100000 61.7 -> 55.5, 262144 121.8 -> 118.9), and with three or
+// four request classes, whose ticks are longer, from 16384 environments (8 servers: 24000 47.2 ->
+// 44.6, 65536 61.5 -> 60.1, 100000 85.1 -> 76.6; 16 servers: 16384 61.5 -> 61.2, 65536 99.6 ->
+// 89.7, 262144 295 -> 285), with the attention policy from 131073 (262144 65.3 -> 56.5; 66000 41.8 ->
+// 41.9, 131072 46.3 -> 48.3). Below, two launches in a chain's place cost more (2 classes: 20000
+// 21.2 -> 23.0, 65536 28.8 -> 28.9; 4 classes: 8192 55.6 -> 56.5).
+constexpr int kHalvesE = 65536, kHalvesAttnE = 131072, kHalvesManyClassesE = 16384;
+static bool two_halves(const sim_ctx* x) {
+  const int E = x->cfg.n_envs;
+  if (x->cfg.policy_kind == SIM_POLICY_ATTN) return E > kHalvesAttnE;
+  return E > kHalvesE || (x->cfg.n_classes > 2 && E >= kHalvesManyClassesE);
+}
+
+// the second chain's stream and events
+static int second_chain(sim_ctx* x) {
+  if (!x->hstream)
+    HIPCHK(hipStreamCreateWithFlags(&x->hstream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
+  if (!x->hev_fork)
+    HIPCHK(hipEventCreateWithFlags(&x->hev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
+  if (!x->hev_join)
+    HIPCHK(hipEventCreateWithFlags(&x->hev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
+  return SIM_OK;
+}
+
 int sim_create(const sim_cfg* cfg, void* hip_stream, sim_ctx** out) {
   if (!out) return fail(SIM_EINVAL, "out is NULL");
   *out = nullptr;
@@ -361,6 +392,9 @@ int sim_create(const sim_cfg* cfg, void* hip_stream, sim_ctx** out) {
   x->m.b2 = reinterpret_cast<float*>(wp); wp += align256(4 * m.H2);
   x->m.w3 = wp; wp += align256(eb * m.AP * m.H2);
   x->m.b3 = reinterpret_cast<float*>(wp);
+  // made here rather than by the first rollout, which a caller may be capturing; a rollout
+  // without them runs as one chain
+  if (two_halves(x)) (void)second_chain(x);
   *out = x;
   return SIM_OK;
 }
@@ -390,6 +424,12 @@ int sim_destroy(sim_ctx* x) {
   }
   if (x->sev_fork) (void)hipEventDestroy(x->sev_fork);
   if (x->sev_join) (void)hipEventDestroy(x->sev_join);
+  if (x->hstream) {
+    (void)hipStreamSynchronize(x->hstream);
+    (void)hipStreamDestroy(x->hstream);
+  }
+  if (x->hev_fork) (void)hipEventDestroy(x->hev_fork);
+  if (x->hev_join) (void)hipEventDestroy(x->hev_join);
   delete x;
   return SIM_OK;
 }
@@ -429,10 +469,13 @@ int sim_obs(sim_ctx* x, float* d_obs) {
 }
 
 // the learned system's tick and, if `shadow`, the static system's
+static EnvPart whole(const sim_ctx* x) { return EnvPart{0, x->cfg.n_envs}; }
+
 static int enqueue_tick(sim_ctx* x, uint32_t k, const uint8_t* act, float* obs_out, double* rew,
-                        double* rew_sh, uint64_t* rchk, bool shadow, int obs_mode = kObsF32) {
+                        double* rew_sh, uint64_t* rchk, bool shadow, EnvPart part,
+                        int obs_mode = kObsF32) {
   HIPCHK(x->timed(SIM_KC_STEP, [&] {
-           return launch_step(x->p, x->s, k, act, obs_out, obs_mode, rew, rchk, x->stream);
+           return launch_step(x->p, x->s, k, act, obs_out, obs_mode, rew, rchk, part, x->stream);
          }), "step kernel launch");
   if (shadow && x->cfg.shadow)
     HIPCHK(x->timed(SIM_KC_STATIC, [&] {
@@ -464,7 +507,8 @@ int sim_step(sim_ctx* x, const uint8_t* d_actions, float* d_obs_next, double* d_
   if (!x || !d_actions) return fail(SIM_EINVAL, "NULL argument");
   if (!x->reset_done) return fail(SIM_ESTATE, "sim_step before sim_reset");
   if (x->tick == 0xFFFFFFFEu) return fail(SIM_ESTATE, "tick counter exhausted");
-  int rc = enqueue_tick(x, x->tick, d_actions, d_obs_next, d_reward, d_reward_shadow, nullptr, true);
+  int rc = enqueue_tick(x, x->tick, d_actions, d_obs_next, d_reward, d_reward_shadow, nullptr, true,
+                        whole(x));
   if (rc) return rc;
   x->tick++;
   return SIM_OK;
@@ -600,11 +644,13 @@ static int prepare_policy(sim_ctx* x, const void* d_weights) {
 // the policy kernel of the configured network (after prepare_policy)
 static hipError_t policy_launch(sim_ctx* x, const float* obs, uint32_t step, uint8_t* act,
                                 float* logp, float* value, float* logits,
-                                float* hidden = nullptr, const uint32_t* obs_bf = nullptr) {
+                                EnvPart part, float* hidden = nullptr,
+                                const uint32_t* obs_bf = nullptr) {
   if (x->cfg.policy_kind == SIM_POLICY_ATTN)
-    return launch_attn_policy(x->a, obs, x->s.seed, step, act, logp, value, logits, x->stream);
+    return launch_attn_policy(x->a, obs, x->s.seed, step, act, logp, value, logits, part,
+                              x->stream);
   return launch_policy(x->m, obs, obs_bf, x->s.seed, step, act, logp, value, logits, hidden,
-                       x->stream);
+                       part, x->stream);
 }
 
 int sim_policy(sim_ctx* x, const void* d_weights, const float* d_obs, uint32_t step,
@@ -614,7 +660,7 @@ int sim_policy(sim_ctx* x, const void* d_weights, const float* d_obs, uint32_t s
   int rc = prepare_policy(x, d_weights);
   if (rc) return rc;
   HIPCHK(x->timed(SIM_KC_POLICY, [&] {
-           return policy_launch(x, d_obs, step, d_act, d_logp, d_value, d_logits);
+           return policy_launch(x, d_obs, step, d_act, d_logp, d_value, d_logits, whole(x));
          }), "policy kernel launch");
   return SIM_OK;
 }
@@ -629,7 +675,8 @@ int sim_policy_hidden(sim_ctx* x, const void* d_weights, const float* d_obs, uin
   int rc = prepare_policy(x, d_weights);
   if (rc) return rc;
   HIPCHK(x->timed(SIM_KC_POLICY, [&] {
-           return policy_launch(x, d_obs, step, d_act, d_logp, d_value, d_logits, d_hidden);
+           return policy_launch(x, d_obs, step, d_act, d_logp, d_value, d_logits, whole(x),
+                                d_hidden);
          }), "policy kernel launch");
   return SIM_OK;
 }
@@ -646,6 +693,14 @@ static bool use_fused(sim_ctx* x) {
   if (x->fuse_plan.cap == 0) return false;
   return x->fuse == SIM_FUSE_ON || x->cfg.n_envs <= x->fuse_plan.cap;
 }
+
+// x->stream set to another stream for a scope
+struct OnStream {
+  sim_ctx* x;
+  hipStream_t old;
+  OnStream(sim_ctx* c, hipStream_t st) : x(c), old(c->stream) { x->stream = st; }
+  ~OnStream() { x->stream = old; }
+};
 
 // Every launch of a rollout of T ticks from tick k0 on x->stream: the policy's weight repack,
 // the static shadow system in multi-tick launches, then per tick the policy and the learned
@@ -695,26 +750,50 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
   if (obs_bf)
     HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
            "observation packing launch");
-  for (int32_t i = 0; i < T; ++i) {
+  EnvPart parts[2] = {whole(x), {0, 0}};
+  // (with per-launch timing on, one chain, so that each kernel's duration is its own)
+  const int chains = two_halves(x) && x->hev_join && !x->timing ? 2 : 1;
+  hipStream_t streams[2] = {x->stream, x->hstream};
+  if (chains == 2) {
+    const int n0 = (x->cfg.n_envs / 2 + kPartAlign - 1) / kPartAlign * kPartAlign;
+    parts[0] = {0, n0};
+    parts[1] = {n0, x->cfg.n_envs - n0};
+  }
+  for (int32_t i = 0; i <= T; ++i) {
     const size_t row = (size_t)i * E;
     const uint32_t k = k0 + (uint32_t)i;
-    HIPCHK(x->timed(SIM_KC_POLICY, [&] {
-             return policy_launch(x, x->s.obs, k, tr->actions + row,
-                                  tr->logp ? tr->logp + row : nullptr,
-                                  tr->value ? tr->value + row : nullptr, nullptr, nullptr,
-                                  obs_bf);
-           }), "policy kernel launch");
-    const int mode = !obs_bf ? kObsF32 : i + 1 < T ? kObsBf16 : kObsF32 | kObsBf16;
-    rc = enqueue_tick(x, k, tr->actions + row, tr->obs ? tr->obs + (size_t)(i + 1) * F * E : nullptr,
-                      tr->reward ? tr->reward + row : nullptr, nullptr,
-                      tr->rchk ? tr->rchk + row : nullptr, false, mode);
-    if (rc) return rc;
+    if (i == T && !tr->value) break;
+    for (int h = 0; h < chains; ++h) {
+      OnStream on(x, streams[h]);
+      if (i == T) {
+        HIPCHK(x->timed(SIM_KC_POLICY, [&] {
+                 return policy_launch(x, x->s.obs, k, nullptr, nullptr, tr->value + row, nullptr,
+                                      parts[h], nullptr, obs_bf);
+               }), "policy kernel launch (final value)");
+        continue;
+      }
+      HIPCHK(x->timed(SIM_KC_POLICY, [&] {
+               return policy_launch(x, x->s.obs, k, tr->actions + row,
+                                    tr->logp ? tr->logp + row : nullptr,
+                                    tr->value ? tr->value + row : nullptr, nullptr, parts[h],
+                                    nullptr, obs_bf);
+             }), "policy kernel launch");
+      // the second chain starts when the first one's policy is done, a policy behind it
+      if (chains == 2 && i == 0 && h == 0) {
+        HIPCHK(hipEventRecord(x->hev_fork, streams[0]), "hipEventRecord");
+        HIPCHK(hipStreamWaitEvent(streams[1], x->hev_fork, 0), "hipStreamWaitEvent");
+      }
+      const int mode = !obs_bf ? kObsF32 : i + 1 < T ? kObsBf16 : kObsF32 | kObsBf16;
+      rc = enqueue_tick(x, k, tr->actions + row, tr->obs ? tr->obs + (size_t)(i + 1) * F * E : nullptr,
+                        tr->reward ? tr->reward + row : nullptr, nullptr,
+                        tr->rchk ? tr->rchk + row : nullptr, false, parts[h], mode);
+      if (rc) return rc;
+    }
   }
-  if (tr->value)
-    HIPCHK(x->timed(SIM_KC_POLICY, [&] {
-             return policy_launch(x, x->s.obs, k0 + (uint32_t)T, nullptr, nullptr,
-                                  tr->value + (size_t)T * E, nullptr, nullptr, obs_bf);
-           }), "policy kernel launch (final value)");
+  if (chains == 2) {
+    HIPCHK(hipEventRecord(x->hev_join, streams[1]), "hipEventRecord");
+    HIPCHK(hipStreamWaitEvent(x->stream, x->hev_join, 0), "hipStreamWaitEvent");
+  }
   if (side) HIPCHK(hipStreamWaitEvent(x->stream, x->sev_join, 0), "hipStreamWaitEvent");
   return SIM_OK;
 }

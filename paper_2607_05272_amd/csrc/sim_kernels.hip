@@ -9,13 +9,13 @@ namespace {
 // ---- learned system: one tick per launch ----------------------------------------------------
 template <int CM, bool PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PF ? 1 : 4))) void learned_k(
-    SimParams p, EnvState g, uint32_t k, int lpw, const uint8_t* __restrict__ act,
+    SimParams p, EnvState g, uint32_t k, int b0, int lpw, const uint8_t* __restrict__ act,
     float* __restrict__ obs_out, int obs_mode, double* __restrict__ rew,
     uint64_t* __restrict__ rchk) {
   __shared__ Stage<kStageLearned> stage[4];
   // wave w owns environments w * lpw .. + lpw - 1 in its first lpw lanes (lanes_per_wave);
   // the episode seed was written by reset_k
-  learned_tick<CM, PF>(p, g, *g.seed, k, (blockIdx.x * 4 + (threadIdx.x >> 6)) * lpw, lpw,
+  learned_tick<CM, PF>(p, g, *g.seed, k, ((b0 + blockIdx.x) * 4 + (threadIdx.x >> 6)) * lpw, lpw,
                        stage[threadIdx.x >> 6], act, obs_out, obs_mode, rew, rchk);
 }
 
@@ -597,32 +597,34 @@ hipError_t launch_reset(const SimParams& p, const EnvState& s, uint64_t seed, hi
 }
 
 template <bool PF>
-void launch_learned(const SimParams& p, const EnvState& s, uint32_t k, int lpw, dim3 grid,
+void launch_learned(const SimParams& p, const EnvState& s, uint32_t k, int b0, int lpw, dim3 grid,
                     const uint8_t* act, float* obs_out, int obs_mode, double* rew,
                     uint64_t* rchk, hipStream_t st) {
   const dim3 block(256);
   if (p.C <= 1)
-    hipLaunchKernelGGL((learned_k<1, PF>), grid, block, 0, st, p, s, k, lpw, act, obs_out, obs_mode, rew, rchk);
+    hipLaunchKernelGGL((learned_k<1, PF>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
   else if (p.C <= 2)
-    hipLaunchKernelGGL((learned_k<2, PF>), grid, block, 0, st, p, s, k, lpw, act, obs_out, obs_mode, rew, rchk);
+    hipLaunchKernelGGL((learned_k<2, PF>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
   else
-    hipLaunchKernelGGL((learned_k<4, PF>), grid, block, 0, st, p, s, k, lpw, act, obs_out, obs_mode, rew, rchk);
+    hipLaunchKernelGGL((learned_k<4, PF>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
 }
 
 hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
                        const uint8_t* act, float* obs_out, int obs_mode, double* rew,
-                       uint64_t* rchk, hipStream_t st) {
+                       uint64_t* rchk, EnvPart part, hipStream_t st) {
   if ((obs_mode & kObsBf16) && !s.obs_bf) return hipErrorInvalidValue;
   const int lpw = lanes_per_wave(p.E);
   const int waves = (p.E + lpw - 1) / lpw;
-  const dim3 grid((waves + 3) / 4);
+  if (part.e0 % (4 * lpw) != 0) return hipErrorInvalidValue;
+  const int b0 = part.e0 / (4 * lpw);
+  const dim3 grid((part.n + 4 * lpw - 1) / (4 * lpw));
   // early end-of-tick reads (and no register limit) while a SIMD has at most two waves: 20000
   // environments with 8 servers, 1250 waves, 36.5 us per tick against 37.0; two waves of the
   // unlimited kernel are all that fit a SIMD
   if (waves <= 2 * kFillWaves && p.K <= kEndChunk)
-    launch_learned<true>(p, s, k, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
+    launch_learned<true>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
   else
-    launch_learned<false>(p, s, k, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
+    launch_learned<false>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
   return hipGetLastError();
 }
 

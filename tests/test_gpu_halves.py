@@ -1,0 +1,40 @@
+"""Per-tick rollouts in two chains of launches, one per half of the batch, against one chain of the
+whole batch (per-launch timing on) bit for bit: just past each size from which the halves are
+taken, with a ragged last tile in the second half, for every policy kernel, with the value
+row, stored observations and the static shadow system beside them; run eagerly, then captured
+and replayed with other work on the caller's stream between the replays."""
+import pytest
+
+from test_gpu_fused import assert_same, bs, snapshot, weights  # noqa: F401
+from workloads import preset
+from workloads.presets import attn_preset
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    ("C1", {}, 65537, 4), ("C2", dict(value_head=1), 65793, 3), ("C3", {}, 65599, 3),
+    ("C4", {}, 16384, 3), ("C4", {}, 16385, 3), ("C5", {}, 16700, 3), ("attn", {}, 131073, 2),
+]
+
+
+@pytest.mark.parametrize("name,kw,E,T", CASES)
+def test_rollout_in_halves_matches_one_chain(bs, name, kw, E, T):  # noqa: F811
+    w = attn_preset(**kw) if name == "attn" else preset(name, **kw)
+    ref = []
+    for one_chain in (True, False):
+        with bs.Sim(w, n_envs=E) as sim:
+            sim.set_fused_rollout(bs.FUSE_OFF)
+            sim.set_timing(one_chain)
+            wb = sim.init_weights(7) if name == "attn" else sim.upload_weights(weights(w, 21))
+            tr = None
+            for i in range(1 if one_chain else 4):
+                sim.reset(0xF0 + E)
+                tr = sim.rollout(wb, T, store_obs=True, rchk=True, traj=tr)
+                out = snapshot(sim, tr)
+                if one_chain:
+                    ref = out
+                else:
+                    assert_same(ref, out, f"{name} {kw} E={E}, call {i}")
+                    tr.actions.zero_()   # other work between the replays
+            assert one_chain or sim.graph_stats()[1] > 0
