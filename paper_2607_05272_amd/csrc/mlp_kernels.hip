@@ -21,46 +21,55 @@ __global__ __launch_bounds__(kThreads) void policy_k(MlpParams m, int b0, const 
                                               smem, (b0 + blockIdx.x) * Shape<M, FP, H1, H2, AP, RT>::ROWS);
 }
 
+// The three layers' weights and biases in one launch (three took 2.4 us each, most of a call to
+// the policy with a thousand environments: 18.3 us, and 12.3 with one): the blocks from blk0 on
+// belong to the layer.
+struct RepackLayer {
+  const unsigned char* w_src;   // [K][N]
+  const float* b_src;           // [N]
+  void* w;                      // padded to Kp inputs, Np units
+  float* b;
+  int K, N, Kp, Np, blk0;
+};
+struct RepackArgs {
+  RepackLayer l[3];
+};
+__device__ __forceinline__ const RepackLayer& repack_layer(const RepackArgs& a) {
+  const int blk = blockIdx.x;
+  return blk >= a.l[2].blk0 ? a.l[2] : blk >= a.l[1].blk0 ? a.l[1] : a.l[0];
+}
+
 // packed bf16 weights in MFMA fragment order: for output tile t (16 units) and k-step ks (32
 // inputs), the 64 lanes' 16-byte A fragments lie back to back, lane = kq*16 + r16 holding
 // W[ks*32 + kq*8 + j][t*16 + r16], j = 0..7 (zero padded). A wave's load of one fragment is
-// one contiguous kilobyte, and consecutive k-steps of a tile are consecutive kilobytes.
-__global__ void repack_frag_k(const unsigned char* __restrict__ src, size_t woff, size_t boff,
-                              int K, int N, int KS, int NTp, uint16_t* __restrict__ w,
-                              float* __restrict__ b) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t total = (size_t)NTp * KS * 512;
-  if (idx < total) {
-    const int t = (int)(idx / ((size_t)KS * 512));
-    const int rem = (int)(idx % ((size_t)KS * 512));
-    const int ks = rem / 512, l = (rem % 512) / 8, j = rem % 8;
-    const int n = t * 16 + (l & 15), k = ks * 32 + (l >> 4) * 8 + j;
-    uint16_t v = 0;
-    if (n < N && k < K) v = reinterpret_cast<const uint16_t*>(src + woff)[(size_t)k * N + n];
-    w[idx] = v;
+// one contiguous kilobyte, and consecutive k-steps of a tile are consecutive kilobytes. One
+// fragment lane per thread.
+__global__ __launch_bounds__(256) void repack_frag_k(RepackArgs args) {
+  const RepackLayer& r = repack_layer(args);
+  const int idx = (int)(blockIdx.x - r.blk0) * 256 + (int)threadIdx.x;
+  if (idx < r.Np * r.Kp / 8) {
+    const int l = idx % 64, ks = idx / 64 % (r.Kp / 32), t = idx / 64 / (r.Kp / 32);
+    const int n = t * 16 + (l & 15), k = ks * 32 + (l >> 4) * 8;
+    const uint16_t* src = reinterpret_cast<const uint16_t*>(r.w_src);
+    uint32_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = n < r.N && k + j < r.K ? src[(size_t)(k + j) * r.N + n] : 0u;
+    static_cast<uint4*>(r.w)[idx] = uint4{v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16,
+                                          v[6] | v[7] << 16};
   }
-  if (idx < (size_t)NTp * 16) {
-    const int n = (int)idx;
-    b[n] = n < N ? reinterpret_cast<const float*>(src + boff)[n] : 0.f;
-  }
+  if (idx < r.Np) r.b[idx] = idx < r.N ? r.b_src[idx] : 0.f;
 }
 
-// packed fp32 weights: W^T [Npad][Kpad], zero padded; bias fp32 [Npad]
-template <typename T>
-__global__ void repack_k(const unsigned char* __restrict__ src, size_t woff, size_t boff, int K,
-                         int N, int Kp, int Np, T* __restrict__ w, float* __restrict__ b) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t total = (size_t)Np * Kp;
-  if (idx < total) {
-    const int n = (int)(idx / Kp), k = (int)(idx % Kp);
-    T v = T(0);
-    if (n < N && k < K) v = reinterpret_cast<const T*>(src + woff)[(size_t)k * N + n];
-    w[idx] = v;
+// packed fp32 weights: W^T [Np][Kp], zero padded; bias fp32 [Np]
+__global__ __launch_bounds__(256) void repack_f32_k(RepackArgs args) {
+  const RepackLayer& r = repack_layer(args);
+  const int idx = (int)(blockIdx.x - r.blk0) * 256 + (int)threadIdx.x;
+  if (idx < r.Np * r.Kp) {
+    const int n = idx / r.Kp, k = idx % r.Kp;
+    static_cast<float*>(r.w)[idx] =
+        n < r.N && k < r.K ? reinterpret_cast<const float*>(r.w_src)[(size_t)k * r.N + n] : 0.f;
   }
-  if (idx < (size_t)Np) {
-    const int n = (int)idx;
-    b[n] = n < N ? reinterpret_cast<const float*>(src + boff)[n] : 0.f;
-  }
+  if (idx < r.Np) r.b[idx] = idx < r.N ? r.b_src[idx] : 0.f;
 }
 
 // Xavier-uniform: element i of layer l takes u from the WEIGHTS block at counter
@@ -238,19 +247,18 @@ hipError_t launch_repack(const MlpParams& m, const void* d_weights, const size_t
   const int Kp[3] = {m.FP, m.H1, m.H2}, Np[3] = {m.H1, m.H2, m.AP};
   void* ws[3] = {w1, w2, w3};
   float* bs[3] = {b1, b2, b3};
+  RepackArgs args;
+  int blocks = 0;
   for (int l = 0; l < 3; ++l) {
-    const size_t total = (size_t)Np[l] * Kp[l];
-    const dim3 grid((unsigned)((total + 255) / 256));
-    if (m.bf16)
-      hipLaunchKernelGGL(repack_frag_k, grid, dim3(256), 0, st, src, off[2 * l], off[2 * l + 1],
-                         Ks[l], Ns[l], Kp[l] / 32, Np[l] / 16, static_cast<uint16_t*>(ws[l]), bs[l]);
-    else
-      hipLaunchKernelGGL(repack_k<float>, grid, dim3(256), 0, st, src, off[2 * l], off[2 * l + 1],
-                         Ks[l], Ns[l], Kp[l], Np[l], static_cast<float*>(ws[l]), bs[l]);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    args.l[l] = RepackLayer{src + off[2 * l], reinterpret_cast<const float*>(src + off[2 * l + 1]),
+                            ws[l], bs[l], Ks[l], Ns[l], Kp[l], Np[l], blocks};
+    // a thread per fragment lane of 8 weights, or per weight (more than there are biases: Kp >= 8)
+    const int items = m.bf16 ? Np[l] * Kp[l] / 8 : Np[l] * Kp[l];
+    blocks += (items + 255) / 256;
   }
-  return hipSuccess;
+  if (m.bf16) hipLaunchKernelGGL(repack_frag_k, dim3(blocks), dim3(256), 0, st, args);
+  else hipLaunchKernelGGL(repack_f32_k, dim3(blocks), dim3(256), 0, st, args);
+  return hipGetLastError();
 }
 
 hipError_t launch_init_weights(int F, int H1, int H2, int Ap, int bf16, uint64_t seed,
