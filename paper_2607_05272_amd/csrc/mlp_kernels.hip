@@ -174,16 +174,29 @@ bool policy_shape_supported(const MlpParams& m) {
 
 // One bf16 shape: the configurations' own action count AC0 for that width (6K of their K)
 // compiled into the sampler, any other with run-time bounds (the diagnostic instantiation
-// always takes the run-time bounds; AC0 = 0 compiles none). run(big, ac) launches the variant.
+// always takes the run-time bounds; AC0 = 0 compiles none). run(ac) launches the variant.
 template <bool DBG, int AC0, class Run>
-static hipError_t run_shape_bf16(const MlpParams& m, bool big, Run&& run) {
-  typedef std::integral_constant<bool, true> T;
-  typedef std::integral_constant<bool, false> F;
+static hipError_t run_shape_bf16(const MlpParams& m, Run&& run) {
   typedef std::integral_constant<int, 0> A0;
   typedef std::integral_constant<int, DBG ? 0 : AC0> AC;
-  if (!DBG && AC0 > 0 && m.A == AC0) return big ? run(T{}, AC{}) : run(F{}, AC{});
-  return big ? run(T{}, A0{}) : run(F{}, A0{});
+  return !DBG && AC0 > 0 && m.A == AC0 ? run(AC{}) : run(A0{});
 }
+
+// Rows per workgroup (of eight waves) of the bf16 policies, by the batch. A tile's chain of
+// layers is what a small batch's launch lasts, and eight waves on 16 rows make it shortest (us at
+// 1024 and 8192 environments, against 32-row tiles of four waves: 12-128-128-6 5.0 and 5.4, 5.6
+// and 5.8; 32-256-256-24 6.6 and 8.1, 10.5 and 10.9; 64-256-256-48 6.9 and 8.7, 12.2 and 12.4;
+// 96-512-512-96 at 1024 and 4096 15.2 and 16.1, 41.8 and 42.2): up to two tiles per CU, of the 512-wide
+// network, whose weights every tile reads anew, up to one. Large batches read the weights least
+// often in 64-row tiles (at 28032, against 32 rows: 7.1, 8.0; 12.1, 13.1; 13.9, 15.7; 29.8, 38.8), and
+// between the two 32 rows are best, up to three tiles per CU (at 16384, against 64 rows: 5.8, 6.6; in a
+// rollout of 20000, per tick 29.2, 30.4) or one of the 512-wide network (8192 in a rollout: 46.5,
+// 49.1; at 12032 the other way round, 20.3, 19.1).
+struct Bf16Rows {
+  int small_e, mid_e;
+};
+constexpr Bf16Rows kRows128{2 * 256 * 16, 3 * 256 * 32}, kRows256 = kRows128,
+    kRows512{256 * 16, 256 * 32};
 
 template <bool DBG>
 static hipError_t launch_policy_t(const MlpParams& m, const float* obs, const uint32_t* obs_bf,
@@ -194,37 +207,34 @@ static hipError_t launch_policy_t(const MlpParams& m, const float* obs, const ui
     return m.E <= kF32SmallE
                ? run_policy<DBG, F32Mode, 8, 64, 64, 16, kF32SmallRT>(m, obs, seed, step, act, logp, value, logits, hid, part, st)
                : run_policy<DBG, F32Mode, 8, 64, 64, 16, kF32RT>(m, obs, seed, step, act, logp, value, logits, hid, part, st);
-  // bf16 shapes: 64-row tiles with 4 waves, two workgroups per CU, when there are enough
-  // rows to fill the chip; 32-row tiles otherwise
-  const bool big = m.E >= 64 * 512;
 #define BSIM_BF16_ARGS (m, obs, obs_bf, seed, step, act, logp, value, logits, hid, part, st)
   if (m.bf16 && m.FP == 32 && m.H1 == 128 && m.H2 == 128 && m.AP == 16)
-    return run_shape_bf16<DBG, 0>(m, big, [&](auto big_v, auto ac_v) {   // 6 measured slower
-      constexpr bool B = decltype(big_v)::value;
+    return run_shape_bf16<DBG, 0>(m, [&](auto ac_v) {   // 6 measured slower
       constexpr int C = decltype(ac_v)::value;
-      return B ? run_policy_bf16<DBG, 32, 128, 128, 16, 4, 8, 2, 1, C> BSIM_BF16_ARGS
-               : run_policy_bf16<DBG, 32, 128, 128, 16, 2, 4, 2, 1, C> BSIM_BF16_ARGS;
+      return m.E <= kRows128.small_e ? run_policy_bf16<DBG, 32, 128, 128, 16, 1, 8, 1, 1, C> BSIM_BF16_ARGS
+             : m.E <= kRows128.mid_e ? run_policy_bf16<DBG, 32, 128, 128, 16, 2, 8, 1, 1, C> BSIM_BF16_ARGS
+                                    : run_policy_bf16<DBG, 32, 128, 128, 16, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
     });
   if (m.bf16 && m.FP == 32 && m.H1 == 256 && m.H2 == 256 && m.AP == 32)
-    return run_shape_bf16<DBG, 24>(m, big, [&](auto big_v, auto ac_v) {
-      constexpr bool B = decltype(big_v)::value;
+    return run_shape_bf16<DBG, 24>(m, [&](auto ac_v) {
       constexpr int C = decltype(ac_v)::value;
-      return B ? run_policy_bf16<DBG, 32, 256, 256, 32, 4, 8, 2, 1, C> BSIM_BF16_ARGS
-               : run_policy_bf16<DBG, 32, 256, 256, 32, 2, 4, 2, 1, C> BSIM_BF16_ARGS;
+      return m.E <= kRows256.small_e ? run_policy_bf16<DBG, 32, 256, 256, 32, 1, 8, 1, 1, C> BSIM_BF16_ARGS
+             : m.E <= kRows256.mid_e ? run_policy_bf16<DBG, 32, 256, 256, 32, 2, 8, 1, 1, C> BSIM_BF16_ARGS
+                                    : run_policy_bf16<DBG, 32, 256, 256, 32, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
     });
   if (m.bf16 && m.FP == 64 && m.H1 == 256 && m.H2 == 256 && m.AP == 64)
-    return run_shape_bf16<DBG, 48>(m, big, [&](auto big_v, auto ac_v) {
-      constexpr bool B = decltype(big_v)::value;
+    return run_shape_bf16<DBG, 48>(m, [&](auto ac_v) {
       constexpr int C = decltype(ac_v)::value;
-      return B ? run_policy_bf16<DBG, 64, 256, 256, 64, 4, 8, 2, 1, C> BSIM_BF16_ARGS
-               : run_policy_bf16<DBG, 64, 256, 256, 64, 2, 4, 2, 1, C> BSIM_BF16_ARGS;
+      return m.E <= kRows256.small_e ? run_policy_bf16<DBG, 64, 256, 256, 64, 1, 8, 1, 1, C> BSIM_BF16_ARGS
+             : m.E <= kRows256.mid_e ? run_policy_bf16<DBG, 64, 256, 256, 64, 2, 8, 1, 1, C> BSIM_BF16_ARGS
+                                    : run_policy_bf16<DBG, 64, 256, 256, 64, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
     });
   if (m.bf16 && m.FP == 96 && m.H1 == 512 && m.H2 == 512 && m.AP == 112)
-    return run_shape_bf16<DBG, 96>(m, big, [&](auto big_v, auto ac_v) {
-      constexpr bool B = decltype(big_v)::value;
+    return run_shape_bf16<DBG, 96>(m, [&](auto ac_v) {
       constexpr int C = decltype(ac_v)::value;
-      return B ? run_policy_bf16<DBG, 96, 512, 512, 112, 4, 8, 2, 2, C> BSIM_BF16_ARGS
-               : run_policy_bf16<DBG, 96, 512, 512, 112, 2, 4, 2, 1, C> BSIM_BF16_ARGS;
+      return m.E <= kRows512.small_e ? run_policy_bf16<DBG, 96, 512, 512, 112, 1, 8, 1, 1, C> BSIM_BF16_ARGS
+             : m.E <= kRows512.mid_e ? run_policy_bf16<DBG, 96, 512, 512, 112, 2, 8, 1, 1, C> BSIM_BF16_ARGS
+                                    : run_policy_bf16<DBG, 96, 512, 512, 112, 4, 8, 2, 2, C> BSIM_BF16_ARGS;
     });
 #undef BSIM_BF16_ARGS
   return hipErrorInvalidValue;

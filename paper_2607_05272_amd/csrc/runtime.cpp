@@ -287,16 +287,17 @@ static void derive(sim_ctx* x) {
 // step; with two chains one half's policy runs beside the other's tick. It pays once the tick fills
 // the chip (more than one 64-lane wave per SIMD: 12-128-128-6 network, 100000 environments 36.3 ->
 // 33.2 us per tick; 32-256-256-24, 100000 61.7 -> 55.5, 262144 121.8 -> 118.9), and with three or
-// four request classes, whose ticks are longer, from 16384 environments (8 servers: 24000 47.2 ->
-// 44.6, 65536 61.5 -> 60.1, 100000 85.1 -> 76.6; 16 servers: 16384 61.5 -> 61.2, 65536 99.6 ->
-// 89.7, 262144 295 -> 285), with the attention policy from 131073 (262144 65.3 -> 56.5; 66000 41.8 ->
-// 41.9, 131072 46.3 -> 48.3). Below, two launches in a chain's place cost more (2 classes: 20000
-// 21.2 -> 23.0, 65536 28.8 -> 28.9; 4 classes: 8192 55.6 -> 56.5).
+// four request classes, whose ticks are longer, from 16385 environments, where the waves pass one
+// per SIMD (8 servers: 17000 44.0 -> 43.4, 24000 46.3 -> 43.5, 65536 61.5 -> 58.7, 100000 85.1 ->
+// 76.6; 16 servers: 17000 59.5 -> 54.3, 65536 100 -> 89.4, 262144 295 -> 285), with the attention
+// policy from 131073 (262144 65.3 -> 56.5; 66000 41.8 -> 41.9, 131072 46.3 -> 48.3). Below, two launches
+// in a chain's place cost more (2 classes: 20000 21.2 -> 23.0, 65536 28.8 -> 28.9; 4 classes: 8192 46.2
+// -> 47.3, 16384 51.5 -> 53.3).
 constexpr int kHalvesE = 65536, kHalvesAttnE = 131072, kHalvesManyClassesE = 16384;
 static bool two_halves(const sim_ctx* x) {
   const int E = x->cfg.n_envs;
   if (x->cfg.policy_kind == SIM_POLICY_ATTN) return E > kHalvesAttnE;
-  return E > kHalvesE || (x->cfg.n_classes > 2 && E >= kHalvesManyClassesE);
+  return E > kHalvesE || (x->cfg.n_classes > 2 && E > kHalvesManyClassesE);
 }
 
 // the second chain's stream and events
