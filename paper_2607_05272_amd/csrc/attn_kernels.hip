@@ -1,6 +1,6 @@
 // attn_kernels.hip -- the attention policy of paper Sec. 4.2, fused with action sampling.
 //
-// Per environment (one lane each), fp32:
+// Per environment, fp32 (one lane each, or eight in small batches):
 //   tokens    e_g = b_in + sum over the features i of group g of x_i W_in[i,:], the F features
 //             split into L contiguous groups of F/L (L = 1 is the plain input projection,
 //             L = F one token per state feature);
@@ -179,9 +179,202 @@ __global__ __launch_bounds__(kBlock) void attn_policy_k(AttnParams p, int b0, co
   }
 }
 
+__device__ __forceinline__ void wave_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The same policy with eight lanes per environment, for batches that leave most SIMDs without a wave
+// at one lane each: lane g holds token g, every eighth unit of the heads and every eighth output
+// (the value is output A). Every sum is taken by one lane in the one-lane kernel's order, from
+// operands that the lanes pass through LDS, so the results are its bits. One wave per workgroup, so
+// that no barrier is needed; a head's units run in chunks of kChunk. Bound by one environment's chain
+// (22 us in one lane, most of it the heads' 128 erff; 7.4 us in eight), then by issue: about as
+// many instructions per environment as the one-lane kernel, whose weights are scalar loads.
+constexpr int kLanes = 8, kEnvs = 64 / kLanes, kChunk = 64;
+template <int L, int NH, int A>
+__global__ __launch_bounds__(64) void attn_policy8_k(AttnParams p, int b0, const float* __restrict__ obs,
+                                                     const uint64_t* __restrict__ seedp, uint32_t step,
+                                                     uint8_t* __restrict__ act,
+                                                     float* __restrict__ logp,
+                                                     float* __restrict__ value,
+                                                     float* __restrict__ logits) {
+  static_assert(L <= kLanes, "a token per lane");
+  constexpr int DH = kD / NH, NO = (A + kLanes) / kLanes;   // outputs per lane, the value among them
+  constexpr float kLog2e = 1.4426950408889634f;
+  const float qscale = (DH == 1 ? 1.0f : DH == 2 ? 0.70710678118654752f : 0.5f) * kLog2e;
+  __shared__ __attribute__((aligned(16))) float kv[kEnvs][kLanes][2 * kD], ys[kEnvs][kLanes][kD];
+  __shared__ __attribute__((aligned(16))) float hid[2][kEnvs][kChunk + 4];
+  __shared__ float lgs[kEnvs][A + 1], exs[kEnvs][A + 1];
+  const int lane = threadIdx.x, el = lane / kLanes, g = lane % kLanes;
+  const int e = (b0 + blockIdx.x) * kEnvs + el;
+  const bool live = e < p.E;
+  const size_t E = (size_t)p.E, ee = live ? e : 0;
+  const int G = p.F / L;
+
+  // the lane's token, its query, key and value
+  float tok[kD], q[kD];
+#pragma unroll
+  for (int d = 0; d < kD; ++d) tok[d] = p.b_in[d];
+  if (g < L)
+    for (int i = g * G; i < (g + 1) * G; ++i) {
+      const float x = obs[(size_t)i * E + ee];
+#pragma unroll
+      for (int d = 0; d < kD; ++d) tok[d] = fmaf(x, p.w_in[i * kD + d], tok[d]);
+    }
+#pragma unroll
+  for (int d = 0; d < kD; ++d) {
+    float aq = p.b_qkv[d], ak = p.b_qkv[kD + d], av = p.b_qkv[2 * kD + d];
+#pragma unroll
+    for (int i = 0; i < kD; ++i) {
+      aq = fmaf(tok[i], p.w_qkv[i * 3 * kD + d], aq);
+      ak = fmaf(tok[i], p.w_qkv[i * 3 * kD + kD + d], ak);
+      av = fmaf(tok[i], p.w_qkv[i * 3 * kD + 2 * kD + d], av);
+    }
+    q[d] = aq * qscale;
+    kv[el][g][d] = ak;
+    kv[el][g][kD + d] = av;
+  }
+  wave_lds();
+  // attention and output projection of the lane's token, then the mean over the tokens
+  float o[kD];
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    float sc[L];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      float dot = 0.f;
+#pragma unroll
+      for (int t = h * DH; t < (h + 1) * DH; ++t) dot = fmaf(q[t], kv[el][j][t], dot);
+      sc[j] = dot;
+      mx = fmaxf(mx, sc[j]);
+    }
+    float S = 0.f;
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      sc[j] = __builtin_amdgcn_exp2f(sc[j] - mx);
+      S += sc[j];
+    }
+    const float inv = __builtin_amdgcn_rcpf(S);
+#pragma unroll
+    for (int t = h * DH; t < (h + 1) * DH; ++t) {
+      float acc = 0.f;
+#pragma unroll
+      for (int j = 0; j < L; ++j) acc = fmaf(sc[j], kv[el][j][kD + t], acc);
+      o[t] = acc * inv;
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < kD; ++d) {
+    float y = p.b_o[d];
+#pragma unroll
+    for (int i = 0; i < kD; ++i) y = fmaf(o[i], p.w_o[i * kD + d], y);
+    ys[el][g][d] = y;
+  }
+  wave_lds();
+  float pool[kD] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int j = 0; j < L; ++j)
+#pragma unroll
+    for (int d = 0; d < kD; ++d) pool[d] += ys[el][j][d];
+#pragma unroll
+  for (int d = 0; d < kD; ++d) pool[d] *= 1.0f / (float)L;
+
+  // the heads, a chunk of units at a time: the lane's units, then its outputs' sums over the chunk
+  float acc[NO];
+#pragma unroll
+  for (int r = 0; r < NO; ++r) {
+    const int a = g + kLanes * r;
+    acc[r] = a < A ? p.bp2[a] : a == A && p.value_head ? p.bv2[0] : 0.f;
+  }
+  auto units = [&](float* h, const float* w1, const float* b1, int n, int c) {
+#pragma unroll 4
+    for (int u = g; u < kChunk; u += kLanes) {
+      const int j = c + u < n ? c + u : n - 1;
+      float z = b1[j];
+#pragma unroll
+      for (int d = 0; d < kD; ++d) z = fmaf(pool[d], w1[d * n + j], z);
+      h[u] = gelu_exact(z);
+    }
+  };
+  const int Hv = p.value_head ? p.Hv : 0, Hm = p.Hp > Hv ? p.Hp : Hv;
+  for (int c = 0; c < Hm; c += kChunk) {
+    wave_lds();
+    if (c < p.Hp) units(hid[0][el], p.wp1, p.bp1, p.Hp, c);
+    if (c < Hv) units(hid[1][el], p.wv1, p.bv1, Hv, c);
+    wave_lds();
+#pragma unroll
+    for (int r = 0; r < NO; ++r) {
+      const int a = g + kLanes * r;
+      const bool val = a >= A;
+      const int n = a > A ? 0 : (val ? Hv : p.Hp) - c;   // units left (none past the value)
+      const float* h = hid[val ? 1 : 0][el];
+      const float* w = val ? p.wv2 + c : p.wp2 + (size_t)c * A + a;
+      const int sw = val ? 1 : A;
+      if (n >= kChunk) {
+#pragma unroll 16
+        for (int u = 0; u < kChunk; ++u) acc[r] = fmaf(h[u], w[u * sw], acc[r]);
+      } else {
+        for (int u = 0; u < n; ++u) acc[r] = fmaf(h[u], w[u * sw], acc[r]);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < NO; ++r) {
+    const int a = g + kLanes * r;
+    if (a < A) lgs[el][a] = acc[r];
+    if (live && a <= A && logits && (a < A || p.value_head)) logits[(size_t)a * E + e] = acc[r];
+    if (live && a == A && value && p.value_head) value[e] = acc[r];
+  }
+  if (!act && !logp) return;
+  // sampling: the exponentials by the lanes, the running sums by the environment's first lane
+  wave_lds();
+  float mx = lgs[el][0];
+#pragma unroll
+  for (int a = 1; a < A; ++a) mx = fmaxf(mx, lgs[el][a]);
+#pragma unroll
+  for (int r = 0; r < NO; ++r) {
+    const int a = g + kLanes * r;
+    if (a < A) exs[el][a] = expf(acc[r] - mx);
+  }
+  const u32x4 w = draw(*seedp, (uint32_t)e, step, P_ACTION, 0, 0);
+  wave_lds();
+  if (g != 0 || !live) return;
+  float S = 0.f;
+#pragma unroll
+  for (int a = 0; a < A; ++a) S += exs[el][a];
+  const float target = (((float)(w.x >> 9) + 0.5f) * 0x1p-23f) * S;
+  float cum = 0.f;
+  int pick = A - 1;
+  bool found = false;
+#pragma unroll
+  for (int a = 0; a < A; ++a) {
+    cum += exs[el][a];
+    const bool take = !found && target < cum;
+    pick = take ? a : pick;
+    found = found || take;
+  }
+  if (act) act[e] = (uint8_t)pick;
+  if (logp) logp[e] = (lgs[el][pick] - mx) - logf(S);
+}
+
+// Batches that take eight lanes per environment: up to five rounds of one wave per SIMD (us, against
+// one lane: 256 environments 7.4, 22.0; 16384 11.7, 22.8; 40000 21.0, 23.1; 50000 23.8, 23.4; with
+// 24 actions 40000 24.5, 40.7; with 256-unit heads 40000 66.5, 72.0).
+constexpr int kWideE = 40960;
+
 template <int L, int NH, int A>
 hipError_t run_attn(const AttnParams& p, const float* obs, const uint64_t* seed, uint32_t step,
                     uint8_t* act, float* logp, float* value, float* logits, EnvPart part, hipStream_t st) {
+  if (p.E <= kWideE) {
+    if (part.e0 % kEnvs != 0) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((part.n + kEnvs - 1) / kEnvs)), block(64);
+    hipLaunchKernelGGL((attn_policy8_k<L, NH, A>), grid, block, 0, st, p, part.e0 / kEnvs, obs, seed,
+                       step, act, logp, value, logits);
+    return hipGetLastError();
+  }
   if (part.e0 % kBlock != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)((part.n + kBlock - 1) / kBlock)), block(kBlock);
   hipLaunchKernelGGL((attn_policy_k<L, NH, A>), grid, block, 0, st, p, part.e0 / kBlock, obs, seed, step, act, logp,
@@ -269,12 +462,6 @@ struct AttnGradLds {
   float dl[kSamples][A], dV[kSamples], pool[kSamples][kD];
   double terms[kSamples][3];
 };
-
-__device__ __forceinline__ void wave_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Sums by DPP moves within rows of 16 lanes (two samples): over a sample's 8 lanes (quads, then
 // the other quad by a half-row mirror), and with the other sample's lane of the same part (a
