@@ -626,11 +626,16 @@ __device__ __forceinline__ void tick_events(const SimParams& p, uint32_t* err, u
 // Only this kernel writes those arrays, at the end of a tick, so the early reads see the same
 // values. Without PF the kernel is held to four waves per SIMD (128 VGPRs): the largest grid
 // fills the chip exactly at that occupancy.
+// SP (fewer than 64 environments per wave, a power of two): the wave's other lanes take a share of
+// the end of the tick, which is a chain of short dependent steps in one lane: lane rl + lpw q holds
+// every (64 / lpw)-th server of environment rl from the q-th on, and a share of the rate averages,
+// read at the start of the tick as with PF.
 // One tick k of the learned system for environments e_lane0 .. e_lane0 + lpw - 1, held by the
 // first lpw lanes of the calling wave (all 64 lanes call it, and lanes past E idle); st is
 // the wave's arrival stage. Reads the actions act[E], writes the observation of tick k + 1
 // (obs_mode), the reward and checksum rows (if not NULL) and the environments' state.
-template <int CM, bool PF>
+constexpr int kShareChunk = 4;   // SP: servers of one lane read at the start of the tick
+template <int CM, bool PF, bool SP>
 __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState& g, uint64_t seed,
                                              uint32_t k, int e_lane0, int lpw,
                                              Stage<kStageLearned>& st,
@@ -651,8 +656,13 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
   const int ee = live ? e : 0;
   const size_t E = (size_t)p.E;
   const SysState& G = g.sys[0];
-  double brow_pf[PF ? kEndChunk : 1], ew_pf[PF ? 4 : 1];
-  uint32_t mrow_pf[PF ? kEndChunk : 1];
+  constexpr int kPf = SP ? kShareChunk : PF ? kEndChunk : 1, kEw = SP ? 2 : PF ? 4 : 1;
+  double brow_pf[kPf], ew_pf[kEw];
+  uint32_t mrow_pf[kPf];
+  // SP: the environment whose end of the tick the lane shares, its part of np
+  const int lg = __builtin_ctz(lpw), np = 64 >> lg, part = SP ? lane >> lg : 0;
+  const int er = SP ? e_lane0 + (lane & (lpw - 1)) : e;
+  const bool row_live = er < p.E;
   const double t1 = (double)(k + 1) * p.dt;
   auto load = [&](Queue<CM>& Q, Count& C, Arrivals& A, int& s, int& b, double& busy_s,
                   uint32_t& meta_s) {
@@ -671,7 +681,19 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
     busy_s = G.busy[(size_t)s * E + ee];
     meta_s = G.meta[(size_t)s * E + ee];
     if (bad_action) atomicOr(g.err, ERR_ACTION);
-    if constexpr (PF) {
+    if constexpr (SP) {
+#pragma unroll
+      for (int i = 0; i < kShareChunk; ++i) {
+        const int j = part + np * i;
+        brow_pf[i] = row_live && j < p.K ? G.busy[(size_t)j * E + er] : 0.0;
+        mrow_pf[i] = row_live && j < p.K ? G.meta[(size_t)j * E + er] : 0u;
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = part + np * i;
+        ew_pf[i] = row_live && r < 4 ? g.ewma[(size_t)r * E + er] : 0.0;
+      }
+    } else if constexpr (PF) {
 #pragma unroll
       for (int i = 0; i < kEndChunk; ++i) {
         brow_pf[i] = i < p.K ? G.busy[(size_t)i * E + ee] : 0.0;
@@ -681,17 +703,90 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
       for (int i = 0; i < 4; ++i) ew_pf[i] = g.ewma[(size_t)i * E + ee];
     }
   };
+  const int per = p.K > 1 ? 4 : 2;
+  // server j's completion before t1 (returned) and its features, from its row as the events left it
+  auto server_end = [&](const ObsPairs& ob, int j, double bu, uint32_t m, bool mine, bool dirty) -> uint32_t {
+    const uint32_t infl = m & 0xffu;
+    uint32_t done = 0;
+    if (infl > 0 && bu < t1) {
+      done = infl;
+      m &= ~0xffu;
+      dirty = true;
+    }
+    if (dirty) {
+      if (mine) G.busy[(size_t)j * E + er] = bu;
+      G.meta[(size_t)j * E + er] = m;
+    }
+    const int base = 2 + per * j;
+    const double bflag = bu > t1 ? 1.0 : 0.0;
+    const double lb = (double)((m >> 8) & 0xffu) * 0.03125;
+    ob.put(base, bflag, lb);
+    if (p.K > 1) {
+      const double rem = (bu > t1 ? bu - t1 : 0.0) * p.inv_tw;
+      const uint32_t lc = (m >> 16) & 0xffu;
+      const double lcv = (double)((lc == 0xffu ? -1 : (int)lc) + 1) * p.inv_c;
+      ob.put(base + 2, rem, lcv);
+    }
+    return done;
+  };
+  const double ewc[4] = {1.0, 0.25, 0.0625, 0.015625};
+  const int i_rate = 2 + per * p.K + (p.C > 1 ? 2 * p.C : 0);   // the rates' first feature
   auto end = [&](Queue<CM>& Q, Count& C, Arrivals& A, int s, int b, double busy_s, uint32_t meta_s,
                  bool dirty_s, int A_k) {
+    const ObsPairs ob{(obs_mode & kObsF32) ? g.obs : nullptr, obs_out,
+                      (obs_mode & kObsBf16) ? g.obs_bf : nullptr, E, er};
+    if constexpr (SP) {
+      // what the events left, from the environment's own lane
+      const int rl = lane & (lpw - 1);
+      const int sd = __shfl(s | (dirty_s ? 256 : 0), rl), A_row = __shfl(A_k, rl);
+      const double busy_row = __hiloint2double(__shfl(__double2hiint(busy_s), rl),
+                                               __shfl(__double2loint(busy_s), rl));
+      const uint32_t meta_row = (uint32_t)__shfl((int)meta_s, rl);
+      int done = 0;
+      if (row_live)
+        for (int i0 = 0; part + np * i0 < p.K; i0 += kShareChunk) {
+#pragma unroll
+          for (int i = 0; i < kShareChunk; ++i) {
+            const int j = part + np * (i0 + i);
+            if (j < p.K) {
+              const bool mine = j == (sd & 255);
+              double bu = brow_pf[i];
+              uint32_t m = mrow_pf[i];
+              if (i0 > 0) {
+                bu = G.busy[(size_t)j * E + er];
+                m = G.meta[(size_t)j * E + er];
+              }
+              done += (int)server_end(ob, j, mine ? busy_row : bu, mine ? meta_row : m, mine,
+                                      mine && sd >= 256);
+            }
+          }
+        }
+      // rate average r; its feature pair's other half is the neighbouring part's
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = part + np * i;
+        double ew = ew_pf[i];
+        ew = ew + (r == 0 ? ewc[0] : r == 1 ? ewc[1] : r == 2 ? ewc[2] : ewc[3]) * ((double)A_row - ew);
+        const double v = ew * p.inv_rs;
+        const double v1 = __hiloint2double(__shfl_xor(__double2hiint(v), lpw),
+                                           __shfl_xor(__double2loint(v), lpw));
+        if (row_live && r < 4) {
+          g.ewma[(size_t)r * E + er] = ew;
+          if ((r & 1) == 0) ob.put(i_rate + r, v, v1);
+        }
+      }
+      if (row_live && obs_out)   // the padding (see ObsPairs::pad)
+        for (int f = i_rate + 4 + part; f < p.F; f += np) obs_out[(size_t)f * E + er] = 0.0f;
+      for (int o = lpw; o < 64; o <<= 1) done += __shfl_xor(done, o);
+      C.c[C_DONE] += (uint32_t)done;
+    }
     if (!live) return;
 
     // end of tick: completions before t1 and the per-server part of obs_{k+1}. The server rows
     // are read kEndChunk at a time, all loads of a chunk issued before any of its stores (the
     // compiler cannot reorder them across the stores, which it must assume may alias), so a
     // chunk costs one memory round trip instead of two per server.
-    const ObsPairs ob{(obs_mode & kObsF32) ? g.obs : nullptr, obs_out,
-                      (obs_mode & kObsBf16) ? g.obs_bf : nullptr, E, e};
-    const int per = p.K > 1 ? 4 : 2;
+    if constexpr (!SP)
     for (int j0 = 0; j0 < p.K; j0 += kEndChunk) {
       double brow[kEndChunk];
       uint32_t mrow[kEndChunk];
@@ -714,29 +809,8 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
         const int j = j0 + i;
         if (j >= p.K) break;
         const bool mine = j == s;
-        const double bu = mine ? busy_s : brow[i];
-        uint32_t m = mine ? meta_s : mrow[i];
-        bool dirty = mine && dirty_s;
-        const uint32_t infl = m & 0xffu;
-        if (infl > 0 && bu < t1) {
-          C.c[C_DONE] += infl;
-          m &= ~0xffu;
-          dirty = true;
-        }
-        if (dirty) {
-          if (mine) G.busy[(size_t)j * E + e] = bu;
-          G.meta[(size_t)j * E + e] = m;
-        }
-        const int base = 2 + per * j;
-        const double bflag = bu > t1 ? 1.0 : 0.0;
-        const double lb = (double)((m >> 8) & 0xffu) * 0.03125;
-        ob.put(base, bflag, lb);
-        if (p.K > 1) {
-          const double rem = (bu > t1 ? bu - t1 : 0.0) * p.inv_tw;
-          const uint32_t lc = (m >> 16) & 0xffu;
-          const double lcv = (double)((lc == 0xffu ? -1 : (int)lc) + 1) * p.inv_c;
-          ob.put(base + 2, rem, lcv);
-        }
+        C.c[C_DONE] += server_end(ob, j, mine ? busy_s : brow[i], mine ? meta_s : mrow[i], mine,
+                                  mine && dirty_s);
       }
     }
     const double r = close_tick(Q, C, p, A.proc, A_k);
@@ -745,14 +819,18 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
 
     // rates: exponentially weighted arrival counts with weights 1, 1/4, 1/16, 1/64
     // (all four read before the first store, for the same reason as the server rows)
-    double ew[4];
-    const double ewc[4] = {1.0, 0.25, 0.0625, 0.015625};
+    if constexpr (!SP) {
+      double ew[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) ew[i] = PF ? ew_pf[PF ? i : 0] : g.ewma[(size_t)i * E + e];
+      for (int i = 0; i < 4; ++i) ew[i] = PF ? ew_pf[PF ? i : 0] : g.ewma[(size_t)i * E + e];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      ew[i] = ew[i] + ewc[i] * ((double)A_k - ew[i]);
-      g.ewma[(size_t)i * E + e] = ew[i];
+      for (int i = 0; i < 4; ++i) {
+        ew[i] = ew[i] + ewc[i] * ((double)A_k - ew[i]);
+        g.ewma[(size_t)i * E + e] = ew[i];
+      }
+      ob.put(i_rate, ew[0] * p.inv_rs, ew[1] * p.inv_rs);
+      ob.put(i_rate + 2, ew[2] * p.inv_rs, ew[3] * p.inv_rs);
+      ob.pad(i_rate + 4, p.F);
     }
     // queue part of obs_{k+1}
     const int h = Q.hh;
@@ -771,11 +849,6 @@ __device__ __forceinline__ void learned_tick(const SimParams& p, const EnvState&
         }
       }
     }
-    ob.put(i, ew[0] * p.inv_rs, ew[1] * p.inv_rs);
-    ob.put(i + 2, ew[2] * p.inv_rs, ew[3] * p.inv_rs);
-    i += 4;
-    ob.pad(i, p.F);
-
     store_queue(Q, G, p, E, e);
     store_count(C, G, E, e);
     store_arrivals(A, G, p, e);

@@ -7,7 +7,7 @@ namespace bsim {
 namespace {
 
 // ---- learned system: one tick per launch ----------------------------------------------------
-template <int CM, bool PF>
+template <int CM, bool PF, bool SP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PF ? 1 : 4))) void learned_k(
     SimParams p, EnvState g, uint32_t k, int b0, int lpw, const uint8_t* __restrict__ act,
     float* __restrict__ obs_out, int obs_mode, double* __restrict__ rew,
@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PF ? 1 : 4)
   __shared__ Stage<kStageLearned> stage[4];
   // wave w owns environments w * lpw .. + lpw - 1 in its first lpw lanes (lanes_per_wave);
   // the episode seed was written by reset_k
-  learned_tick<CM, PF>(p, g, *g.seed, k, ((b0 + blockIdx.x) * 4 + (threadIdx.x >> 6)) * lpw, lpw,
+  learned_tick<CM, PF, SP>(p, g, *g.seed, k, ((b0 + blockIdx.x) * 4 + (threadIdx.x >> 6)) * lpw, lpw,
                        stage[threadIdx.x >> 6], act, obs_out, obs_mode, rew, rchk);
 }
 
@@ -596,19 +596,20 @@ hipError_t launch_reset(const SimParams& p, const EnvState& s, uint64_t seed, hi
   return hipGetLastError();
 }
 
-template <bool PF>
+template <bool PF, bool SP>
 void launch_learned(const SimParams& p, const EnvState& s, uint32_t k, int b0, int lpw, dim3 grid,
                     const uint8_t* act, float* obs_out, int obs_mode, double* rew,
                     uint64_t* rchk, hipStream_t st) {
   const dim3 block(256);
   if (p.C <= 1)
-    hipLaunchKernelGGL((learned_k<1, PF>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
+    hipLaunchKernelGGL((learned_k<1, PF, SP>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
   else if (p.C <= 2)
-    hipLaunchKernelGGL((learned_k<2, PF>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
+    hipLaunchKernelGGL((learned_k<2, PF, SP>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
   else
-    hipLaunchKernelGGL((learned_k<4, PF>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
+    hipLaunchKernelGGL((learned_k<4, PF, SP>), grid, block, 0, st, p, s, k, b0, lpw, act, obs_out, obs_mode, rew, rchk);
 }
 
+constexpr int kShareServers = 4;
 hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
                        const uint8_t* act, float* obs_out, int obs_mode, double* rew,
                        uint64_t* rchk, EnvPart part, hipStream_t st) {
@@ -618,13 +619,18 @@ hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
   if (part.e0 % (4 * lpw) != 0) return hipErrorInvalidValue;
   const int b0 = part.e0 / (4 * lpw);
   const dim3 grid((part.n + 4 * lpw - 1) / (4 * lpw));
-  // early end-of-tick reads (and no register limit) while a SIMD has at most two waves: 20000
-  // environments with 8 servers, 1250 waves, 36.5 us per tick against 37.0; two waves of the
-  // unlimited kernel are all that fit a SIMD
-  if (waves <= 2 * kFillWaves && p.K <= kEndChunk)
-    launch_learned<true>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
+  // waves of fewer than 64 environments (at most two per SIMD) share the end of the tick among their
+  // lanes from four servers on (us per tick: 8 servers, 20000 environments 35.3 -> 32.9; 4 servers,
+  // 2000 15.1 -> 13.9, 40000 22.5 -> 22.1; 16 servers, 4096 70.5 -> 63.4; one server, 4096 9.5 -> 10.1, as
+  // the lanes then only pass values on); else early end-of-tick reads (and no register limit) while
+  // a SIMD has at most two waves, all that fit it without the limit (20000 environments with 8
+  // servers, 1250 waves, 36.5 us per tick against 37.0)
+  if (lpw < 64 && p.K >= kShareServers)
+    launch_learned<true, true>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
+  else if (waves <= 2 * kFillWaves && p.K <= kEndChunk)
+    launch_learned<true, false>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
   else
-    launch_learned<false>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
+    launch_learned<false, false>(p, s, k, b0, lpw, grid, act, obs_out, obs_mode, rew, rchk, st);
   return hipGetLastError();
 }
 
