@@ -157,6 +157,9 @@ __device__ __forceinline__ void sq_scan(BusyTimes<KM>& busy, ServerBytes& infl, 
 // processes its own events, dispatches and closes in the order of its timeline.
 // The event counts of bursty environments differ widely from tick to tick; stepping the lanes
 // tick by tick would take, at every tick, as many passes as the busiest lane.
+// Arrivals that nothing can come between are taken in runs, at about a third of a pass's
+// instructions each (16 servers, 262144 environments: 51.4 -> 47.0 us per tick in 32-tick launches,
+// one-tick launches of 4096 30 -> 26).
 //
 // A dispatch stores its server's meta word at once; a completion clears the in-flight byte
 // only in registers and marks the server in `clear`, and `dirty` marks servers whose
@@ -244,7 +247,37 @@ __device__ __forceinline__ void static_run(const SimParams& p, const SysState& G
         ++A_k;
         enqueue(Q, C, p, cls, now);
       }
-      if (due()) mode = PEND;
+      bool pend = due();
+      // a run of arrivals, as in the learned tick (tick_events): until the next switch, completion or
+      // tick's end, the head of line's timeout, or a batch due
+      if (!pend && p.arrival_kind != 1) {
+        const double wend = fmin(fmin(A.next_sw, next_done), t1);
+        const uint32_t j0 = A.jarr;
+        const int lim = min((int)(staged_hi - j0) - 2, (int)kMaxEventsPerTick - (int)it);
+        int r = 0, drops = 0;
+        auto in_run = [&]() -> bool {
+          const double tout = idle != 0u && Q.qsum > 0 ? Q.hts_h + p.static_timeout : kInf;
+          return r <= lim && A.next_arr < wend && A.next_arr < tout;
+        };
+        bool more = in_run();
+        while (more) {
+          now = A.next_arr;
+          const uint32_t j = (j0 + (uint32_t)r) % kStageStatic;
+          const int c = st.cls[j][lane];
+          A.next_arr = now + st.E[j][lane] * A.gap;
+          ++r;
+          drops += enqueue_sel(Q, p, c, now) ? 0 : 1;
+          pend = due();
+          more = !pend && in_run();
+        }
+        A.jarr += (uint32_t)r;
+        it += (uint32_t)r;
+        A_k += r;
+        C.c[C_ARR] += (uint32_t)r;
+        C.c[C_DROP] += (uint32_t)drops;
+        C.c[C_ACC] += (uint32_t)(r - drops);
+      }
+      if (pend) mode = PEND;
     }
     const int n_act = __popcll(__ballot(mode != OFF));
     const int n_pend = __popcll(__ballot(mode == PEND));
