@@ -647,7 +647,15 @@ hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
                        const uint8_t* act, float* obs_out, int obs_mode, double* rew,
                        uint64_t* rchk, EnvPart part, hipStream_t st) {
   if ((obs_mode & kObsBf16) && !s.obs_bf) return hipErrorInvalidValue;
-  const int lpw = lanes_per_wave(p.E);
+  int lpw = lanes_per_wave(p.E);
+  // a rollout in two halves takes the next smaller number also where the batch is one wave per SIMD
+  // exactly: the halves' ticks then overlap each other's policies as two waves per SIMD (8 servers,
+  // us per tick: 32768 environments 48.8 -> 45.0, 65536 60.3 -> 56.9; in one chain the tick alone is
+  // slower for it, 43.7 -> 46.9), if the lanes then hold all servers' rows (16 servers: 32768 63.0 ->
+  // 61.1; 65536, where they would not, 92.0 -> 95.2)
+  if (part.n < p.E && lpw > 4 && (p.E + lpw - 1) / lpw <= kFillWaves && p.K >= kShareServers &&
+      p.K <= kShareChunk * (64 / (lpw / 2)))
+    lpw /= 2;
   const int waves = (p.E + lpw - 1) / lpw;
   if (part.e0 % (4 * lpw) != 0) return hipErrorInvalidValue;
   const int b0 = part.e0 / (4 * lpw);

@@ -1,8 +1,9 @@
 """Per-tick rollouts in two chains of launches, one per half of the batch, against one chain of the
 whole batch (per-launch timing on) bit for bit: just past each size from which the halves are
-taken, with a ragged last tile in the second half, for every policy kernel, with the value
-row, stored observations and the static shadow system beside them; run eagerly, then captured
-and replayed with other work on the caller's stream between the replays."""
+taken and at those where their waves take fewer environments, with a ragged last tile in the
+second half, for every policy kernel, with the value row, stored observations and the static
+shadow system beside them; run eagerly, then captured and replayed with other work on the
+caller's stream between the replays."""
 import pytest
 
 from test_gpu_fused import assert_same, bs, snapshot, weights  # noqa: F401
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ("C1", {}, 65537, 4), ("C2", dict(value_head=1), 65793, 3), ("C3", {}, 65599, 3),
-    ("C4", {}, 16385, 3), ("C4", {}, 16640, 3), ("C5", {}, 16700, 3), ("attn", {}, 131073, 2),
+    ("C4", {}, 16385, 3), ("C4", {}, 32768, 3), ("C4", {}, 65536, 2), ("C5", {}, 32768, 2), ("C5", {}, 16700, 3), ("attn", {}, 131073, 2),
 ]
 
 
