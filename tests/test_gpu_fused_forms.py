@@ -1,7 +1,8 @@
 """The fused rollout's forms (which tile, weights in registers or from L2, request rings in LDS or in
 memory) at the edges of what each takes, against the per-tick launches bit for bit: batches
 just past what the smaller tile holds at once, one environment, queues too long for LDS, the
-largest server count of each padded width, three classes, and few ticks in a row."""
+largest server count of each padded width, three classes, more workgroups than are resident at
+once, and few ticks in a row."""
 import pytest
 
 from test_gpu_fused import assert_same, bs, snapshot, weights  # noqa: F401
@@ -21,6 +22,7 @@ CASES = [
     ("C3", dict(MIX3, n_servers=4), 4300, 4), ("C3", dict(queue_cap=255), 500, 8),
     ("C4", dict(n_servers=10), 129, 5), ("C4", {}, 4099, 3), ("C4", {}, 8300, 3),
     ("C4", dict(queue_cap=255, rates=[40000.0] * 3), 64, 12),
+    ("C1", {}, 16401, 3), ("C2", {}, 16401, 3), ("C3", {}, 32769, 2),   # two rounds and a third
 ]
 
 
