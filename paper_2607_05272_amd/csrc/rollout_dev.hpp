@@ -13,10 +13,10 @@
 // holds simply runs in rounds).
 //
 // Bound by the chain of one wave's instructions through a tick, at one or two waves per SIMD (us
-// per tick, state and weights through L2 before and as here): the 8-64-64-6 network 10.2 -> 5.4
-// at 256 environments (of 13000 cycles 3300 in the policy's layers, 1700 in the sampler, 2500
-// in loads and events, 3200 at the end of the tick, the rest at barriers), the 12-128-128-6 one
-// 8.4 -> 6.5 at 4096, the 32-256-256-24 one 18.6 -> 7.9 at 2000 and 19.8 -> 14.1 at 16384, the
+// per tick, state and weights through L2 before and as here): the 8-64-64-6 network 10.2 -> 5.1
+// at 256 environments (of 12500 cycles 3300 in the policy's layers, 1700 in the sampler, 2500
+// in loads and events, 2500 at the end of the tick, the rest at barriers), the 12-128-128-6 one
+// 8.4 -> 6.5 at 4096, the 32-256-256-24 one 18.6 -> 7.7 at 2000 and 19.8 -> 14.1 at 16384, the
 // 64-256-256-48 one 40.6 -> 13.7 at 1024 and 36.0 -> 26.9 at 16384.
 //
 // The tick is the per-tick kernel's own device code (sim_dev.hpp), and every policy sum takes
@@ -387,12 +387,33 @@ struct TileState {
   }
 };
 
+// The tick's checksum and reward of row r (environment e) with `done` more requests completed.
+template <int CM, class State>
+__device__ __forceinline__ void close_row(const SimParams& p, State& S, int r, int e, uint32_t qp,
+                                          int A_k, uint32_t done, double* rew, uint64_t* rchk) {
+  Count C;
+  C.chk = S.chk[r];
+  C.n_k = S.n_k[r];
+  C.Lw = S.Lw[r];
+  C.c[C_DONE] = S.cnt[C_DONE][r] + done;
+  C.c[C_DROP] = S.cnt[C_DROP][r];
+  Queue<CM> Q;
+  Q.qp = qp;
+  const double rw = close_tick(Q, C, p, S.proc[r], A_k);
+  S.chk[r] = C.chk;
+  S.cnt[C_DONE][r] = C.c[C_DONE];
+  if (rew) rew[e] = rw;
+  if (rchk) rchk[e] = C.chk;
+}
+
 // One tick of the wave's rows r0 .. r0 + lpw - 1 (environments e0 + r0 .., `n` of the workgroup's
 // rows live), state in LDS. The first lpw lanes take the events, one row each; then the end of
 // the tick (completions, checksum, reward, rate averages, observation), which is a chain of
 // short dependent steps in one lane (3000 to 8000 of a tick's cycles for 1 to 8 servers), is
 // shared by eight lanes per row: every eighth server, a class or the queues' total, a rate each.
-template <class Net, int CM, bool INL, int LN, class State>
+// DEFER: the checksum and the reward, which the next tick's policy does not need, are left to the
+// caller (close_row).
+template <class Net, int CM, bool INL, int LN, bool DEFER, class State>
 __device__ __forceinline__ void tile_tick(const SimParams& p, State& S, uint32_t* err,
                                           double* rings, uint64_t seed, uint32_t k, int e0, int r0,
                                           int lpw, int n, Stage<kStageLearned, LN>& st,
@@ -494,19 +515,8 @@ __device__ __forceinline__ void tile_tick(const SimParams& p, State& S, uint32_t
   if (ob.traj)   // features past the state's: zero (the policy's rows hold zeros there)
     for (int f = i + 4 + s; f < p.F; f += 8) ob.traj[(size_t)f * ob.E + ob.e] = 0.0f;
   if (s == 7) {
-    Count C;
-    C.chk = S.chk[r];
-    C.n_k = S.n_k[r];
-    C.Lw = S.Lw[r];
-    C.c[C_DONE] = S.cnt[C_DONE][r] + (uint32_t)done;
-    C.c[C_DROP] = S.cnt[C_DROP][r];
-    Queue<CM> Q;
-    Q.qp = qp;
-    const double rw = close_tick(Q, C, p, S.proc[r], A_k);
-    S.chk[r] = C.chk;
-    S.cnt[C_DONE][r] = C.c[C_DONE];
-    if (rew) rew[ob.e] = rw;
-    if (rchk) rchk[ob.e] = C.chk;
+    if constexpr (DEFER) S.cnt[C_DONE][r] += (uint32_t)done;
+    else close_row<CM>(p, S, r, ob.e, qp, A_k, (uint32_t)done, rew, rchk);
   }
 }
 
@@ -553,6 +563,18 @@ __global__ __launch_bounds__(Net::NW * 64) __attribute__((amdgpu_waves_per_eu(2)
   // have no rows to sample, else by each wave for its own rows (one block per lane)
   constexpr int kIdle = NW - ROWS / 8;
   const int npre = p.arrival_kind == 1 ? 0 : kIdle > 0 ? 8 : 64 / LN;
+  // the last of those waves also takes the previous tick's checksums and rewards, off the chain of
+  // the tick (us per tick, 256 environments of one server 5.40 -> 5.10, 128 of the 12-128-128-6 network
+  // 6.55 -> 6.09; with four classes it costs registers, 8192 with 8 servers 22.2 -> 23.0)
+  constexpr bool kDefer = kIdle > 0 && CM <= 2;
+
+  auto close = [&](int i) {   // tick i's, a row per lane
+    const int r = tid & 63;
+    const size_t row = (size_t)i * E;
+    if (r < n)
+      close_row<CM>(p, state, r, e0 + r, state.qpack[r], state.A_k[r], 0u,
+                    o.rew ? o.rew + row : nullptr, o.rchk ? o.rchk + row : nullptr);
+  };
 
   for (int i = 0; i <= T; ++i) {
     const uint32_t k = k0 + (uint32_t)i;
@@ -567,6 +589,9 @@ __global__ __launch_bounds__(Net::NW * 64) __attribute__((amdgpu_waves_per_eu(2)
                                       !last && o.logp ? o.logp + row : nullptr,
                                       o.value ? o.value + row : nullptr, nullptr, us, n, act);
     if (last) break;
+    if constexpr (kDefer) {
+      if (wave == NW - 1 && i > 0) close(i - 1);
+    }
     if constexpr (kIdle > 0) {
       const int w0 = wave - ROWS / 8;
       if (w0 >= 0)
@@ -589,10 +614,14 @@ __global__ __launch_bounds__(Net::NW * 64) __attribute__((amdgpu_waves_per_eu(2)
     const bool end = i + 1 == T;
     const ObsPairs out{end ? g.obs : nullptr, o.obs ? o.obs + (size_t)(i + 1) * F * E : nullptr,
                        Net::kBf16 && end ? g.obs_bf : nullptr, E, 0};
-    tile_tick<Net, CM, kInl, LN>(p, state, g.err, RL ? ring_lds : ring_mem, seed, k, e0, r0, lpw, n,
+    tile_tick<Net, CM, kInl, LN, kDefer>(p, state, g.err, RL ? ring_lds : ring_mem, seed, k, e0, r0, lpw, n,
                                  stage[wave], (uint32_t)npre, act, smem, out,
                                  o.rew ? o.rew + row : nullptr, o.rchk ? o.rchk + row : nullptr);
     __syncthreads();   // the tile's next observation and state are written
+  }
+  if constexpr (kDefer) {
+    if (wave == NW - 1) close(T - 1);
+    __syncthreads();
   }
   state.each(p, g, e0, n, [](auto& l, auto& v) { v = l; });
   if constexpr (RL)
