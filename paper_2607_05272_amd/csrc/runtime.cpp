@@ -702,6 +702,18 @@ static bool use_fused(sim_ctx* x) {
   return x->fuse == SIM_FUSE_ON || x->cfg.n_envs <= max_e;
 }
 
+// whether a rollout's launches (when they are not fused) form two chains now. With per-launch timing
+// on they form one, so that each kernel's duration is its own, and under a capture: a graph's
+// branches are submitted one after the other, so the second chain of a long rollout would start
+// when the first is almost done (ms, as a graph of one chain, as one of two, and launched: 65536
+// environments with 8 servers, 1024 ticks, 60.9, 64.9 and 52.4; 262144 with 16, 2048 ticks, 606, 647
+// and 575; the four launches of a tick take the host 13 us).
+static bool in_halves(const sim_ctx* x) { return two_halves(x) && x->hev_join && !x->timing; }
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
 // x->stream set to another stream for a scope
 struct OnStream {
   sim_ctx* x;
@@ -759,8 +771,7 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
     HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
            "observation packing launch");
   EnvPart parts[2] = {whole(x), {0, 0}};
-  // (with per-launch timing on, one chain, so that each kernel's duration is its own)
-  const int chains = two_halves(x) && x->hev_join && !x->timing ? 2 : 1;
+  const int chains = in_halves(x) && !capturing(x->stream) ? 2 : 1;
   hipStream_t streams[2] = {x->stream, x->hstream};
   if (chains == 2) {
     const int n0 = (x->cfg.n_envs / 2 + kPartAlign - 1) / kPartAlign * kPartAlign;
@@ -870,7 +881,7 @@ int sim_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr
            "hipMemcpyAsync obs_0");
   const RolloutKey key{d_weights, T, *tr, x->tick};
   int rc;
-  if (x->graphs && !x->timing) {
+  if (x->graphs && !x->timing && (!in_halves(x) || use_fused(x))) {
     // a call that repeats the previous one (same weights, length, outputs, starting tick) is
     // captured as a graph; later repeats replay it
     bool have = x->rkey_valid && same_key(key, x->rkey);

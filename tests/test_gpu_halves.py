@@ -2,8 +2,8 @@
 whole batch (per-launch timing on) bit for bit: just past each size from which the halves are
 taken and at those where their waves take fewer environments, with a ragged last tile in the
 second half, for every policy kernel, with the value row, stored observations and the static
-shadow system beside them; run eagerly, then captured and replayed with other work on the
-caller's stream between the replays."""
+shadow system beside them, several times with other work on the caller's stream in between (such
+rollouts are not captured as graphs); and inside a caller's own capture."""
 import pytest
 
 from test_gpu_fused import assert_same, bs, snapshot, weights  # noqa: F401
@@ -37,5 +37,30 @@ def test_rollout_in_halves_matches_one_chain(bs, name, kw, E, T):  # noqa: F811
                     ref = out
                 else:
                     assert_same(ref, out, f"{name} {kw} E={E}, call {i}")
-                    tr.actions.zero_()   # other work between the replays
-            assert one_chain or sim.graph_stats()[1] > 0
+                    tr.actions.zero_()
+            assert one_chain or sim.graph_stats() == (0, 0)
+
+
+def test_rollout_in_a_callers_capture(bs):  # noqa: F811
+    w, E, T = preset("C4"), 16385, 3
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st), bs.Sim(w, n_envs=E) as sim:
+        sim.set_fused_rollout(bs.FUSE_OFF)
+        sim.set_graphs(False)
+        wb = sim.upload_weights(weights(w, 21))
+        sim.reset(0xCA)
+        tr = sim.rollout(wb, T, store_obs=True, rchk=True)
+        ref = snapshot(sim, tr)
+        sim.reset(0xCA)
+        st.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st, capture_error_mode="thread_local"):
+            sim.rollout(wb, T, traj=tr)
+        for i in range(3):
+            sim.reset(0xCA)
+            for t in (tr.actions, tr.reward, tr.obs):
+                t.zero_()
+            g.replay()
+            got = snapshot(sim, tr)
+            del got["state"]   # its tick counter is the host's, which a replay does not advance
+            assert_same({k: ref[k] for k in got}, got, f"replay {i}")
