@@ -711,7 +711,9 @@ static bool use_fused(sim_ctx* x) {
 static bool in_halves(const sim_ctx* x) { return two_halves(x) && x->hev_join && !x->timing; }
 static bool capturing(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();   // not a launch's
+  return false;
 }
 
 // x->stream set to another stream for a scope
@@ -732,6 +734,17 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
   int rc = prepare_policy(x, d_weights);
   if (rc) return rc;
   const size_t E = (size_t)x->cfg.n_envs, F = (size_t)x->cfg.obs_dim;
+  // a bf16 policy reads the observation as bf16 pairs, which the ticks write instead of the
+  // fp32 observation (half its bytes, both for the tick that writes it and the policy that
+  // reads it); the fp32 observation is written again by the last tick
+  const uint32_t* obs_bf = x->s.obs_bf;
+  const bool fused = use_fused(x);
+  // packed ahead of the shadow's launch, whose waves fill every CU as they come: behind them the
+  // whole chain waited (16 servers, us per tick: 131072 environments x 512 160.4 -> 156.6, 262144 x
+  // 1024 281.0 -> 271.4)
+  if (obs_bf && !fused)
+    HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
+           "observation packing launch");
   // The static shadow system never reads the learned system, so its launches run beside the
   // learned chain on a second stream (forked from and joined back to the rollout's stream,
   // which a graph capture follows); with per-launch timing on, everything stays on one stream
@@ -755,11 +768,7 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
     rc = run_static(x, k0, T, tr->reward_shadow);
     if (rc) return rc;
   }
-  // a bf16 policy reads the observation as bf16 pairs, which the ticks write instead of the
-  // fp32 observation (half its bytes, both for the tick that writes it and the policy that
-  // reads it); the fp32 observation is written again by the last tick
-  const uint32_t* obs_bf = x->s.obs_bf;
-  if (use_fused(x)) {
+  if (fused) {
     const RolloutOut o{tr->actions, tr->logp, tr->value, tr->reward, tr->rchk, tr->obs};
     HIPCHK(x->timed(SIM_KC_ROLLOUT, [&] {
              return launch_rollout_fused(x->p, x->s, x->m, x->fuse_plan, k0, T, o, x->stream);
@@ -767,9 +776,6 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
     if (side) HIPCHK(hipStreamWaitEvent(x->stream, x->sev_join, 0), "hipStreamWaitEvent");
     return SIM_OK;
   }
-  if (obs_bf)
-    HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
-           "observation packing launch");
   EnvPart parts[2] = {whole(x), {0, 0}};
   const int chains = in_halves(x) && !capturing(x->stream) ? 2 : 1;
   hipStream_t streams[2] = {x->stream, x->hstream};
