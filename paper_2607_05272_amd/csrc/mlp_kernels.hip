@@ -211,30 +211,30 @@ static hipError_t launch_policy_t(const MlpParams& m, const float* obs, const ui
   if (m.bf16 && m.FP == 32 && m.H1 == 128 && m.H2 == 128 && m.AP == 16)
     return run_shape_bf16<DBG, 0>(m, [&](auto ac_v) {   // 6 measured slower
       constexpr int C = decltype(ac_v)::value;
-      return m.E <= kRows128.small_e ? run_policy_bf16<DBG, 32, 128, 128, 16, 1, 8, 1, 1, C> BSIM_BF16_ARGS
-             : m.E <= kRows128.mid_e ? run_policy_bf16<DBG, 32, 128, 128, 16, 2, 8, 1, 1, C> BSIM_BF16_ARGS
-                                    : run_policy_bf16<DBG, 32, 128, 128, 16, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows128.small_e) return run_policy_bf16<DBG, 32, 128, 128, 16, 1, 8, 1, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows128.mid_e) return run_policy_bf16<DBG, 32, 128, 128, 16, 2, 8, 1, 1, C> BSIM_BF16_ARGS;
+      return run_policy_bf16<DBG, 32, 128, 128, 16, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
     });
   if (m.bf16 && m.FP == 32 && m.H1 == 256 && m.H2 == 256 && m.AP == 32)
     return run_shape_bf16<DBG, 24>(m, [&](auto ac_v) {
       constexpr int C = decltype(ac_v)::value;
-      return m.E <= kRows256.small_e ? run_policy_bf16<DBG, 32, 256, 256, 32, 1, 8, 1, 1, C> BSIM_BF16_ARGS
-             : m.E <= kRows256.mid_e ? run_policy_bf16<DBG, 32, 256, 256, 32, 2, 8, 1, 1, C> BSIM_BF16_ARGS
-                                    : run_policy_bf16<DBG, 32, 256, 256, 32, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows256.small_e) return run_policy_bf16<DBG, 32, 256, 256, 32, 1, 8, 1, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows256.mid_e) return run_policy_bf16<DBG, 32, 256, 256, 32, 2, 8, 1, 1, C> BSIM_BF16_ARGS;
+      return run_policy_bf16<DBG, 32, 256, 256, 32, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
     });
   if (m.bf16 && m.FP == 64 && m.H1 == 256 && m.H2 == 256 && m.AP == 64)
     return run_shape_bf16<DBG, 48>(m, [&](auto ac_v) {
       constexpr int C = decltype(ac_v)::value;
-      return m.E <= kRows256.small_e ? run_policy_bf16<DBG, 64, 256, 256, 64, 1, 8, 1, 1, C> BSIM_BF16_ARGS
-             : m.E <= kRows256.mid_e ? run_policy_bf16<DBG, 64, 256, 256, 64, 2, 8, 1, 1, C> BSIM_BF16_ARGS
-                                    : run_policy_bf16<DBG, 64, 256, 256, 64, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows256.small_e) return run_policy_bf16<DBG, 64, 256, 256, 64, 1, 8, 1, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows256.mid_e) return run_policy_bf16<DBG, 64, 256, 256, 64, 2, 8, 1, 1, C> BSIM_BF16_ARGS;
+      return run_policy_bf16<DBG, 64, 256, 256, 64, 4, 8, 2, 1, C> BSIM_BF16_ARGS;
     });
   if (m.bf16 && m.FP == 96 && m.H1 == 512 && m.H2 == 512 && m.AP == 112)
     return run_shape_bf16<DBG, 96>(m, [&](auto ac_v) {
       constexpr int C = decltype(ac_v)::value;
-      return m.E <= kRows512.small_e ? run_policy_bf16<DBG, 96, 512, 512, 112, 1, 8, 1, 1, C> BSIM_BF16_ARGS
-             : m.E <= kRows512.mid_e ? run_policy_bf16<DBG, 96, 512, 512, 112, 2, 8, 1, 1, C> BSIM_BF16_ARGS
-                                    : run_policy_bf16<DBG, 96, 512, 512, 112, 4, 8, 2, 2, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows512.small_e) return run_policy_bf16<DBG, 96, 512, 512, 112, 1, 8, 1, 1, C> BSIM_BF16_ARGS;
+      if (m.E <= kRows512.mid_e) return run_policy_bf16<DBG, 96, 512, 512, 112, 2, 8, 1, 1, C> BSIM_BF16_ARGS;
+      return run_policy_bf16<DBG, 96, 512, 512, 112, 4, 8, 2, 2, C> BSIM_BF16_ARGS;
     });
 #undef BSIM_BF16_ARGS
   return hipErrorInvalidValue;

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     ("C1", {}, 65537, 4), ("C2", dict(value_head=1), 65793, 3), ("C3", {}, 65599, 3),
-    ("C4", {}, 16385, 3), ("C4", {}, 32768, 3), ("C4", {}, 65536, 2), ("C5", {}, 32768, 2), ("C5", {}, 16700, 3), ("attn", {}, 131073, 2),
+    ("C4", {}, 16385, 3), ("C4", {}, 32768, 3), ("C4", {}, 65536, 2), ("C5", {}, 32768, 2),
+    ("C5", {}, 16700, 3), ("attn", {}, 131073, 2),
 ]
 
 
