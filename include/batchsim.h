@@ -262,9 +262,9 @@ int sim_rollout(sim_ctx* ctx, const void* d_weights, int32_t T, const sim_traj* 
  * graph on a private stream of the context, and that graph is replayed by every further
  * repeat (ordered after earlier work on the context's stream, and before later work, by
  * events). Kernels read the seed from device memory written by sim_reset, so a new seed needs
- * no new graph. Tracing (sim_set_timing) launches eagerly, and so do rollouts of large batches
- * in two halves (more than 65536 environments, 16384 with three or four request classes, 131072
- * with the attention policy, unless fused): the halves' launches run side by side, which a
+ * no new graph. Tracing (sim_set_timing) launches eagerly, and so do per-tick rollouts in two
+ * halves of the batch (from 8192 environments, 2048 with four servers or more, unless fused):
+ * the halves' launches run side by side, which a
  * replayed graph's branches would not. sim_set_trace discards the graph.
  * on = 0 launches every rollout eagerly.                                                    */
 int sim_set_graphs(sim_ctx* ctx, int32_t on);

@@ -284,20 +284,14 @@ static void derive(sim_ctx* x) {
 
 // whether a per-tick rollout runs as two chains of launches, one per half of the batch. A tick waits
 // on its slowest wave with the rest of the chip idle, and its waves load, compute and store in
-// step; with two chains one half's policy runs beside the other's tick. It pays once the tick fills
-// the chip (more than one 64-lane wave per SIMD: 12-128-128-6 network, 100000 environments 36.3 ->
-// 33.2 us per tick; 32-256-256-24, 100000 61.7 -> 55.5, 262144 121.8 -> 118.9), and with three or
-// four request classes, whose ticks are longer, from 16385 environments, where the waves pass one
-// per SIMD (8 servers: 17000 44.0 -> 43.4, 24000 46.3 -> 43.5, 65536 61.5 -> 58.7, 100000 85.1 ->
-// 76.6; 16 servers: 17000 59.5 -> 54.3, 65536 100 -> 89.4, 262144 295 -> 285), with the attention
-// policy from 131073 (262144 65.3 -> 56.5; 66000 41.8 -> 41.9, 131072 46.3 -> 48.3). Below, two launches
-// in a chain's place cost more (2 classes: 20000 21.2 -> 23.0, 65536 28.8 -> 28.9; 4 classes: 8192 46.2
-// -> 47.3, 16384 51.5 -> 53.3).
-constexpr int kHalvesE = 65536, kHalvesAttnE = 131072, kHalvesManyClassesE = 16384;
+// step; with two chains one half's policy runs beside the other's tick. Us per tick, one chain and
+// two: one server 20000 environments 24.5, 21.2; 12-128-128-6 8192 17.9, 16.7, 40000 25.7, 22.4; 4
+// servers 2048 19.8, 18.9, 40000 38.0, 30.8; 8 servers 17000 41.6, 38.5; 16 servers 2048 35.7, 33.4,
+// 17000 56.9, 48.3; attention policy 8192 20.6, 19.1, 262144 65.3, 54. Ticks of few servers and small
+// batches are too short for four launches in place of two (one server 4096 16.8, 17.1).
+constexpr int kHalvesE = 8192, kHalvesLongE = 2048, kHalvesLongK = 4;
 static bool two_halves(const sim_ctx* x) {
-  const int E = x->cfg.n_envs;
-  if (x->cfg.policy_kind == SIM_POLICY_ATTN) return E > kHalvesAttnE;
-  return E > kHalvesE || (x->cfg.n_classes > 2 && E > kHalvesManyClassesE);
+  return x->cfg.n_envs >= (x->cfg.n_servers >= kHalvesLongK ? kHalvesLongE : kHalvesE);
 }
 
 // the second chain's stream and events

@@ -1,5 +1,5 @@
 """Per-tick rollouts in two chains of launches, one per half of the batch, against one chain of the
-whole batch (per-launch timing on) bit for bit: just past each size from which the halves are
+whole batch (per-launch timing on) bit for bit: at and past each size from which the halves are
 taken and at those where their waves take fewer environments, with a ragged last tile in the
 second half, for every policy kernel, with the value row, stored observations and the static
 shadow system beside them, several times with other work on the caller's stream in between (such
@@ -14,9 +14,10 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    ("C1", {}, 65537, 4), ("C2", dict(value_head=1), 65793, 3), ("C3", {}, 65599, 3),
-    ("C4", {}, 16385, 3), ("C4", {}, 32768, 3), ("C4", {}, 65536, 2), ("C5", {}, 32768, 2),
-    ("C5", {}, 16700, 3), ("attn", {}, 131073, 2),
+    ("C1", {}, 8192, 4), ("C1", {}, 65537, 4), ("C2", dict(value_head=1), 8449, 3),
+    ("C3", {}, 2048, 3), ("C3", {}, 65599, 3), ("C4", {}, 2049, 3), ("C4", {}, 8192, 3),
+    ("C4", {}, 32768, 3), ("C4", {}, 65536, 2), ("C5", {}, 32768, 2), ("C5", {}, 16700, 3),
+    ("attn", {}, 8200, 2), ("attn", {}, 41100, 2),
 ]
 
 
