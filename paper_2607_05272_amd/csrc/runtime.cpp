@@ -680,11 +680,11 @@ int sim_policy_hidden(sim_ctx* x, const void* d_weights, const float* d_obs, uin
 // whether a rollout runs as one fused launch (sim_set_fused_rollout): forced on, whenever the
 // network has a fused kernel; automatically, when all of the batch's workgroups of that kernel
 // are resident at once, or with one or two request classes in two rounds of them (each round runs
-// every tick for its workgroups; us per tick in two rounds against the per-tick launches: one server
-// 16384 environments 15.3, 21.9; 12-128-128-6 17000 19.9, 21.2, 32768 19.9, 23.4; 32-256-256-24 17000
-// 25.2, 27.4, 32768 27.3, 32.0; in three 40000 36.0, 38.4, 49152 40.4, 39.3; 8 servers and four classes
-// 17000 44.3, 41.4), the second at most half full beside a shadow system, which then runs on the
-// same CUs (24000 30.8, 34.8; 32768 38.3, 36.9)
+// every tick for its workgroups), the second at most half full from four servers on or beside a
+// shadow system, which then runs on the same CUs. Us per tick, fused and in launches of halves: one
+// server 16384 environments 14.0, 21.1; 12-128-128-6 17000 19.1, 18.7, 32768 18.8, 20.7; 32-256-256-24
+// 17000 24.5, 25.1, 24000 23.5, 25.7, 28000 26.8, 26.1; with a shadow 32768 38.3, 32.0; four classes
+// 17000 44.3, 38.5
 static bool use_fused(sim_ctx* x) {
   if (x->fuse == SIM_FUSE_OFF || x->cfg.policy_kind != SIM_POLICY_MLP) return false;
   if (x->fuse_plan.cap < 0) {
@@ -693,7 +693,9 @@ static bool use_fused(sim_ctx* x) {
   }
   if (x->fuse_plan.cap == 0) return false;
   const int64_t cap = x->fuse_plan.cap;
-  const int64_t max_e = x->cfg.n_classes > 2 ? cap : x->cfg.shadow ? cap * 3 / 2 : 2 * cap;
+  const int64_t max_e = x->cfg.n_classes > 2 ? cap
+                        : x->cfg.shadow || x->cfg.n_servers >= kHalvesLongK ? cap * 3 / 2
+                                                                            : 2 * cap;
   return x->fuse == SIM_FUSE_ON || x->cfg.n_envs <= max_e;
 }
 
