@@ -721,6 +721,32 @@ struct OnStream {
   ~OnStream() { x->stream = old; }
 };
 
+// Work forked from `main` onto `side`, joined back on every way out: after a failed launch, too, what
+// the caller enqueues or frees next must not overtake the work already on `side`.
+struct Forked {
+  hipStream_t main;
+  hipStream_t side = nullptr;   // NULL: nothing to join
+  hipEvent_t done = nullptr;
+  hipError_t fork(hipStream_t to, hipEvent_t start, hipEvent_t join_ev) {
+    hipError_t e = hipEventRecord(start, main);
+    if (e == hipSuccess) e = hipStreamWaitEvent(to, start, 0);
+    if (e != hipSuccess) return e;
+    side = to;
+    done = join_ev;
+    return hipSuccess;
+  }
+  hipError_t join() {
+    if (!side) return hipSuccess;
+    const hipStream_t from = side;
+    side = nullptr;
+    hipError_t e = hipEventRecord(done, from);
+    if (e == hipSuccess) e = hipStreamWaitEvent(main, done, 0);
+    if (e != hipSuccess) (void)hipStreamSynchronize(from);
+    return e;
+  }
+  ~Forked() { (void)join(); }
+};
+
 // Every launch of a rollout of T ticks from tick k0 on x->stream: the policy's weight repack,
 // the static shadow system in multi-tick launches, then per tick the policy and the learned
 // system's tick, and the final value. Its arguments depend only on the weights pointer, T, the
@@ -746,21 +772,17 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
   // learned chain on a second stream (forked from and joined back to the rollout's stream,
   // which a graph capture follows); with per-launch timing on, everything stays on one stream
   // so that each kernel's duration is its own.
-  const bool side = x->cfg.shadow && !x->timing;
-  if (side) {
+  Forked shadow{x->stream}, second{x->stream};
+  if (x->cfg.shadow && !x->timing) {
     if (!x->sstream) {
       HIPCHK(hipStreamCreateWithFlags(&x->sstream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
       HIPCHK(hipEventCreateWithFlags(&x->sev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
       HIPCHK(hipEventCreateWithFlags(&x->sev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
     }
-    HIPCHK(hipEventRecord(x->sev_fork, x->stream), "hipEventRecord");
-    HIPCHK(hipStreamWaitEvent(x->sstream, x->sev_fork, 0), "hipStreamWaitEvent");
-    hipStream_t main = x->stream;
-    x->stream = x->sstream;
+    HIPCHK(shadow.fork(x->sstream, x->sev_fork, x->sev_join), "fork of the shadow system's launches");
+    OnStream on(x, x->sstream);
     rc = run_static(x, k0, T, tr->reward_shadow);
-    x->stream = main;
     if (rc) return rc;
-    HIPCHK(hipEventRecord(x->sev_join, x->sstream), "hipEventRecord");
   } else if (x->cfg.shadow) {
     rc = run_static(x, k0, T, tr->reward_shadow);
     if (rc) return rc;
@@ -770,7 +792,7 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
     HIPCHK(x->timed(SIM_KC_ROLLOUT, [&] {
              return launch_rollout_fused(x->p, x->s, x->m, x->fuse_plan, k0, T, o, x->stream);
            }), "fused rollout launch");
-    if (side) HIPCHK(hipStreamWaitEvent(x->stream, x->sev_join, 0), "hipStreamWaitEvent");
+    HIPCHK(shadow.join(), "join of the shadow system's launches");
     return SIM_OK;
   }
   EnvPart parts[2] = {whole(x), {0, 0}};
@@ -801,10 +823,8 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
                                     nullptr, obs_bf);
              }), "policy kernel launch");
       // the second chain starts when the first one's policy is done, a policy behind it
-      if (chains == 2 && i == 0 && h == 0) {
-        HIPCHK(hipEventRecord(x->hev_fork, streams[0]), "hipEventRecord");
-        HIPCHK(hipStreamWaitEvent(streams[1], x->hev_fork, 0), "hipStreamWaitEvent");
-      }
+      if (chains == 2 && i == 0 && h == 0)
+        HIPCHK(second.fork(x->hstream, x->hev_fork, x->hev_join), "fork of the second chain");
       const int mode = !obs_bf ? kObsF32 : i + 1 < T ? kObsBf16 : kObsF32 | kObsBf16;
       rc = enqueue_tick(x, k, tr->actions + row, tr->obs ? tr->obs + (size_t)(i + 1) * F * E : nullptr,
                         tr->reward ? tr->reward + row : nullptr, nullptr,
@@ -812,11 +832,8 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
       if (rc) return rc;
     }
   }
-  if (chains == 2) {
-    HIPCHK(hipEventRecord(x->hev_join, streams[1]), "hipEventRecord");
-    HIPCHK(hipStreamWaitEvent(x->stream, x->hev_join, 0), "hipStreamWaitEvent");
-  }
-  if (side) HIPCHK(hipStreamWaitEvent(x->stream, x->sev_join, 0), "hipStreamWaitEvent");
+  HIPCHK(second.join(), "join of the second chain");
+  HIPCHK(shadow.join(), "join of the shadow system's launches");
   return SIM_OK;
 }
 

@@ -1,0 +1,80 @@
+"""The host runtime's launch sequences (csrc/runtime.cpp linked with the recording stand-ins of
+runtime_stub.cpp, no GPU): a rollout that fails in the middle of its two chains still joins
+every stream it forked back to the caller's."""
+import ctypes as C
+import os
+import subprocess
+
+import pytest
+
+from paper_2607_05272_amd import _lib as L
+from workloads.presets import attn_preset, preset
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CALLER = 1000   # the caller's stream handle
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("stub") / "libstub.so")
+    csrc = os.path.join(ROOT, "paper_2607_05272_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-w",
+                    "-I", "/opt/rocm/include", "-I", csrc, "-I", os.path.join(ROOT, "include"),
+                    os.path.join(csrc, "runtime.cpp"), os.path.join(HERE, "runtime_stub.cpp"),
+                    "-Wl,-Bsymbolic", "-o", out], check=True)
+    lib = C.CDLL(out)
+    lib.stub_log.restype = C.c_char_p
+    return lib
+
+
+class Ctx:
+    """A context over the stand-ins; rollout() returns (status, log lines split into words)."""
+
+    def __init__(self, lib, w, n_envs, fused_cap=0):
+        self.lib, self.cap = lib, fused_cap
+        self.cfg = L.make_cfg(w, n_envs)
+        self.h = C.c_void_p()
+        lib.stub_reset(-1, fused_cap)
+        assert lib.sim_create(C.byref(self.cfg), C.c_void_p(CALLER), C.byref(self.h)) == 0
+        self.created = self.log()
+        assert lib.sim_reset(self.h, C.c_uint64(1)) == 0
+        fields = ["actions", "logp", "reward"] + (["reward_shadow"] if w["shadow"] else []) + \
+            (["value"] if w["value_head"] else [])
+        self.traj = L.SimTraj(**{f: (i + 1) << 40 for i, f in enumerate(fields)})
+
+    def log(self):
+        return [l.split() for l in self.lib.stub_log().decode().splitlines()]
+
+    def rollout(self, T, fail_after=-1, reset=True):
+        if reset:
+            assert self.lib.sim_reset(self.h, C.c_uint64(1)) == 0
+        self.lib.stub_reset(fail_after, self.cap)
+        rc = self.lib.sim_rollout(self.h, C.c_void_p(1 << 50), T, C.byref(self.traj))
+        return rc, self.log()
+
+
+def launches(log, kind):
+    return [l for l in log if l[0] == "launch" and l[2] == kind]
+
+
+def assert_joined(log):
+    """Every stream with a launch is followed by an event that the caller's stream waits for."""
+    for s in {l[1] for l in log if l[0] in ("launch", "graph")} - {str(CALLER)}:
+        last = max(i for i, l in enumerate(log) if l[0] in ("launch", "graph") and l[1] == s)
+        events = [(i, l[2]) for i, l in enumerate(log) if i > last and l[:2] == ["record", s]]
+        assert any(l[:2] == ["wait", str(CALLER)] and l[2] == ev for i, ev in events
+                   for l in log[i:]), f"stream {s} is not joined: {log[last:]}"
+
+
+@pytest.mark.parametrize("name,n", [("C4", 65536), ("C5", 65536)])
+def test_failed_rollout_joins_its_streams(stub, name, n):
+    x = Ctx(stub, preset(name), n)
+    rc, log = x.rollout(8)
+    assert rc == 0 and {l[3] for l in launches(log, "step")} == {"0", "32768"}
+    assert_joined(log)
+    total = sum(l[0] == "launch" for l in log)
+    for k in range(total):
+        rc, log = x.rollout(8, fail_after=k)
+        assert rc == -3
+        assert_joined(log)
