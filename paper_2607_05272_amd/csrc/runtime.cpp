@@ -294,15 +294,16 @@ static bool two_halves(const sim_ctx* x) {
   return x->cfg.n_envs >= (x->cfg.n_servers >= kHalvesLongK ? kHalvesLongE : kHalvesE);
 }
 
-// the second chain's stream and events
-static int second_chain(sim_ctx* x) {
-  if (!x->hstream)
-    HIPCHK(hipStreamCreateWithFlags(&x->hstream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
-  if (!x->hev_fork)
-    HIPCHK(hipEventCreateWithFlags(&x->hev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
-  if (!x->hev_join)
-    HIPCHK(hipEventCreateWithFlags(&x->hev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
-  return SIM_OK;
+// Whether there are the second chain's stream and events, made by the first rollout in halves: a
+// context that fuses its rollouts, steps or trains never needs them. (Without them a rollout is
+// one chain, and so it is under a caller's capture, which need not bear their creation.)
+static bool second_chain(sim_ctx* x) {
+  hipError_t e = hipSuccess;
+  if (!x->hstream) e = hipStreamCreateWithFlags(&x->hstream, hipStreamNonBlocking);
+  if (e == hipSuccess && !x->hev_fork) e = hipEventCreateWithFlags(&x->hev_fork, hipEventDisableTiming);
+  if (e == hipSuccess && !x->hev_join) e = hipEventCreateWithFlags(&x->hev_join, hipEventDisableTiming);
+  if (e != hipSuccess) (void)hipGetLastError();   // not a launch's
+  return e == hipSuccess;
 }
 
 int sim_create(const sim_cfg* cfg, void* hip_stream, sim_ctx** out) {
@@ -387,9 +388,6 @@ int sim_create(const sim_cfg* cfg, void* hip_stream, sim_ctx** out) {
   x->m.b2 = reinterpret_cast<float*>(wp); wp += align256(4 * m.H2);
   x->m.w3 = wp; wp += align256(eb * m.AP * m.H2);
   x->m.b3 = reinterpret_cast<float*>(wp);
-  // made here rather than by the first rollout, which a caller may be capturing; a rollout
-  // without them runs as one chain
-  if (two_halves(x)) (void)second_chain(x);
   *out = x;
   return SIM_OK;
 }
@@ -705,7 +703,7 @@ static bool use_fused(sim_ctx* x) {
 // when the first is almost done (ms, as a graph of one chain, as one of two, and launched: 65536
 // environments with 8 servers, 1024 ticks, 60.9, 64.9 and 52.4; 262144 with 16, 2048 ticks, 606, 647
 // and 575; the four launches of a tick take the host 13 us).
-static bool in_halves(const sim_ctx* x) { return two_halves(x) && x->hev_join && !x->timing; }
+static bool in_halves(const sim_ctx* x) { return two_halves(x) && !x->timing; }
 static bool capturing(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
@@ -796,7 +794,7 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
     return SIM_OK;
   }
   EnvPart parts[2] = {whole(x), {0, 0}};
-  const int chains = in_halves(x) && !capturing(x->stream) ? 2 : 1;
+  const int chains = in_halves(x) && !capturing(x->stream) && second_chain(x) ? 2 : 1;
   hipStream_t streams[2] = {x->stream, x->hstream};
   if (chains == 2) {
     const int n0 = (x->cfg.n_envs / 2 + kPartAlign - 1) / kPartAlign * kPartAlign;

@@ -78,3 +78,12 @@ def test_failed_rollout_joins_its_streams(stub, name, n):
         rc, log = x.rollout(8, fail_after=k)
         assert rc == -3
         assert_joined(log)
+
+
+def test_second_stream_only_for_rollouts_in_halves(stub):
+    x = Ctx(stub, preset("C4"), 65536)
+    assert not [l for l in x.created if l[0] == "stream"]   # a context may never roll out in halves
+    rc, log = x.rollout(64)
+    assert rc == 0 and len([l for l in log if l[0] == "stream"]) == 1
+    rc, log = x.rollout(65)
+    assert rc == 0 and not [l for l in log if l[0] == "stream"]
