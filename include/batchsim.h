@@ -262,10 +262,12 @@ int sim_rollout(sim_ctx* ctx, const void* d_weights, int32_t T, const sim_traj* 
  * graph on a private stream of the context, and that graph is replayed by every further
  * repeat (ordered after earlier work on the context's stream, and before later work, by
  * events). Kernels read the seed from device memory written by sim_reset, so a new seed needs
- * no new graph. Tracing (sim_set_timing) launches eagerly, and so do per-tick rollouts in two
- * halves of the batch (from 8192 environments, 2048 with four servers or more, unless fused):
- * the halves' launches run side by side, which a
- * replayed graph's branches would not. sim_set_trace discards the graph.
+ * no new graph. Tracing (sim_set_timing) launches eagerly. Per-tick rollouts in two halves of the
+ * batch (from 8192 environments, 2048 with four servers or more, unless fused) run as two chains
+ * of launches side by side, which one replayed graph's branches would not: with up to three
+ * servers a repeat of 128 ticks or more replays a graph per half and 256 ticks, other such
+ * rollouts are launched (the host then takes about 14 us per tick). sim_set_trace discards the
+ * graphs.
  * on = 0 launches every rollout eagerly.                                                    */
 int sim_set_graphs(sim_ctx* ctx, int32_t on);
 
@@ -284,8 +286,8 @@ int sim_set_graphs(sim_ctx* ctx, int32_t on);
 enum { SIM_FUSE_OFF = 0, SIM_FUSE_AUTO = 1, SIM_FUSE_ON = 2 };
 int sim_set_fused_rollout(sim_ctx* ctx, int32_t mode);
 
-/* Diagnostics of the rollout graphs: graphs captured and rollouts replayed from a graph so far
- * (either pointer may be NULL).                                                          */
+/* Diagnostics of the rollout graphs: graphs of a whole rollout captured, and rollouts replayed
+ * from one, so far (either pointer may be NULL).                                         */
 int sim_graph_stats(sim_ctx* ctx, int64_t* h_captures, int64_t* h_replays);
 
 /* Discounted returns and GAE (Sec. 4.3), per environment backwards in t:

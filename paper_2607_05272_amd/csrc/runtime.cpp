@@ -84,6 +84,7 @@ struct sim_ctx {
   hipStream_t gstream = nullptr;
   hipEvent_t gev_in = nullptr, gev_out = nullptr;
   hipGraphExec_t rgraph = nullptr;
+  std::vector<hipGraphExec_t> rchain[2];   // of a rollout in halves: each chain's runs of ticks
   // a rollout's static shadow launches run on a second stream (default priority), forked
   // from and joined back to the rollout's stream by events
   hipStream_t sstream = nullptr;
@@ -392,6 +393,19 @@ int sim_create(const sim_cfg* cfg, void* hip_stream, sim_ctx** out) {
   return SIM_OK;
 }
 
+// the graphs of the rollout captured last, once their replays are done
+static void drop_graphs(sim_ctx* x) {
+  x->rkey_valid = false;
+  if (x->gstream) (void)hipStreamSynchronize(x->gstream);
+  if (x->hstream) (void)hipStreamSynchronize(x->hstream);
+  if (x->rgraph) (void)hipGraphExecDestroy(x->rgraph);
+  x->rgraph = nullptr;
+  for (auto& chain : x->rchain) {
+    for (hipGraphExec_t g : chain) (void)hipGraphExecDestroy(g);
+    chain.clear();
+  }
+}
+
 int sim_destroy(sim_ctx* x) {
   if (!x) return SIM_OK;
   (void)hipStreamSynchronize(x->stream);
@@ -404,7 +418,7 @@ int sim_destroy(sim_ctx* x) {
   (void)hipFree(x->wpack);
   (void)hipFree(x->ppo_scratch);
   (void)hipFree(x->grads);
-  if (x->rgraph) (void)hipGraphExecDestroy(x->rgraph);
+  drop_graphs(x);
   if (x->gev_in) (void)hipEventDestroy(x->gev_in);
   if (x->gev_out) (void)hipEventDestroy(x->gev_out);
   if (x->gstream) {
@@ -613,7 +627,8 @@ static int repack_weights(sim_ctx* x, const void* d_weights) {
   return SIM_OK;
 }
 
-static int prepare_policy(sim_ctx* x, const void* d_weights) {
+// the shape check, and where the attention policy's kernels find the weights
+static int point_policy(sim_ctx* x, const void* d_weights) {
   if (x->cfg.policy_kind == SIM_POLICY_ATTN) {
     AttnParams& a = x->a;
     if (!attn_shape_supported(a))
@@ -632,7 +647,12 @@ static int prepare_policy(sim_ctx* x, const void* d_weights) {
     return fail(SIM_EUNSUPPORTED,
                 "policy shape (bf16=%d, F_pad=%d, H1=%d, H2=%d, A_pad=%d) is not compiled",
                 x->m.bf16, x->m.FP, x->m.H1, x->m.H2, x->m.AP);
-  return repack_weights(x, d_weights);
+  return SIM_OK;
+}
+
+static int prepare_policy(sim_ctx* x, const void* d_weights) {
+  const int rc = point_policy(x, d_weights);
+  return rc || x->cfg.policy_kind == SIM_POLICY_ATTN ? rc : repack_weights(x, d_weights);
 }
 
 // the policy kernel of the configured network (after prepare_policy)
@@ -698,17 +718,19 @@ static bool use_fused(sim_ctx* x) {
 }
 
 // whether a rollout's launches (when they are not fused) form two chains now. With per-launch timing
-// on they form one, so that each kernel's duration is its own, and under a capture: a graph's
+// on they form one, so that each kernel's duration is its own, and under a caller's capture: a graph's
 // branches are submitted one after the other, so the second chain of a long rollout would start
 // when the first is almost done (ms, as a graph of one chain, as one of two, and launched: 65536
 // environments with 8 servers, 1024 ticks, 60.9, 64.9 and 52.4; 262144 with 16, 2048 ticks, 606, 647
-// and 575; the four launches of a tick take the host 13 us).
-static bool in_halves(const sim_ctx* x) { return two_halves(x) && !x->timing; }
+// and 575).
 static bool capturing(hipStream_t st) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
   (void)hipGetLastError();   // not a launch's
   return false;
+}
+static bool in_halves(sim_ctx* x, bool captured) {
+  return two_halves(x) && !x->timing && !captured && !use_fused(x) && second_chain(x);
 }
 
 // x->stream set to another stream for a scope
@@ -745,91 +767,145 @@ struct Forked {
   ~Forked() { (void)join(); }
 };
 
-// Every launch of a rollout of T ticks from tick k0 on x->stream: the policy's weight repack,
-// the static shadow system in multi-tick launches, then per tick the policy and the learned
-// system's tick, and the final value. Its arguments depend only on the weights pointer, T, the
-// trajectory pointers and k0 (the seed is read from device memory), so the sequence can be
-// captured once as a graph and replayed.
-static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr,
-                           uint32_t k0) {
+// What precedes a rollout's ticks on x->stream: the policy's weight repack, the bf16 observation
+// pairs and, beside the ticks, the static shadow system in multi-tick launches.
+static int enqueue_head(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr, uint32_t k0,
+                        bool fused, Forked& shadow) {
   int rc = prepare_policy(x, d_weights);
   if (rc) return rc;
-  const size_t E = (size_t)x->cfg.n_envs, F = (size_t)x->cfg.obs_dim;
   // a bf16 policy reads the observation as bf16 pairs, which the ticks write instead of the
   // fp32 observation (half its bytes, both for the tick that writes it and the policy that
-  // reads it); the fp32 observation is written again by the last tick
-  const uint32_t* obs_bf = x->s.obs_bf;
-  const bool fused = use_fused(x);
-  // packed ahead of the shadow's launch, whose waves fill every CU as they come: behind them the
+  // reads it); the fp32 observation is written again by the last tick.
+  // Packed ahead of the shadow's launch, whose waves fill every CU as they come: behind them the
   // whole chain waited (16 servers, us per tick: 131072 environments x 512 160.4 -> 156.6, 262144 x
   // 1024 281.0 -> 271.4)
-  if (obs_bf && !fused)
+  if (x->s.obs_bf && !fused)
     HIPCHK(x->timed(SIM_KC_OTHER, [&] { return launch_obs_pack(x->p, x->s, x->stream); }),
            "observation packing launch");
   // The static shadow system never reads the learned system, so its launches run beside the
   // learned chain on a second stream (forked from and joined back to the rollout's stream,
   // which a graph capture follows); with per-launch timing on, everything stays on one stream
   // so that each kernel's duration is its own.
-  Forked shadow{x->stream}, second{x->stream};
-  if (x->cfg.shadow && !x->timing) {
-    if (!x->sstream) {
-      HIPCHK(hipStreamCreateWithFlags(&x->sstream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
-      HIPCHK(hipEventCreateWithFlags(&x->sev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
-      HIPCHK(hipEventCreateWithFlags(&x->sev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
-    }
-    HIPCHK(shadow.fork(x->sstream, x->sev_fork, x->sev_join), "fork of the shadow system's launches");
-    OnStream on(x, x->sstream);
-    rc = run_static(x, k0, T, tr->reward_shadow);
-    if (rc) return rc;
-  } else if (x->cfg.shadow) {
-    rc = run_static(x, k0, T, tr->reward_shadow);
-    if (rc) return rc;
+  if (!x->cfg.shadow) return SIM_OK;
+  if (x->timing) return run_static(x, k0, T, tr->reward_shadow);
+  if (!x->sstream) {
+    HIPCHK(hipStreamCreateWithFlags(&x->sstream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
+    HIPCHK(hipEventCreateWithFlags(&x->sev_fork, hipEventDisableTiming), "hipEventCreateWithFlags");
+    HIPCHK(hipEventCreateWithFlags(&x->sev_join, hipEventDisableTiming), "hipEventCreateWithFlags");
   }
+  HIPCHK(shadow.fork(x->sstream, x->sev_fork, x->sev_join), "fork of the shadow system's launches");
+  OnStream on(x, x->sstream);
+  return run_static(x, k0, T, tr->reward_shadow);
+}
+
+// A part's chain of launches: item 2 i is tick i's policy, item 2 i + 1 the learned system's tick, and
+// item 2 T the policy for the final value.
+static int64_t chain_items(int32_t T, const sim_traj* tr) { return 2 * (int64_t)T + (tr->value ? 1 : 0); }
+// items a .. b - 1 on x->stream
+static int enqueue_items(sim_ctx* x, int32_t T, const sim_traj* tr, uint32_t k0, EnvPart part,
+                         int64_t a, int64_t b) {
+  const size_t E = (size_t)x->cfg.n_envs, F = (size_t)x->cfg.obs_dim;
+  const uint32_t* obs_bf = x->s.obs_bf;
+  for (int64_t it = a; it < b; ++it) {
+    const int64_t i = it / 2;
+    const size_t row = (size_t)i * E;
+    const uint32_t k = k0 + (uint32_t)i;
+    if (i == T) {
+      HIPCHK(x->timed(SIM_KC_POLICY, [&] {
+               return policy_launch(x, x->s.obs, k, nullptr, nullptr, tr->value + row, nullptr,
+                                    part, nullptr, obs_bf);
+             }), "policy kernel launch (final value)");
+    } else if (it % 2 == 0) {
+      HIPCHK(x->timed(SIM_KC_POLICY, [&] {
+               return policy_launch(x, x->s.obs, k, tr->actions + row,
+                                    tr->logp ? tr->logp + row : nullptr,
+                                    tr->value ? tr->value + row : nullptr, nullptr, part,
+                                    nullptr, obs_bf);
+             }), "policy kernel launch");
+    } else {
+      const int mode = !obs_bf ? kObsF32 : i + 1 < T ? kObsBf16 : kObsF32 | kObsBf16;
+      int rc = enqueue_tick(x, k, tr->actions + row, tr->obs ? tr->obs + (size_t)(i + 1) * F * E : nullptr,
+                            tr->reward ? tr->reward + row : nullptr, nullptr,
+                            tr->rchk ? tr->rchk + row : nullptr, false, part, mode);
+      if (rc) return rc;
+    }
+  }
+  return SIM_OK;
+}
+
+// Every launch of a rollout of T ticks from tick k0 on x->stream, fused or as one chain of the whole
+// batch. Its arguments depend only on the weights pointer, T, the trajectory pointers and k0 (the
+// seed is read from device memory), so the sequence can be captured once as a graph and replayed.
+static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr,
+                           uint32_t k0) {
+  const bool fused = use_fused(x);
+  Forked shadow{x->stream};
+  int rc = enqueue_head(x, d_weights, T, tr, k0, fused, shadow);
+  if (rc) return rc;
   if (fused) {
     const RolloutOut o{tr->actions, tr->logp, tr->value, tr->reward, tr->rchk, tr->obs};
     HIPCHK(x->timed(SIM_KC_ROLLOUT, [&] {
              return launch_rollout_fused(x->p, x->s, x->m, x->fuse_plan, k0, T, o, x->stream);
            }), "fused rollout launch");
-    HIPCHK(shadow.join(), "join of the shadow system's launches");
-    return SIM_OK;
+  } else {
+    rc = enqueue_items(x, T, tr, k0, whole(x), 0, chain_items(T, tr));
+    if (rc) return rc;
   }
-  EnvPart parts[2] = {whole(x), {0, 0}};
-  const int chains = in_halves(x) && !capturing(x->stream) && second_chain(x) ? 2 : 1;
-  hipStream_t streams[2] = {x->stream, x->hstream};
-  if (chains == 2) {
-    const int n0 = (x->cfg.n_envs / 2 + kPartAlign - 1) / kPartAlign * kPartAlign;
-    parts[0] = {0, n0};
-    parts[1] = {n0, x->cfg.n_envs - n0};
-  }
-  for (int32_t i = 0; i <= T; ++i) {
-    const size_t row = (size_t)i * E;
-    const uint32_t k = k0 + (uint32_t)i;
-    if (i == T && !tr->value) break;
-    for (int h = 0; h < chains; ++h) {
+  HIPCHK(shadow.join(), "join of the shadow system's launches");
+  return SIM_OK;
+}
+
+// A repeated rollout in two halves can be replayed from graphs, one per half and kRunTicks ticks,
+// launched in turn on the halves' streams, so that both chains are under way from the start (the
+// first policy of all is launched by itself). It takes the host 1.5 us per tick where a tick's four
+// launches take 13.6; but a graph's nodes follow each other 0.4 to 0.9 us later than launches, and the
+// replay's own forks and joins take 35 us. So long rollouts of few servers, whose ticks of 17 to 37 us a
+// busy or slower host would hold up, are replayed (ms on the GPU and of the host, launched and replayed:
+// one server 40000 environments x 512 14.1 and 6.9, 14.7 and 0.8; 12-128-128-6 131072 x 512 17.4 and 6.7,
+// 17.7 and 0.8; attention policy 65536 x 256 9.5 and 3.9, 9.7 and 0.5), and those with longer ticks
+// launched (8 servers 65536 x 1024 53.6 and 15.8, 54.5 and 1.6; 4 servers 65536 x 256 10.4 and 3.9, 10.5
+// and 0.5). Runs of 64 ticks take the host 2.1 us per tick.
+constexpr int64_t kRunTicks = 256;
+constexpr int32_t kReplayTicks = 128;
+static bool halves_replayed(const sim_ctx* x, int32_t T) {
+  return x->cfg.n_servers < kHalvesLongK && T >= kReplayTicks;
+}
+static EnvPart half(const sim_ctx* x, int h) {
+  const int n0 = (x->cfg.n_envs / 2 + kPartAlign - 1) / kPartAlign * kPartAlign;
+  return h == 0 ? EnvPart{0, n0} : EnvPart{n0, x->cfg.n_envs - n0};
+}
+// the items of chain h in its run r of `ticks` ticks
+struct Run {
+  int64_t a, b;
+};
+static Run run_of(int h, int64_t r, int64_t ticks, int64_t items) {
+  return {r == 0 && h == 0 ? 1 : 2 * ticks * r, std::min(2 * ticks * (r + 1), items)};
+}
+
+// Every launch of a rollout as two chains, one per half of the batch, from x->stream: `replay` its
+// captured runs, else a tick of each chain in turn.
+static int enqueue_halves(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr, uint32_t k0,
+                          bool replay) {
+  Forked shadow{x->stream}, second{x->stream};
+  int rc = enqueue_head(x, d_weights, T, tr, k0, false, shadow);
+  if (rc) return rc;
+  // the second chain starts when the first one's policy is done, a policy behind it
+  rc = enqueue_items(x, T, tr, k0, half(x, 0), 0, 1);
+  if (rc) return rc;
+  HIPCHK(second.fork(x->hstream, x->hev_fork, x->hev_join), "fork of the second chain");
+  const hipStream_t streams[2] = {x->stream, x->hstream};
+  const int64_t items = chain_items(T, tr), ticks = replay ? kRunTicks : 1;
+  for (int64_t r = 0; 2 * ticks * r < items; ++r)
+    for (int h = 0; h < 2; ++h) {
       OnStream on(x, streams[h]);
-      if (i == T) {
-        HIPCHK(x->timed(SIM_KC_POLICY, [&] {
-                 return policy_launch(x, x->s.obs, k, nullptr, nullptr, tr->value + row, nullptr,
-                                      parts[h], nullptr, obs_bf);
-               }), "policy kernel launch (final value)");
+      if (replay) {
+        HIPCHK(hipGraphLaunch(x->rchain[h][(size_t)r], x->stream), "hipGraphLaunch");
         continue;
       }
-      HIPCHK(x->timed(SIM_KC_POLICY, [&] {
-               return policy_launch(x, x->s.obs, k, tr->actions + row,
-                                    tr->logp ? tr->logp + row : nullptr,
-                                    tr->value ? tr->value + row : nullptr, nullptr, parts[h],
-                                    nullptr, obs_bf);
-             }), "policy kernel launch");
-      // the second chain starts when the first one's policy is done, a policy behind it
-      if (chains == 2 && i == 0 && h == 0)
-        HIPCHK(second.fork(x->hstream, x->hev_fork, x->hev_join), "fork of the second chain");
-      const int mode = !obs_bf ? kObsF32 : i + 1 < T ? kObsBf16 : kObsF32 | kObsBf16;
-      rc = enqueue_tick(x, k, tr->actions + row, tr->obs ? tr->obs + (size_t)(i + 1) * F * E : nullptr,
-                        tr->reward ? tr->reward + row : nullptr, nullptr,
-                        tr->rchk ? tr->rchk + row : nullptr, false, parts[h], mode);
+      const Run run = run_of(h, r, 1, items);
+      rc = enqueue_items(x, T, tr, k0, half(x, h), run.a, run.b);
       if (rc) return rc;
     }
-  }
   HIPCHK(second.join(), "join of the second chain");
   HIPCHK(shadow.join(), "join of the shadow system's launches");
   return SIM_OK;
@@ -839,49 +915,75 @@ static bool same_key(const RolloutKey& a, const RolloutKey& b) {
   return a.w == b.w && a.T == b.T && a.k0 == b.k0 && std::memcmp(&a.tr, &b.tr, sizeof a.tr) == 0;
 }
 
-// Captures the rollout's launch sequence on the context's private stream into a graph.
-static int capture_rollout(sim_ctx* x, const RolloutKey& key, const sim_traj* tr) {
+}  // extern "C"
+
+// What `enqueue` puts on x->stream, captured on the context's private stream into a graph.
+template <class F>
+static int capture(sim_ctx* x, hipGraphExec_t* out, F&& enqueue) {
+  OnStream on(x, x->gstream);
+  hipError_t e = hipStreamBeginCapture(x->gstream, hipStreamCaptureModeThreadLocal);
+  if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
+  int rc = enqueue();
+  hipGraph_t g = nullptr;
+  e = hipStreamEndCapture(x->gstream, &g);
+  if (e != hipSuccess && rc == SIM_OK) rc = hip_fail(e, "hipStreamEndCapture");
+  if (rc == SIM_OK) {
+    e = hipGraphInstantiate(out, g, nullptr, nullptr, 0);
+    if (e != hipSuccess) rc = hip_fail(e, "hipGraphInstantiate");
+  }
+  if (g) (void)hipGraphDestroy(g);
+  return rc;
+}
+
+extern "C" {
+
+// Captures the rollout's launches, in halves run by run of each chain.
+static int capture_rollout(sim_ctx* x, const RolloutKey& key, const sim_traj* tr, bool halves) {
   if (!x->gstream) {
     HIPCHK(hipStreamCreateWithFlags(&x->gstream, hipStreamNonBlocking), "hipStreamCreateWithFlags");
     HIPCHK(hipEventCreateWithFlags(&x->gev_in, hipEventDisableTiming), "hipEventCreateWithFlags");
     HIPCHK(hipEventCreateWithFlags(&x->gev_out, hipEventDisableTiming), "hipEventCreateWithFlags");
   }
-  hipStream_t caller = x->stream;
-  x->stream = x->gstream;
-  hipError_t e = hipStreamBeginCapture(x->gstream, hipStreamCaptureModeThreadLocal);
-  int rc = e == hipSuccess ? enqueue_rollout(x, key.w, key.T, tr, key.k0) : SIM_EDEVICE;
-  hipGraph_t g = nullptr;
-  if (e == hipSuccess) {
-    const hipError_t e2 = hipStreamEndCapture(x->gstream, &g);
-    if (e2 != hipSuccess && rc == SIM_OK) rc = hip_fail(e2, "hipStreamEndCapture");
+  drop_graphs(x);
+  int rc = SIM_OK;
+  if (!halves) {
+    rc = capture(x, &x->rgraph, [&] { return enqueue_rollout(x, key.w, key.T, tr, key.k0); });
+    if (rc) return rc;
+    x->graph_captures++;
   } else {
-    rc = hip_fail(e, "hipStreamBeginCapture");
+    rc = point_policy(x, key.w);
+    const int64_t items = chain_items(key.T, tr);
+    for (int h = 0; h < 2; ++h)
+      for (int64_t r = 0; 2 * kRunTicks * r < items && rc == SIM_OK; ++r) {
+        const Run run = run_of(h, r, kRunTicks, items);
+        hipGraphExec_t g = nullptr;
+        rc = capture(x, &g, [&] { return enqueue_items(x, key.T, tr, key.k0, half(x, h), run.a, run.b); });
+        if (rc == SIM_OK) x->rchain[h].push_back(g);
+      }
+    if (rc) {
+      drop_graphs(x);
+      return rc;
+    }
   }
-  x->stream = caller;
-  hipGraphExec_t ex = nullptr;
-  if (rc == SIM_OK && g) {
-    e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-    if (e != hipSuccess) rc = hip_fail(e, "hipGraphInstantiate");
-  }
-  if (g) (void)hipGraphDestroy(g);
-  if (rc) return rc;
-  if (x->rgraph) (void)hipGraphExecDestroy(x->rgraph);
-  x->rgraph = ex;
   x->rkey = key;
   x->rkey_valid = true;
-  x->graph_captures++;
   return SIM_OK;
 }
 
 // Replays the captured rollout on the private stream, ordered after the work already on the
 // caller's stream and before any work enqueued there later.
-static int replay_rollout(sim_ctx* x) {
-  HIPCHK(hipEventRecord(x->gev_in, x->stream), "hipEventRecord");
-  HIPCHK(hipStreamWaitEvent(x->gstream, x->gev_in, 0), "hipStreamWaitEvent");
-  HIPCHK(hipGraphLaunch(x->rgraph, x->gstream), "hipGraphLaunch");
-  HIPCHK(hipEventRecord(x->gev_out, x->gstream), "hipEventRecord");
-  HIPCHK(hipStreamWaitEvent(x->stream, x->gev_out, 0), "hipStreamWaitEvent");
-  x->graph_replays++;
+static int replay_rollout(sim_ctx* x, const RolloutKey& key, const sim_traj* tr, bool halves) {
+  Forked replay{x->stream};
+  HIPCHK(replay.fork(x->gstream, x->gev_in, x->gev_out), "fork of the replay");
+  if (halves) {
+    OnStream on(x, x->gstream);
+    const int rc = enqueue_halves(x, key.w, key.T, tr, key.k0, true);
+    if (rc) return rc;
+  } else {
+    HIPCHK(hipGraphLaunch(x->rgraph, x->gstream), "hipGraphLaunch");
+    x->graph_replays++;
+  }
+  HIPCHK(replay.join(), "join of the replay");
   return SIM_OK;
 }
 
@@ -898,14 +1000,16 @@ int sim_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr
     HIPCHK(hipMemcpyAsync(tr->obs, x->s.obs, 4 * F * E, hipMemcpyDeviceToDevice, x->stream),
            "hipMemcpyAsync obs_0");
   const RolloutKey key{d_weights, T, *tr, x->tick};
+  const bool captured = capturing(x->stream), halves = in_halves(x, captured);
   int rc;
-  if (x->graphs && !x->timing && (!in_halves(x) || use_fused(x))) {
+  if (x->graphs && !x->timing && !captured && (!halves || halves_replayed(x, T))) {
     // a call that repeats the previous one (same weights, length, outputs, starting tick) is
-    // captured as a graph; later repeats replay it
-    bool have = x->rkey_valid && same_key(key, x->rkey);
-    if (!have && x->seen_valid && same_key(key, x->seen)) have = capture_rollout(x, key, tr) == SIM_OK;
+    // captured as a graph, or as one per run of ticks of each half; later repeats replay it
+    bool have = x->rkey_valid && same_key(key, x->rkey) && halves == !x->rchain[0].empty();
+    if (!have && x->seen_valid && same_key(key, x->seen))
+      have = capture_rollout(x, key, tr, halves) == SIM_OK;
     if (have) {
-      rc = replay_rollout(x);
+      rc = replay_rollout(x, key, tr, halves);
       if (rc) return rc;
       x->tick += (uint32_t)T;
       return SIM_OK;
@@ -913,7 +1017,8 @@ int sim_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr
     x->seen = key;
     x->seen_valid = true;
   }
-  rc = enqueue_rollout(x, d_weights, T, tr, x->tick);
+  rc = halves ? enqueue_halves(x, d_weights, T, tr, x->tick, false)
+              : enqueue_rollout(x, d_weights, T, tr, x->tick);
   if (rc) return rc;
   x->tick += (uint32_t)T;
   return SIM_OK;

@@ -2,8 +2,9 @@
 whole batch (per-launch timing on) bit for bit: at and past each size from which the halves are
 taken and at those where their waves take fewer environments, with a ragged last tile in the
 second half, for every policy kernel, with the value row, stored observations and the static
-shadow system beside them, several times with other work on the caller's stream in between (such
-rollouts are not captured as graphs); and inside a caller's own capture."""
+shadow system beside them, several times with other work on the caller's stream in between (short
+such rollouts are not captured as graphs; long ones of few servers are, run by run); and inside a
+caller's own capture."""
 import pytest
 
 from test_gpu_fused import assert_same, bs, snapshot, weights  # noqa: F401
@@ -66,3 +67,30 @@ def test_rollout_in_a_callers_capture(bs):  # noqa: F811
             got = snapshot(sim, tr)
             del got["state"]   # its tick counter is the host's, which a replay does not advance
             assert_same({k: ref[k] for k in got}, got, f"replay {i}")
+
+
+@pytest.mark.parametrize("name,kw,E,T", [("C1", dict(shadow=1), 8200, 300), ("C2", dict(value_head=1), 8449, 256),
+                                         ("attn", {}, 41100, 130)])
+def test_replayed_halves_match_one_chain(bs, name, kw, E, T):  # noqa: F811
+    """Long rollouts of few servers: launched, captured and replayed run by run, with a new seed that
+    only device memory carries and other device work between the replays."""
+    w = attn_preset(**kw) if name == "attn" else preset(name, **kw)
+    seeds, ref = (0xA1, 0xA1, 0xA2, 0xA1, 0xA2), {}
+    for one_chain in (True, False):
+        with bs.Sim(w, n_envs=E) as sim:
+            sim.set_fused_rollout(bs.FUSE_OFF)
+            sim.set_timing(one_chain)
+            wb = sim.init_weights(7) if name == "attn" else sim.upload_weights(weights(w, 21))
+            tr = None
+            for i, seed in enumerate(seeds[1:3] if one_chain else seeds):
+                sim.reset(seed)
+                tr = sim.rollout(wb, T, rchk=True, traj=tr)
+                out = snapshot(sim, tr)
+                if i > 2:   # a ring's unused slots keep the previous episode's times
+                    del out["state"]
+                if one_chain:
+                    ref[seed] = out
+                else:
+                    assert_same({k: ref[seed][k] for k in out}, out, f"{name} E={E}, call {i}")
+                for t in (tr.actions, tr.reward, tr.rchk):
+                    t.zero_()

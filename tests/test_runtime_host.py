@@ -1,6 +1,7 @@
 """The host runtime's launch sequences (csrc/runtime.cpp linked with the recording stand-ins of
 runtime_stub.cpp, no GPU): a rollout that fails in the middle of its two chains still joins
-every stream it forked back to the caller's."""
+every stream it forked back to the caller's; the second stream is made when a rollout needs it; a
+repeated rollout in halves is replayed from graphs."""
 import ctypes as C
 import os
 import subprocess
@@ -58,24 +59,38 @@ def launches(log, kind):
     return [l for l in log if l[0] == "launch" and l[2] == kind]
 
 
+def joined(log, s, after):
+    """Whether the caller's stream waits, directly or over others, for what s holds at `after`."""
+    return any(l[0] == "wait" and l[2] == ev and (l[1] == str(CALLER) or joined(log, l[1], j))
+               for i, ev in [(i, l[2]) for i, l in enumerate(log) if i > after and l[:2] == ["record", s]]
+               for j, l in enumerate(log) if j > i)
+
+
 def assert_joined(log):
-    """Every stream with a launch is followed by an event that the caller's stream waits for."""
     for s in {l[1] for l in log if l[0] in ("launch", "graph")} - {str(CALLER)}:
         last = max(i for i, l in enumerate(log) if l[0] in ("launch", "graph") and l[1] == s)
-        events = [(i, l[2]) for i, l in enumerate(log) if i > last and l[:2] == ["record", s]]
-        assert any(l[:2] == ["wait", str(CALLER)] and l[2] == ev for i, ev in events
-                   for l in log[i:]), f"stream {s} is not joined: {log[last:]}"
+        assert joined(log, s, last), f"stream {s} is not joined: {log[last:]}"
 
 
 @pytest.mark.parametrize("name,n", [("C4", 65536), ("C5", 65536)])
 def test_failed_rollout_joins_its_streams(stub, name, n):
     x = Ctx(stub, preset(name), n)
+    assert stub.sim_set_graphs(x.h, 0) == 0
     rc, log = x.rollout(8)
     assert rc == 0 and {l[3] for l in launches(log, "step")} == {"0", "32768"}
     assert_joined(log)
     total = sum(l[0] == "launch" for l in log)
     for k in range(total):
         rc, log = x.rollout(8, fail_after=k)
+        assert rc == -3
+        assert_joined(log)
+    # the same of a replay (three servers at most): its launches are the head's and the first policy
+    x = Ctx(stub, preset(name, n_servers=3), n)
+    x.rollout(128)
+    rc, log = x.rollout(128)
+    assert rc == 0 and [l for l in log if l[0] == "graph"]
+    for k in range(sum(l[0] == "launch" for l in log)):
+        rc, log = x.rollout(128, fail_after=k)
         assert rc == -3
         assert_joined(log)
 
@@ -87,3 +102,27 @@ def test_second_stream_only_for_rollouts_in_halves(stub):
     assert rc == 0 and len([l for l in log if l[0] == "stream"]) == 1
     rc, log = x.rollout(65)
     assert rc == 0 and not [l for l in log if l[0] == "stream"]
+
+
+@pytest.mark.parametrize("w,n,T", [(preset("C2"), 40000, 600), (preset("C1"), 40000, 256),
+                                   (attn_preset(), 65536, 256),
+                                   (preset("C3", n_servers=2, obs_dim=18), 65536, 128)])
+def test_repeated_rollout_in_halves_is_replayed(stub, w, n, T):
+    x = Ctx(stub, w, n)
+    rc, first = x.rollout(T)
+    assert rc == 0 and not [l for l in first if l[0] == "graph"]
+    per_chain = 2 * T + (1 if w["value_head"] else 0)
+    for i in range(3):   # captured and replayed, then replayed
+        rc, log = x.rollout(T)
+        assert rc == 0
+        assert_joined(log)
+        # the host's part no longer grows with every tick's launches
+        assert len([l for l in log if l[0] == "launch"]) <= 4
+        g = [l for l in log if l[0] == "graph"]
+        assert len(g) == 2 * -(-per_chain // 512)
+        assert all(a[1] != b[1] for a, b in zip(g, g[1:])), "the chains' graphs take turns"
+        first_policy = len(launches(log, "policy"))
+        assert sum(int(l[2]) for l in g) + first_policy == 2 * per_chain and first_policy == 1
+    # another length is launched again
+    rc, log = x.rollout(T + 1)
+    assert rc == 0 and not [l for l in log if l[0] == "graph"]
