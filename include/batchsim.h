@@ -262,11 +262,12 @@ int sim_rollout(sim_ctx* ctx, const void* d_weights, int32_t T, const sim_traj* 
  * graph on a private stream of the context, and that graph is replayed by every further
  * repeat (ordered after earlier work on the context's stream, and before later work, by
  * events). Kernels read the seed from device memory written by sim_reset, so a new seed needs
- * no new graph. Tracing (sim_set_timing) launches eagerly. Per-tick rollouts in two halves of the
- * batch (from 8192 environments, 2048 with four servers or more, unless fused) run as two chains
- * of launches side by side, which one replayed graph's branches would not: with up to three
- * servers a repeat of 128 ticks or more replays a graph per half and 256 ticks, other such
- * rollouts are launched (the host then takes about 14 us per tick). sim_set_trace discards the
+ * no new graph. Tracing (sim_set_timing) launches eagerly. Per-tick rollouts of large
+ * batches (from 8192 environments, 2048 with four servers or more, unless fused) run as two chains
+ * of launches side by side, one per half of the batch, from 16 ticks (fewer with many environments
+ * and servers), which one replayed graph's branches would not: with up to three servers and 40960
+ * environments a repeat of 128 ticks or more replays a graph per half and 256 ticks, other rollouts
+ * of such batches are launched (the host then takes about 14 us per tick in two chains). sim_set_trace discards the
  * graphs.
  * on = 0 launches every rollout eagerly.                                                    */
 int sim_set_graphs(sim_ctx* ctx, int32_t on);

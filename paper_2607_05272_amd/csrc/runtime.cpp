@@ -290,9 +290,23 @@ static void derive(sim_ctx* x) {
 // servers 2048 19.8, 18.9, 40000 38.0, 30.8; 8 servers 17000 41.6, 38.5; 16 servers 2048 35.7, 33.4,
 // 17000 56.9, 48.3; attention policy 8192 20.6, 19.1, 262144 65.3, 54. Ticks of few servers and small
 // batches are too short for four launches in place of two (one server 4096 16.8, 17.1).
+// The second chain's fork and join take 25 to 45 us of a rollout, which a tick in halves earns back at
+// 1 to 3 us, with many environments and servers (the attention policy counted as one) at 5 to 30: so
+// from 16 ticks, or with those from 2^21 of the three's product. Us per rollout that goes on from the
+// last, one chain and two: one server 65536 x 1 34, 66, x 16 513, 518; attention policy 65536 x 1 59, 102,
+// x 8 312, 356; 262144 x 4 288, 280; 12-128-128-6 131072 x 8 294, 302, x 16 582, 564; 8 servers 17000 x
+// 8 314, 335, x 16 610, 620, x 32 1202, 1191; 65536 x 4 266, 273, x 8 497, 487; 16 servers 16384 x 8 451,
+// 508; 65536 x 2 319, 299, x 8 1009, 881.
 constexpr int kHalvesE = 8192, kHalvesLongE = 2048, kHalvesLongK = 4;
+constexpr int32_t kHalvesT = 16;
+constexpr int64_t kHalvesRows = 1 << 19, kHalvesRowTicks = 1 << 21;
 static bool two_halves(const sim_ctx* x) {
   return x->cfg.n_envs >= (x->cfg.n_servers >= kHalvesLongK ? kHalvesLongE : kHalvesE);
+}
+static bool halves_pay(const sim_ctx* x, int32_t T) {
+  const bool attn = x->cfg.policy_kind == SIM_POLICY_ATTN;
+  const int64_t rows = (int64_t)x->cfg.n_envs * (x->cfg.n_servers + (attn ? 1 : 0));
+  return T >= kHalvesT || (rows >= kHalvesRows && T * rows >= kHalvesRowTicks);
 }
 
 // Whether there are the second chain's stream and events, made by the first rollout in halves: a
@@ -729,8 +743,9 @@ static bool capturing(hipStream_t st) {
   (void)hipGetLastError();   // not a launch's
   return false;
 }
-static bool in_halves(sim_ctx* x, bool captured) {
-  return two_halves(x) && !x->timing && !captured && !use_fused(x) && second_chain(x);
+static bool in_halves(sim_ctx* x, int32_t T, bool captured) {
+  return two_halves(x) && halves_pay(x, T) && !x->timing && !captured && !use_fused(x) &&
+         second_chain(x);
 }
 
 // x->stream set to another stream for a scope
@@ -859,16 +874,17 @@ static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const s
 // launched in turn on the halves' streams, so that both chains are under way from the start (the
 // first policy of all is launched by itself). It takes the host 1.5 us per tick where a tick's four
 // launches take 13.6; but a graph's nodes follow each other 0.4 to 0.9 us later than launches, and the
-// replay's own forks and joins take 35 us. So long rollouts of few servers, whose ticks of 17 to 37 us a
-// busy or slower host would hold up, are replayed (ms on the GPU and of the host, launched and replayed:
-// one server 40000 environments x 512 14.1 and 6.9, 14.7 and 0.8; 12-128-128-6 131072 x 512 17.4 and 6.7,
-// 17.7 and 0.8; attention policy 65536 x 256 9.5 and 3.9, 9.7 and 0.5), and those with longer ticks
-// launched (8 servers 65536 x 1024 53.6 and 15.8, 54.5 and 1.6; 4 servers 65536 x 256 10.4 and 3.9, 10.5
-// and 0.5). Runs of 64 ticks take the host 2.1 us per tick.
+// replay's own forks and joins take 35 us. So long rollouts of few servers and up to 40960
+// environments, whose ticks of 17 to 28 us a busy or slower host would hold up, are replayed (ms on
+// the GPU, among others and alone, and of the host, launched and replayed: one server 40000 x 512 14.1,
+// 14.2 and 6.9, 14.7, 14.9 and 0.8; attention policy 8192 x 256 4.8, 5.4 and 4.0, 5.0, 5.2 and 0.4; 40000 x
+// 256 6.8, 6.9 and 3.9, 7.1, 7.3 and 0.5), and those with longer ticks launched (8 servers 65536 x 1024
+// 53.6 and 15.8, 54.5 and 1.6; attention policy 65536 x 256 9.4, 9.3 and 3.8, 9.7, 10.1 and 0.5). Runs of 64
+// ticks take the host 2.1 us per tick.
 constexpr int64_t kRunTicks = 256;
-constexpr int32_t kReplayTicks = 128;
+constexpr int32_t kReplayTicks = 128, kReplayE = 40960;
 static bool halves_replayed(const sim_ctx* x, int32_t T) {
-  return x->cfg.n_servers < kHalvesLongK && T >= kReplayTicks;
+  return x->cfg.n_servers < kHalvesLongK && x->cfg.n_envs <= kReplayE && T >= kReplayTicks;
 }
 static EnvPart half(const sim_ctx* x, int h) {
   const int n0 = (x->cfg.n_envs / 2 + kPartAlign - 1) / kPartAlign * kPartAlign;
@@ -1000,9 +1016,12 @@ int sim_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr
     HIPCHK(hipMemcpyAsync(tr->obs, x->s.obs, 4 * F * E, hipMemcpyDeviceToDevice, x->stream),
            "hipMemcpyAsync obs_0");
   const RolloutKey key{d_weights, T, *tr, x->tick};
-  const bool captured = capturing(x->stream), halves = in_halves(x, captured);
+  const bool captured = capturing(x->stream), halves = in_halves(x, T, captured);
+  // batches of that size are launched also as one chain: it is short then, and a replay's forks, joins
+  // and start take 25 us (one server 65536 x 4: 159 us replayed, 135 launched)
+  const bool graph = halves ? halves_replayed(x, T) : !two_halves(x) || use_fused(x);
   int rc;
-  if (x->graphs && !x->timing && !captured && (!halves || halves_replayed(x, T))) {
+  if (x->graphs && !x->timing && !captured && graph) {
     // a call that repeats the previous one (same weights, length, outputs, starting tick) is
     // captured as a graph, or as one per run of ticks of each half; later repeats replay it
     bool have = x->rkey_valid && same_key(key, x->rkey) && halves == !x->rchain[0].empty();

@@ -22,6 +22,11 @@ CASES = [
 ]
 
 
+# the same in rollouts long enough for two chains (from 16 ticks, fewer with many
+# environments and servers)
+CASES += [(n, kw, E, 16 + i % 3) for i, (n, kw, E, _) in enumerate(CASES)] + [("C5", {}, 33000, 4), ("C5", {}, 65540, 2)]
+
+
 @pytest.mark.parametrize("name,kw,E,T", CASES)
 def test_rollout_in_halves_matches_one_chain(bs, name, kw, E, T):  # noqa: F811
     w = attn_preset(**kw) if name == "attn" else preset(name, **kw)
@@ -70,7 +75,7 @@ def test_rollout_in_a_callers_capture(bs):  # noqa: F811
 
 
 @pytest.mark.parametrize("name,kw,E,T", [("C1", dict(shadow=1), 8200, 300), ("C2", dict(value_head=1), 8449, 256),
-                                         ("attn", {}, 41100, 130)])
+                                         ("attn", {}, 8200, 130)])
 def test_replayed_halves_match_one_chain(bs, name, kw, E, T):  # noqa: F811
     """Long rollouts of few servers: launched, captured and replayed run by run, with a new seed that
     only device memory carries and other device work between the replays."""

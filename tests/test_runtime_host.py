@@ -1,7 +1,7 @@
 """The host runtime's launch sequences (csrc/runtime.cpp linked with the recording stand-ins of
 runtime_stub.cpp, no GPU): a rollout that fails in the middle of its two chains still joins
 every stream it forked back to the caller's; the second stream is made when a rollout needs it; a
-repeated rollout in halves is replayed from graphs."""
+repeated rollout in halves is replayed from graphs; short rollouts are one chain."""
 import ctypes as C
 import os
 import subprocess
@@ -85,7 +85,7 @@ def test_failed_rollout_joins_its_streams(stub, name, n):
         assert rc == -3
         assert_joined(log)
     # the same of a replay (three servers at most): its launches are the head's and the first policy
-    x = Ctx(stub, preset(name, n_servers=3), n)
+    x = Ctx(stub, preset(name, n_servers=3), 32768)
     x.rollout(128)
     rc, log = x.rollout(128)
     assert rc == 0 and [l for l in log if l[0] == "graph"]
@@ -105,8 +105,8 @@ def test_second_stream_only_for_rollouts_in_halves(stub):
 
 
 @pytest.mark.parametrize("w,n,T", [(preset("C2"), 40000, 600), (preset("C1"), 40000, 256),
-                                   (attn_preset(), 65536, 256),
-                                   (preset("C3", n_servers=2, obs_dim=18), 65536, 128)])
+                                   (attn_preset(), 40960, 256),
+                                   (preset("C3", n_servers=2, obs_dim=18), 36864, 128)])
 def test_repeated_rollout_in_halves_is_replayed(stub, w, n, T):
     x = Ctx(stub, w, n)
     rc, first = x.rollout(T)
@@ -119,10 +119,25 @@ def test_repeated_rollout_in_halves_is_replayed(stub, w, n, T):
         # the host's part no longer grows with every tick's launches
         assert len([l for l in log if l[0] == "launch"]) <= 4
         g = [l for l in log if l[0] == "graph"]
-        assert len(g) == 2 * -(-per_chain // 512)
+        assert len(g) == 2 * -(-per_chain // 512)   # 256 ticks each
         assert all(a[1] != b[1] for a, b in zip(g, g[1:])), "the chains' graphs take turns"
         first_policy = len(launches(log, "policy"))
         assert sum(int(l[2]) for l in g) + first_policy == 2 * per_chain and first_policy == 1
     # another length is launched again
     rc, log = x.rollout(T + 1)
     assert rc == 0 and not [l for l in log if l[0] == "graph"]
+
+
+@pytest.mark.parametrize("w,n,T,chains", [
+    (preset("C1"), 65536, 1, 1), (preset("C1"), 65536, 15, 1), (preset("C1"), 65536, 16, 2),
+    (attn_preset(), 65536, 8, 1), (attn_preset(), 262144, 4, 2), (preset("C4"), 32768, 15, 1), (preset("C4"), 32768, 16, 2),
+    (preset("C5"), 32768, 3, 1), (preset("C5"), 32768, 4, 2), (preset("C5"), 32767, 4, 1),
+    (preset("C5"), 65536, 2, 2)])
+def test_short_rollouts_are_one_chain(stub, w, n, T, chains):
+    x = Ctx(stub, w, n)
+    for i in range(3):
+        rc, log = x.rollout(T)
+        assert rc == 0 and not [l for l in log if l[0] == "graph"]
+        assert len(launches(log, "step")) == chains * T
+        forks = len([l for l in log if l[0] == "record"])
+        assert forks == (2 if chains == 2 else 0) + (2 if w["shadow"] else 0)
