@@ -281,7 +281,7 @@ int sim_set_graphs(sim_ctx* ctx, int32_t on);
  * 32-256-256-24 and 64-256-256-48 bf16 networks, any action count up to the padded width)
  * and all of the batch's workgroups of that kernel are resident on the GPU at once, or, with
  * one or two request classes, at most twice as many (one and a half times from four servers
- * on or beside a shadow system);
+ * on or beside a shadow system) for rollouts of four ticks or more;
  * SIM_FUSE_ON fuses whenever the shape has a fused kernel; SIM_FUSE_OFF always launches per
  * tick. SIM_EINVAL for another mode. A change discards the rollout graph.                  */
 enum { SIM_FUSE_OFF = 0, SIM_FUSE_AUTO = 1, SIM_FUSE_ON = 2 };

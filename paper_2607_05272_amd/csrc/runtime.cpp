@@ -714,10 +714,15 @@ int sim_policy_hidden(sim_ctx* x, const void* d_weights, const float* d_obs, uin
 // are resident at once, or with one or two request classes in two rounds of them (each round runs
 // every tick for its workgroups), the second at most half full from four servers on or beside a
 // shadow system, which then runs on the same CUs. Us per tick, fused and in launches of halves: one
-// server 16384 environments 14.0, 21.1; 12-128-128-6 17000 19.1, 18.7, 32768 18.8, 20.7; 32-256-256-24
-// 17000 24.5, 25.1, 24000 23.5, 25.7, 28000 26.8, 26.1; with a shadow 32768 38.3, 32.0; four classes
-// 17000 44.3, 38.5
-static bool use_fused(sim_ctx* x) {
+// server 16384 environments 14.0, 21.1; 12-128-128-6 17000 19.1, 18.7 (alone 19.2, 20.5: the launches
+// also take the host 13.6), 32768 18.8, 20.7; 32-256-256-24 17000 24.5, 25.1, 24000 23.5, 25.7, 28000
+// 26.8, 26.1; with a shadow 32768 38.3, 32.0; four classes 17000 44.3, 38.5. A second round loads and
+// stores its state again, 10 to 20 us of a rollout, so it is for kRoundsT ticks or more (us per
+// rollout that goes on from the last, fused and as one chain of launches: one server 16384 x 1 45.5,
+// 23.0, x 3 71.8, 64.1, x 4 85, 89; 12-128-128-6 32768 x 1 37.1, 26.4, x 3 76.0, 68.2; 32-256-256-24 24000
+// x 1 52.4, 43.0, x 3 102.8, 96.5).
+constexpr int32_t kRoundsT = 4;
+static bool use_fused(sim_ctx* x, int32_t T) {
   if (x->fuse == SIM_FUSE_OFF || x->cfg.policy_kind != SIM_POLICY_MLP) return false;
   if (x->fuse_plan.cap < 0) {
     FusedPlan plan{0, 0};
@@ -725,7 +730,7 @@ static bool use_fused(sim_ctx* x) {
   }
   if (x->fuse_plan.cap == 0) return false;
   const int64_t cap = x->fuse_plan.cap;
-  const int64_t max_e = x->cfg.n_classes > 2 ? cap
+  const int64_t max_e = x->cfg.n_classes > 2 || T < kRoundsT ? cap
                         : x->cfg.shadow || x->cfg.n_servers >= kHalvesLongK ? cap * 3 / 2
                                                                             : 2 * cap;
   return x->fuse == SIM_FUSE_ON || x->cfg.n_envs <= max_e;
@@ -744,7 +749,7 @@ static bool capturing(hipStream_t st) {
   return false;
 }
 static bool in_halves(sim_ctx* x, int32_t T, bool captured) {
-  return two_halves(x) && halves_pay(x, T) && !x->timing && !captured && !use_fused(x) &&
+  return two_halves(x) && halves_pay(x, T) && !x->timing && !captured && !use_fused(x, T) &&
          second_chain(x);
 }
 
@@ -853,7 +858,7 @@ static int enqueue_items(sim_ctx* x, int32_t T, const sim_traj* tr, uint32_t k0,
 // seed is read from device memory), so the sequence can be captured once as a graph and replayed.
 static int enqueue_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr,
                            uint32_t k0) {
-  const bool fused = use_fused(x);
+  const bool fused = use_fused(x, T);
   Forked shadow{x->stream};
   int rc = enqueue_head(x, d_weights, T, tr, k0, fused, shadow);
   if (rc) return rc;
@@ -1019,7 +1024,7 @@ int sim_rollout(sim_ctx* x, const void* d_weights, int32_t T, const sim_traj* tr
   const bool captured = capturing(x->stream), halves = in_halves(x, T, captured);
   // batches of that size are launched also as one chain: it is short then, and a replay's forks, joins
   // and start take 25 us (one server 65536 x 4: 159 us replayed, 135 launched)
-  const bool graph = halves ? halves_replayed(x, T) : !two_halves(x) || use_fused(x);
+  const bool graph = halves ? halves_replayed(x, T) : !two_halves(x) || use_fused(x, T);
   int rc;
   if (x->graphs && !x->timing && !captured && graph) {
     // a call that repeats the previous one (same weights, length, outputs, starting tick) is

@@ -1,7 +1,8 @@
 """The host runtime's launch sequences (csrc/runtime.cpp linked with the recording stand-ins of
 runtime_stub.cpp, no GPU): a rollout that fails in the middle of its two chains still joins
 every stream it forked back to the caller's; the second stream is made when a rollout needs it; a
-repeated rollout in halves is replayed from graphs; short rollouts are one chain."""
+repeated rollout in halves is replayed from graphs; short rollouts take neither a second chain nor
+a second round of fused workgroups."""
 import ctypes as C
 import os
 import subprocess
@@ -141,3 +142,14 @@ def test_short_rollouts_are_one_chain(stub, w, n, T, chains):
         assert len(launches(log, "step")) == chains * T
         forks = len([l for l in log if l[0] == "record"])
         assert forks == (2 if chains == 2 else 0) + (2 if w["shadow"] else 0)
+
+
+@pytest.mark.parametrize("w,n,fused_from", [(preset("C1"), 8192, 1), (preset("C1"), 8193, 4),
+                                            (preset("C1"), 16384, 4), (preset("C1"), 16385, None),
+                                            (preset("C3"), 12288, 4), (preset("C4"), 8193, None)])
+def test_a_second_round_is_for_more_than_a_few_ticks(stub, w, n, fused_from):
+    x = Ctx(stub, w, n, fused_cap=8192)
+    for T in (1, 3, 4, 200):
+        rc, log = x.rollout(T)
+        assert rc == 0
+        assert bool(launches(log, "fused")) == (fused_from is not None and T >= fused_from)
