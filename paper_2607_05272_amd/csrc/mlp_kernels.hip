@@ -114,13 +114,9 @@ hipError_t run_policy_bf16(const MlpParams& m, const float* obs, const uint32_t*
   static_assert(Sh::LDS <= 160 * 1024, "LDS budget");
   if (AC > 0 && m.A != AC) return hipErrorInvalidValue;
   auto kern = policy_bf16_k<FP, H1, H2, AP, RT, NW, MINB, TPW, DBG, AC>;
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)Sh::LDS);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static std::atomic<uint64_t> lds_on{0};
+  const hipError_t e = allow_lds((const void*)kern, Sh::LDS, lds_on);
+  if (e != hipSuccess) return e;
   if (part.e0 % Sh::ROWS != 0) return hipErrorInvalidValue;
   const dim3 grid((part.n + Sh::ROWS - 1) / Sh::ROWS), block(NW * 64);
   hipLaunchKernelGGL(kern, grid, block, Sh::LDS, st, m, part.e0 / Sh::ROWS, obs, obs_bf, seed, step, act, logp, value,
@@ -134,13 +130,9 @@ hipError_t run_policy(const MlpParams& m, const float* obs, const uint64_t* seed
                       EnvPart part, hipStream_t st) {
   typedef Shape<M, FP, H1, H2, AP, RT> Sh;
   auto kern = policy_k<M, FP, H1, H2, AP, RT, DBG>;
-  static bool attr = false;
-  if (!attr) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)Sh::LDS);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static std::atomic<uint64_t> lds_on{0};
+  const hipError_t e = allow_lds((const void*)kern, Sh::LDS, lds_on);
+  if (e != hipSuccess) return e;
   if (part.e0 % Sh::ROWS != 0) return hipErrorInvalidValue;
   const dim3 grid((part.n + Sh::ROWS - 1) / Sh::ROWS), block(kThreads);
   hipLaunchKernelGGL(kern, grid, block, Sh::LDS, st, m, part.e0 / Sh::ROWS, obs, seed, step, act, logp, value, logits,

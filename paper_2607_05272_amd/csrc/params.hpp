@@ -5,7 +5,25 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace bsim {
+
+constexpr size_t kLdsMax = 160 * 1024;   // of a CU
+// Raises a kernel's limit of dynamic LDS on the current device to `bytes`, the most any launch of it
+// asks for (past the 64 KiB that every kernel may have). The limit belongs to the kernel on that
+// device, whichever context launches it; `devices` are those where it is raised already.
+inline hipError_t allow_lds(const void* kern, size_t bytes, std::atomic<uint64_t>& devices) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+  if (devices.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) devices.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
 
 constexpr int kMaxK = 16, kMaxC = 4, kMaxS = 4;
 constexpr int kNcnt = 6;                 // arrivals, accepted, dropped, dispatched, batches, completed

@@ -789,13 +789,9 @@ hipError_t launch_mlp(const MlpArgs<Md>& a, int nwg, hipStream_t st) {
   typedef MlpLds<Md, FK, H1, H2, AK, RT> L;
   static_assert(L::LDS <= 160 * 1024, "LDS budget");
   auto kern = pg_mlp_k<Md, FK, H1, H2, AK, RT, NW>;
-  static bool attr = false;   // dynamic LDS beyond the default limit, once per kernel
-  if (L::LDS > 64 * 1024 && !attr) {
-    const hipError_t e = hipFuncSetAttribute(
-        (const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L::LDS);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  static std::atomic<uint64_t> lds_on{0};
+  const hipError_t e = allow_lds((const void*)kern, L::LDS, lds_on);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(nwg), dim3(NW * 64), L::LDS, st, a);
   return hipGetLastError();
 }

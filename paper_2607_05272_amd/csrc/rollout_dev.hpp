@@ -629,8 +629,6 @@ __global__ __launch_bounds__(Net::NW * 64) __attribute__((amdgpu_waves_per_eu(2)
 }
 
 // ---- host ------------------------------------------------------------------------------------
-constexpr size_t kLdsMax = 160 * 1024;
-
 template <class Net, int CM, bool RL>
 struct Fused {
   static constexpr auto kern = rollout_fused_k<Net, CM, RL>;
@@ -640,12 +638,15 @@ struct Fused {
   static constexpr size_t kStatic =
       sizeof(Stage<kStageLearned, Net::ROWS / Net::NW>) * Net::NW +
       sizeof(TileState<CM, Net::KM, Net::ROWS>) + Net::ROWS * 5 + 64;
+  // (the rings' size is the context's, the limit the kernel's: the most that fits)
+  static hipError_t allow() {
+    static std::atomic<uint64_t> lds_on{0};
+    return allow_lds((const void*)kern, kLdsMax - kStatic, lds_on);
+  }
   static bool fits(const SimParams& p) { return kStatic + dynamic_lds(p) <= kLdsMax; }
   // environments resident at once
   static hipError_t capacity(const SimParams& p, int cus, int* envs) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)dynamic_lds(p));
+    hipError_t e = allow();
     int per_cu = 0;
     if (e == hipSuccess)
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, Net::NW * 64, dynamic_lds(p));
@@ -662,6 +663,8 @@ struct Fused {
       rows = (p.E + slots - 1) / slots;
       rows = (rows + Net::NW - 1) / Net::NW * Net::NW;
     }
+    const hipError_t e = allow();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3((p.E + rows - 1) / rows), dim3(Net::NW * 64), dynamic_lds(p), st,
                        p, s, m, k0, T, rows, o);
     return hipGetLastError();

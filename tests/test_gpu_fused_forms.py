@@ -40,3 +40,21 @@ def test_fused_forms_match_per_tick(bs, name, kw, E, T):  # noqa: F811
                         for t in (T, 1, T)])
     for i, (a, b) in enumerate(zip(*out)):
         assert_same(a, b, f"{name} {kw} E={E}, call {i}")
+
+
+def test_contexts_with_other_queues_between(bs):  # noqa: F811
+    """Two contexts of one network whose rings take different shares of LDS, rolled out in turn."""
+    w = {"long": preset("C4", queue_cap=100), "short": preset("C4", queue_cap=5)}
+    out = []
+    for mode in (bs.FUSE_OFF, bs.FUSE_ON):
+        with bs.Sim(w["long"], n_envs=64) as a, bs.Sim(w["short"], n_envs=64) as b:
+            got = []
+            for sim, k in ((a, "long"), (b, "short"), (a, "long"), (b, "short")):
+                sim.set_fused_rollout(mode)
+                sim.set_graphs(False)
+                sim.reset(0xAB)
+                wb = sim.upload_weights(weights(w[k], 21))
+                got.append(snapshot(sim, sim.rollout(wb, 6, rchk=True)))
+            out.append(got)
+    for i, (x, y) in enumerate(zip(*out)):
+        assert_same(x, y, f"rollout {i}")
