@@ -319,8 +319,9 @@ int returns_gae(sim_ctx* ctx, int32_t T, const double* d_r, const float* d_v, do
  * fp32 x fp32 otherwise; the reductions over the samples are summed in a fixed order, so
  * repeated calls return identical results. Scratch of at most Mp (e (2 F + 4 H1 + 6 H2 + 4 A')
  * + 4 (H1 + H2 + A')) bytes (Mp = M rounded up to 64, e = 2 bytes for bf16 or 4 for fp32,
- * F and A' rounded up to 64) plus about 8 MiB of split-k partial sums is held by the context
- * after the first call (grown if a later call needs more). A stored action out of range latches SIM_ESTATE (reported by sim_sync);
+ * F and A' rounded up to 64; about half of that for the rollout policies' networks) plus about
+ * 8 MiB of split-k partial sums is held by the context after the first call (grown if a later
+ * call needs more). A stored action out of range latches SIM_ESTATE (reported by sim_sync);
  * that sample then contributes nothing.
  * For the attention policy (policy_kind = SIM_POLICY_ATTN) the forward is fp32 with exact
  * GELU and d_grads holds the fourteen arrays of sim_attn_layout in its order (w_in, b_in,
@@ -338,8 +339,8 @@ int ppo_minibatch_grad(sim_ctx* ctx, const void* d_weights, int32_t T, const flo
  * library holds in device memory (96 MiB per GPU, allocated when the library's code is loaded
  * on that GPU and kept until the process ends) instead of the context's on-demand buffer. It
  * calls no hipMalloc, hipFree or other allocating routine and records no tracing events.
- * SIM_EINVAL, with the sizes in the message, when the minibatch needs more scratch than that
- * (C4's shape at M = 8192 needs about 76 MiB). Every call on a GPU uses the same scratch: calls
+ * SIM_EINVAL, with the sizes in the message, when the bytes stated for ppo_minibatch_grad exceed
+ * that (C4's shape at M = 8192: about 76 MiB), whatever the kernels use of them. Every call on a GPU uses the same scratch: calls
  * whose work overlaps on one GPU (several streams or threads) race and must be serialised by
  * the caller; calls in order on one stream are safe. The scratch keeps the previous call's
  * contents; every byte a call reads is written by that call first.                        */

@@ -220,7 +220,8 @@ hipError_t launch_primitive(int kind, int64_t n, uint64_t key, const void* in, v
 hipError_t launch_init_attn(uint64_t seed, void* d_weights, const size_t off[14], const int fin[7],
                             const int fout[7], hipStream_t st);
 // MLP policy-gradient minibatch (ppo_kernels.hip), value head required: the library's own MFMA
-// products with fused epilogues; scratch holds ppo_scratch_bytes(m, M) bytes. adam != NULL (here
+// products with fused epilogues, in the four-launch form (ppo_fused.hip) for the networks it takes;
+// scratch holds ppo_scratch_bytes(m, M) bytes, what that form uses. adam != NULL (here
 // and for the attention policy) takes an Adam step with the gradient; grads is then scratch.
 hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t off[6], int T,
                       const float* obs, const uint8_t* act, const float* logp_old,
@@ -229,9 +230,10 @@ hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t of
                       float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
                       hipStream_t st);
 bool ppo_shape_supported(const MlpParams& m);
-// The same in four launches for the rollout policies' networks (ppo_fused.hip), in a scratch of
-// ppo_scratch_bytes: whether it takes this network and minibatch, and its launch.
-bool pg_fused_supported(const MlpParams& m, int M, size_t scratch_bytes);
+// The four-launch form for the rollout policies' networks, whatever the minibatch: whether it takes
+// this network, its scratch and its launch.
+bool pg_fused_supported(const MlpParams& m);
+size_t pg_fused_bytes(const MlpParams& m, int M);
 hipError_t launch_pg_fused(const MlpParams& m, const void* d_weights, const size_t off[6], int T,
                            const float* obs, const uint8_t* act, const float* logp_old,
                            const double* adv, const double* ret, int M, uint64_t seed, float clip,
@@ -239,6 +241,8 @@ hipError_t launch_pg_fused(const MlpParams& m, const void* d_weights, const size
                            float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
                            hipStream_t st);
 size_t ppo_scratch_bytes(const MlpParams& m, int M);
+// the scratch by which ppo_minibatch_grad_noalloc states its limit: the layer-by-layer form's
+size_t ppo_stated_bytes(const MlpParams& m, int M);
 // The fixed device scratch of ppo_minibatch_grad_noalloc: its size, and its address on the
 // current device (looked up once per device with hipGetSymbolAddress; allocates nothing).
 constexpr size_t kStaticScratchBytes = (size_t)96 << 20;

@@ -905,10 +905,11 @@ hipError_t run(const MlpParams& m, const void* d_weights, const size_t off[6], i
 
 }  // namespace
 
-bool pg_fused_supported(const MlpParams& m, int M, size_t scratch_bytes) {
-  return with_net(m, [](auto) { return hipSuccess; }) == hipSuccess &&
-         plan_of(m, M).bytes <= scratch_bytes;
+bool pg_fused_supported(const MlpParams& m) {
+  return with_net(m, [](auto) { return hipSuccess; }) == hipSuccess;
 }
+
+size_t pg_fused_bytes(const MlpParams& m, int M) { return plan_of(m, M).bytes; }
 
 hipError_t launch_pg_fused(const MlpParams& m, const void* d_weights, const size_t off[6], int T,
                            const float* obs, const uint8_t* act, const float* logp_old,

@@ -770,7 +770,11 @@ hipError_t run_minibatch(const MlpParams& m, const void* d_weights, const size_t
 
 }  // namespace
 
-size_t ppo_scratch_bytes(const MlpParams& m, int M) { return carve(m, M, nullptr, nullptr); }
+size_t ppo_scratch_bytes(const MlpParams& m, int M) {
+  return pg_fused_supported(m) ? pg_fused_bytes(m, M) : carve(m, M, nullptr, nullptr);
+}
+
+size_t ppo_stated_bytes(const MlpParams& m, int M) { return carve(m, M, nullptr, nullptr); }
 
 hipError_t static_scratch(void** ptr) {
   constexpr int kDevices = 64;
@@ -803,7 +807,7 @@ hipError_t launch_ppo(const MlpParams& m, const void* d_weights, const size_t of
                       float* grads, const AdamStep* adam, int64_t* idx_out, uint32_t* err,
                       hipStream_t st) {
   if (M < 1 || !ppo_shape_supported(m)) return hipErrorInvalidValue;
-  if (pg_fused_supported(m, M, ppo_scratch_bytes(m, M)))
+  if (pg_fused_supported(m))
     return launch_pg_fused(m, d_weights, off, T, obs, act, logp_old, adv, ret, M, seed, clip, c_v,
                            c_h, reinforce, scratch, loss_out, grads, adam, idx_out, err, st);
   const hipError_t e =

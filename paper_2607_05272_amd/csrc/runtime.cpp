@@ -1096,12 +1096,15 @@ int sim_ppo_grad_count(const sim_cfg* c, int64_t* h_count) {
 }
 
 // The minibatch's scratch: the context's buffer, grown with hipMalloc when a call needs more,
-// or (no_alloc) the library's fixed device scratch, which allocates nothing.
-static int mb_scratch(sim_ctx* x, size_t need, bool no_alloc, const char* who, void** out) {
+// or (no_alloc) the library's fixed device scratch, which allocates nothing; that entry's limit is
+// stated by a formula of the sizes, `stated`, not by what the kernels use of it.
+static int mb_scratch(sim_ctx* x, size_t need, size_t stated, bool no_alloc, const char* who,
+                      void** out) {
   if (no_alloc) {
-    if (need > kStaticScratchBytes)
+    const size_t n = std::max(need, stated);
+    if (n > kStaticScratchBytes)
       return fail(SIM_EINVAL, "%s: this minibatch needs %zu bytes of scratch; the fixed scratch "
-                  "holds %zu (use fewer samples, or ppo_minibatch_grad)", who, need,
+                  "holds %zu (use fewer samples, or ppo_minibatch_grad)", who, n,
                   kStaticScratchBytes);
     HIPCHK(static_scratch(out), "hipGetSymbolAddress of the fixed scratch");
     return SIM_OK;
@@ -1144,7 +1147,7 @@ static int pg_grad(sim_ctx* x, int reinforce, const void* d_weights, int32_t T, 
     int rc = prepare_policy(x, d_weights);  // shape check and weight pointers
     if (rc) return rc;
     void* scr = nullptr;
-    rc = mb_scratch(x, attn_grad_scratch_bytes(x->a, M), no_alloc, who, &scr);
+    rc = mb_scratch(x, attn_grad_scratch_bytes(x->a, M), 0, no_alloc, who, &scr);
     if (rc) return rc;
     auto launch = [&] {
       return launch_attn_grad(x->a, T, d_obs, d_actions, d_logp_old, d_adv, d_ret, M, seed, clip,
@@ -1162,7 +1165,7 @@ static int pg_grad(sim_ctx* x, int reinforce, const void* d_weights, int32_t T, 
     return fail(SIM_EUNSUPPORTED, "%s: hidden widths must be multiples of 64, obs_dim <= 128 and A' <= 128",
                 who);
   void* scr = nullptr;
-  int rc = mb_scratch(x, ppo_scratch_bytes(x->m, M), no_alloc, who, &scr);
+  int rc = mb_scratch(x, ppo_scratch_bytes(x->m, M), ppo_stated_bytes(x->m, M), no_alloc, who, &scr);
   if (rc) return rc;
   size_t off[6];
   offsets(x->cfg, off);

@@ -150,6 +150,7 @@ hipError_t launch_attn_grad(const AttnParams&, int, const float*, const uint8_t*
                             const double*, int, uint64_t, float, float, float, int, void*, double*, float*,
                             const AdamStep*, int64_t*, uint32_t*, hipStream_t st) { return kernel("grad", st); }
 size_t ppo_scratch_bytes(const MlpParams&, int) { return 1; }
+size_t ppo_stated_bytes(const MlpParams&, int) { return 1; }
 hipError_t launch_ppo(const MlpParams&, const void*, const size_t*, int, const float*, const uint8_t*,
                       const float*, const double*, const double*, int, uint64_t, float, float, float, int,
                       void*, double*, float*, const AdamStep*, int64_t*, uint32_t*, hipStream_t st) {

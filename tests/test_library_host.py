@@ -42,3 +42,35 @@ def test_lds_limits_on_another_device(stub, call):
     assert all(rc == 0 for rc, _ in out)
     first, second = [assert_lds_allowed(out[i][1]) for i in (2, 5)]
     assert first == second > 0
+
+
+def grad(c, M, name="ppo_minibatch_grad"):
+    return dict(call=name, ctx=c, args=[P, 4, P, P, P, P, P, M, 1, 0.2, 0.5, 0.01, P, P, None])
+
+
+@pytest.mark.parametrize("name", ["C1", "C2", "C3", "C4", "C5"])
+def test_rollout_networks_gradients_take_four_launches(stub, name):
+    """From the smallest minibatch on, in the scratch that this form uses."""
+    w = preset(name, value_head=1)
+    F, H1, H2, A = (-(-x // 64) * 64 for x in (w["obs_dim"], w["mlp_h1"], w["mlp_h2"],
+                                               6 * w["n_servers"] + 1))
+    e, two = (2, 2) if w["mlp_bf16"] else (4, 1)
+    for M in (16, 32, 48, 64, 80, 4096, 8192, 16384):
+        out = hip_stub.run(stub, [dict(new="a", w=w, n_envs=4096), grad("a", M)])
+        assert all(rc == 0 for rc, _ in out)
+        log = out[1][1]
+        names = [l[1] for l in log if l[0] == "launch"]
+        assert len(names) == 4 and "pg_mlp_k" in names[1], f"M = {M}: {names}"
+        # x twice, both activations, the gradients' terms and 32 bytes per sample; partial sums
+        Mp = -(-M // 64) * 64
+        per = e * (2 * F + H1 + H2 + two * (A + H2 + H1)) + 32 + 4 * (A + H2 + H1) // 16
+        (size,) = [int(l[1]) for l in log if l[0] == "malloc"]
+        assert size <= Mp * per + (8 << 20)
+
+
+def test_noalloc_limit_stays(stub):
+    """The no-allocation entry point's limit is the one that batchsim.h states."""
+    w = preset("C4")
+    for M, rc in ((8192, 0), (16384, -1)):
+        out = hip_stub.run(stub, [dict(new="a", w=w, n_envs=512), grad("a", M, "ppo_minibatch_grad_noalloc")])
+        assert out[1][0] == rc and not [l for l in out[1][1] if l[0] == "malloc"]
