@@ -326,8 +326,9 @@ int returns_gae(sim_ctx* ctx, int32_t T, const double* d_r, const float* d_v, do
  * For the attention policy (policy_kind = SIM_POLICY_ATTN) the forward is fp32 with exact
  * GELU and d_grads holds the fourteen arrays of sim_attn_layout in its order (w_in, b_in,
  * w_qkv, b_qkv, w_o, b_o, wp1, bp1, wp2, bp2, wv1, bv1, wv2, bv2), each [in][out] as in the
- * weights; per-sample gradient terms are summed over the minibatch in a fixed order (the
- * scratch then holds 4 M P + 24 M bytes, P = sim_ppo_grad_count).                        */
+ * weights; the gradient terms of 32 samples at a time are summed over the minibatch in a fixed
+ * order, in a scratch of 4 P + 24 bytes per 32 samples (P = sim_ppo_grad_count; the limit of
+ * ppo_minibatch_grad_noalloc is stated by 4 M P + 24 M bytes).                            */
 int ppo_minibatch_grad(sim_ctx* ctx, const void* d_weights, int32_t T, const float* d_obs,
                        const uint8_t* d_actions, const float* d_logp_old, const double* d_adv,
                        const double* d_ret, int32_t M, uint64_t seed, float clip, float c_value,
@@ -339,8 +340,9 @@ int ppo_minibatch_grad(sim_ctx* ctx, const void* d_weights, int32_t T, const flo
  * library holds in device memory (96 MiB per GPU, allocated when the library's code is loaded
  * on that GPU and kept until the process ends) instead of the context's on-demand buffer. It
  * calls no hipMalloc, hipFree or other allocating routine and records no tracing events.
- * SIM_EINVAL, with the sizes in the message, when the bytes stated for ppo_minibatch_grad exceed
- * that (C4's shape at M = 8192: about 76 MiB), whatever the kernels use of them. Every call on a GPU uses the same scratch: calls
+ * SIM_EINVAL, with the sizes in the message, when the bytes stated for ppo_minibatch_grad (the
+ * formula in full, also for networks that need half of it) exceed that (C4's shape at M = 8192:
+ * about 76 MiB), whatever the kernels use of them. Every call on a GPU uses the same scratch: calls
  * whose work overlaps on one GPU (several streams or threads) race and must be serialised by
  * the caller; calls in order on one stream are safe. The scratch keeps the previous call's
  * contents; every byte a call reads is written by that call first.                        */

@@ -955,7 +955,8 @@ __global__ __launch_bounds__(kFinThr) void attn_finish_k(AttnFinArgs a) {
 
 template <int L, int NH, int A>
 hipError_t run_grad(const AttnGradArgs& g, hipStream_t st) {
-  hipLaunchKernelGGL((attn_grad_k<L, NH, A>), dim3((unsigned)((g.M + kSamples - 1) / kSamples)), dim3(kGradThr), 0, st, g);
+  hipLaunchKernelGGL((attn_grad_k<L, NH, A>), dim3((unsigned)((g.M + kSamples - 1) / kSamples)),
+                     dim3(kGradThr), 0, st, g);
   return hipGetLastError();
 }
 template <int L, int NH>
@@ -990,7 +991,13 @@ int attn_param_count(const AttnParams& p, int off[14]) {
   return acc;
 }
 
+// a row of partial sums and the loss terms per workgroup
+static int grad_workgroups(int M) { return (M + kSamples - 1) / kSamples; }
 size_t attn_grad_scratch_bytes(const AttnParams& p, int M) {
+  return (size_t)grad_workgroups(M) *
+         ((size_t)attn_param_count(p, nullptr) * sizeof(float) + 3 * sizeof(double));
+}
+size_t attn_stated_bytes(const AttnParams& p, int M) {
   return (size_t)attn_param_count(p, nullptr) * M * sizeof(float) + (size_t)M * 3 * sizeof(double);
 }
 
@@ -1006,7 +1013,7 @@ hipError_t launch_attn_grad(const AttnParams& p, int T, const float* obs, const 
   g.seed = seed; g.clip = clip; g.c_v = c_v; g.c_h = c_h;
   g.P = attn_param_count(p, g.off);
   // the loss terms (8-byte aligned at the start), then the partial sums
-  const int nwg = (M + kSamples - 1) / kSamples;
+  const int nwg = grad_workgroups(M);
   g.terms = static_cast<double*>(scratch);
   g.part = reinterpret_cast<float*>(g.terms + (size_t)nwg * 3);
   g.idx_out = idx_out; g.err = err;

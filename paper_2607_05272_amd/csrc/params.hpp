@@ -201,6 +201,8 @@ hipError_t launch_attn_policy(const AttnParams& p, const float* obs, const uint6
 // attn_grad_scratch_bytes bytes
 int attn_param_count(const AttnParams& p, int off[14]);
 size_t attn_grad_scratch_bytes(const AttnParams& p, int M);
+// the scratch by which ppo_minibatch_grad_noalloc states its limit: every sample's terms
+size_t attn_stated_bytes(const AttnParams& p, int M);
 hipError_t launch_attn_grad(const AttnParams& p, int T, const float* obs, const uint8_t* act,
                             const float* logp_old, const double* adv, const double* ret, int M,
                             uint64_t seed, float clip, float c_v, float c_h, int reinforce,

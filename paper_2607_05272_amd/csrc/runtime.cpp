@@ -1147,7 +1147,8 @@ static int pg_grad(sim_ctx* x, int reinforce, const void* d_weights, int32_t T, 
     int rc = prepare_policy(x, d_weights);  // shape check and weight pointers
     if (rc) return rc;
     void* scr = nullptr;
-    rc = mb_scratch(x, attn_grad_scratch_bytes(x->a, M), 0, no_alloc, who, &scr);
+    rc = mb_scratch(x, attn_grad_scratch_bytes(x->a, M), attn_stated_bytes(x->a, M), no_alloc, who,
+                    &scr);
     if (rc) return rc;
     auto launch = [&] {
       return launch_attn_grad(x->a, T, d_obs, d_actions, d_logp_old, d_adv, d_ret, M, seed, clip,

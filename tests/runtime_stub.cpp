@@ -146,6 +146,7 @@ hipError_t launch_gae(int, int, const double*, const float*, double, double, dou
 }
 int attn_param_count(const AttnParams&, int*) { return 1; }
 size_t attn_grad_scratch_bytes(const AttnParams&, int) { return 1; }
+size_t attn_stated_bytes(const AttnParams&, int) { return 1; }
 hipError_t launch_attn_grad(const AttnParams&, int, const float*, const uint8_t*, const float*, const double*,
                             const double*, int, uint64_t, float, float, float, int, void*, double*, float*,
                             const AdamStep*, int64_t*, uint32_t*, hipStream_t st) { return kernel("grad", st); }

@@ -4,7 +4,7 @@ for in between."""
 import pytest
 
 import hip_stub
-from workloads import preset
+from workloads import attn_preset, preset
 
 P = 1 << 40   # a device pointer (nothing reads it)
 
@@ -74,3 +74,18 @@ def test_noalloc_limit_stays(stub):
     for M, rc in ((8192, 0), (16384, -1)):
         out = hip_stub.run(stub, [dict(new="a", w=w, n_envs=512), grad("a", M, "ppo_minibatch_grad_noalloc")])
         assert out[1][0] == rc and not [l for l in out[1][1] if l[0] == "malloc"]
+
+
+def test_attention_gradient_scratch(stub):
+    """A row of partial sums and three loss terms per 32 samples; the no-allocation entry's limit of
+    4 M P + 24 M bytes stays."""
+    w = attn_preset()
+    n = 8 * 4 + 4 + 4 * 12 + 12 + 4 * 4 + 4 + 4 * 64 + 64 + 64 * 6 + 6 + 4 * 64 + 64 + 64 + 1
+    for M in (16, 48, 8192):
+        out = hip_stub.run(stub, [dict(new="a", w=w, n_envs=512), grad("a", M)])
+        assert out[1][0] == 0
+        assert [int(l[1]) for l in out[1][1] if l[0] == "malloc"] == [-(-M // 32) * (4 * n + 24)]
+    M = ((96 << 20) // (4 * n + 24)) // 16 * 16
+    for m, rc in ((M, 0), (M + 16, -1)):
+        out = hip_stub.run(stub, [dict(new="a", w=w, n_envs=512), grad("a", m, "ppo_minibatch_grad_noalloc")])
+        assert out[1][0] == rc
