@@ -11,18 +11,17 @@
 namespace bsim {
 namespace {
 
-// Large batches: one lane per environment, every row access coalesced. Bound by HBM once enough
-// loads are in flight: a lane that loads one row, sums it and stores it waits out a memory
-// round trip per step (65536 x 1024: 1080 us, 1.7 TB/s), so the rows of the next kAhead steps
-// are loaded while the current ones are summed and stored (345 us, 5.45 TB/s; a plain copy
-// reaches 5.2).
-constexpr int kAhead = 8;
-template <bool HASV>
-__global__ __launch_bounds__(64) void gae_stream_k(int T, int E, const double* __restrict__ r,
-                                                   const float* __restrict__ v, double gamma,
-                                                   double gl, double* __restrict__ adv,
-                                                   double* __restrict__ ret) {
-  const int e = blockIdx.x * 64 + threadIdx.x;
+// One lane per environment, every row access coalesced. Bound by HBM once enough loads are in flight:
+// a lane that loads one row, sums it and stores it waits out a memory round trip per step (65536 x
+// 1024: 1080 us, 1.7 TB/s), so the rows of the next AHEAD steps are loaded while the current ones are
+// summed and stored (8 rows 345 us, 5.45 TB/s; a plain copy reaches 5.2). The more waves there are, the
+// fewer rows each needs, and more only scatter the accesses: see launch_gae.
+template <bool HASV, int AHEAD, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void gae_stream_k(int T, int E, const double* __restrict__ r,
+                                                      const float* __restrict__ v, double gamma,
+                                                      double gl, double* __restrict__ adv,
+                                                      double* __restrict__ ret) {
+  const int e = blockIdx.x * BLOCK + threadIdx.x;
   if (e >= E) return;
   const size_t sE = (size_t)E;
   double a = 0.0, vn = HASV ? (double)v[(size_t)T * sE + e] : 0.0;
@@ -34,31 +33,50 @@ __global__ __launch_bounds__(64) void gae_stream_k(int T, int E, const double* _
     vn = vt;
   };
   int t = T;
-  for (; t % kAhead; --t) {
+  for (; t % AHEAD; --t) {
     const size_t i = (size_t)(t - 1) * sE + e;
     step(i, r[i], HASV ? (double)v[i] : 0.0);
   }
   if (t == 0) return;
-  double rb[kAhead];
-  float vb[kAhead];
+  double rb[AHEAD];
+  float vb[AHEAD];
   auto load = [&](int hi) {
 #pragma unroll
-    for (int j = 0; j < kAhead; ++j) {
+    for (int j = 0; j < AHEAD; ++j) {
       const size_t i = (size_t)(hi - 1 - j) * sE + e;
       rb[j] = r[i];
       vb[j] = HASV ? v[i] : 0.f;
     }
   };
   load(t);
-  for (; t > 0; t -= kAhead) {
-    double rc[kAhead];
-    float vc[kAhead];
+  for (; t > 0; t -= AHEAD) {
+    double rc[AHEAD];
+    float vc[AHEAD];
 #pragma unroll
-    for (int j = 0; j < kAhead; ++j) { rc[j] = rb[j]; vc[j] = vb[j]; }
-    if (t > kAhead) load(t - kAhead);
+    for (int j = 0; j < AHEAD; ++j) { rc[j] = rb[j]; vc[j] = vb[j]; }
+    if (t > AHEAD) load(t - AHEAD);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < kAhead; ++j) step((size_t)(t - 1 - j) * sE + e, rc[j], (double)vc[j]);
+    for (int j = 0; j < AHEAD; ++j) step((size_t)(t - 1 - j) * sE + e, rc[j], (double)vc[j]);
+  }
+}
+
+// The largest batches, whose waves alone keep HBM busy: a row at a time, V's load before r's.
+__global__ __launch_bounds__(256) void gae_row_k(int T, int E, const double* __restrict__ r,
+                                                 const float* __restrict__ v, double gamma, double gl,
+                                                 double* __restrict__ adv, double* __restrict__ ret) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= E) return;
+  const size_t sE = (size_t)E;
+  double a = 0.0, vn = v ? (double)v[(size_t)T * sE + e] : 0.0;
+  for (int t = T - 1; t >= 0; --t) {
+    const size_t i = (size_t)t * sE + e;
+    const double vt = v ? (double)v[i] : 0.0;
+    const double delta = (r[i] + gamma * vn) - vt;
+    a = delta + gl * a;
+    adv[i] = a;
+    ret[i] = a + vt;
+    vn = vt;
   }
 }
 
@@ -66,9 +84,9 @@ __global__ __launch_bounds__(64) void gae_stream_k(int T, int E, const double* _
 // environments per workgroup, kSteps steps per chunk. One wave runs the recurrence (a
 // lane per environment) over the deltas of chunk c in LDS while the mover threads write out
 // chunk c - 1, put the deltas of chunk c + 1 in its place and issue the loads of chunk c + 2.
-// Bound by the recurrence's own chain (T = 1000: about 16 cycles a step) once the movers keep
-// up: 256 x 1000 without V 17.7 us, against 34 us in the streaming form and 265 us with a memory
-// round trip per step.
+// Bound by the recurrence's wave and what feeds it: 256 x 1000 without V 17.1 us, 13.3 of them after
+// the launch, about 31 cycles a step, of which the dependent multiplication and addition are 16 (34 us
+// in the streaming form, 265 with a memory round trip per step).
 constexpr int kEnvs = 16, kItems = 8, kMovers = 256, kSteps = kItems * kMovers / kEnvs;
 constexpr int kUnroll = 8;
 static_assert(kSteps % kUnroll == 0, "whole groups of steps");
@@ -175,22 +193,39 @@ __global__ __launch_bounds__(64 + kMovers) void gae_tile_k(int T, int E,
 // Up to which batch the tiled form is used: it has a sixteenth of the other's environments per
 // wave, so it fills more of the chip, but its rows are read in 16-environment segments. Where
 // those start on cache lines (E a multiple of 16; us with V, tiled against streaming, T = 512):
-// 4096 environments 17.7 / 31.3, 12288 30.7 / 34.2, 15360 38.0 / 37.0, 65536 213 / 171. Where
-// they straddle lines: 5001 23.4 / 34.0, 9999 39.7 / 35.8, 14001 55.0 / 39.2.
+// 4096 environments 16.9 / 31.2, 12288 30.1 / 34.1, 14336 35.9 / 36.1, 65536 213 / 171. Where
+// they straddle lines: 5001 23.4 / 34.0, 9999 39.7 / 35.8, 14001 55.0 / 39.2. Trajectories shorter than
+// its chunks of 128 steps leave it nothing to overlap (14336 x 16 6.6 / 5.3, 14336 x 64 8.6 / 6.2, 16 x
+// 64 5.2 / 5.2, 16 x 96 5.2 / 6.3, 4096 x 96 6.0 / 6.8, 8192 x 96 7.3 / 7.4, 8192 x 128 8.5 / 8.9, 12288 x 256 18.2 /
+// 18.6).
 constexpr int kTileE = 14336, kTileEOdd = 8192;
+static bool tiled(int T, int E) {
+  return E <= (E % kEnvs ? kTileEOdd : kTileE) && T >= 64 + E / 128;
+}
+// From which batches on the streaming form loads one row ahead in place of 8, earlier where the waves'
+// rows straddle cache lines, and none (us with and without V, 8, 1 and none: 163840 x 300 271 and 241,
+// 276 and 267, 456 and 277; 170001 x 300 387 and 341, 306 and 293, 485 and 303; 184320 x 300 318 and 274,
+// 293 and 273, 466 and 282; 262144 x 300 427 and 372, 377 and 343, 492 and 339; 393216 x 100 one and none
+// 214 and 170, 203 and 169; 524288 x 100 293 and 257, 255 and 254).
+constexpr int kAhead1E = 184320, kAhead1EOdd = 163840, kRowE = 393216;
+
+template <bool HASV>
+static void launch(int T, int E, const double* r, const float* v, double gamma, double gl,
+                   double* adv, double* ret, hipStream_t st) {
+  auto go = [&](auto kern, int envs, int block) {
+    hipLaunchKernelGGL(kern, dim3((E + envs - 1) / envs), dim3(block), 0, st, T, E, r, v, gamma, gl,
+                       adv, ret);
+  };
+  if (tiled(T, E)) go(gae_tile_k<HASV>, kEnvs, 64 + kMovers);
+  else if (E < (E % kEnvs ? kAhead1EOdd : kAhead1E)) go(gae_stream_k<HASV, 8, 64>, 64, 64);
+  else if (E < kRowE) go(gae_stream_k<HASV, 1, 256>, 256, 256);
+  else go(gae_row_k, 256, 256);
+}
 
 hipError_t launch_gae(int T, int E, const double* r, const float* v, double gamma, double lam,
                       double* adv, double* ret, hipStream_t st) {
-  const double gl = gamma * lam;
-  if (E <= (E % kEnvs ? kTileEOdd : kTileE)) {
-    const dim3 grid((E + kEnvs - 1) / kEnvs), block(64 + kMovers);
-    if (v) hipLaunchKernelGGL(gae_tile_k<true>, grid, block, 0, st, T, E, r, v, gamma, gl, adv, ret);
-    else hipLaunchKernelGGL(gae_tile_k<false>, grid, block, 0, st, T, E, r, v, gamma, gl, adv, ret);
-  } else {
-    const dim3 grid((E + 63) / 64), block(64);
-    if (v) hipLaunchKernelGGL(gae_stream_k<true>, grid, block, 0, st, T, E, r, v, gamma, gl, adv, ret);
-    else hipLaunchKernelGGL(gae_stream_k<false>, grid, block, 0, st, T, E, r, v, gamma, gl, adv, ret);
-  }
+  if (v) launch<true>(T, E, r, v, gamma, gamma * lam, adv, ret, st);
+  else launch<false>(T, E, r, v, gamma, gamma * lam, adv, ret, st);
   return hipGetLastError();
 }
 

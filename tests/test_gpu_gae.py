@@ -1,7 +1,8 @@
-"""Returns / GAE (Sec. 4.3) at the edges of its kernels' tiles: the batch sizes around the
-switch between the tiled and the streaming form, 16-environment tiles with a remainder, step
-counts around a chunk (128 steps) and around the streaming form's groups of 8. Both forms take
-the recurrence's fp64 operations in the oracle's order, so the results are the same bits."""
+"""Returns / GAE (Sec. 4.3) at the edges of its kernels' tiles: the batch sizes and trajectory
+lengths around the switch between the tiled and the streaming form, 16-environment tiles with a
+remainder, step counts around a chunk (128 steps) and around the streaming form's groups of 8, the
+batches that load one row ahead or none. All forms take the recurrence's fp64 operations in the
+oracle's order, so the results are the same bits."""
 import numpy as np
 import pytest
 
@@ -16,6 +17,18 @@ pytestmark = pytest.mark.gpu
                                  (8193, 9), (14336, 3), (14352, 16), (20001, 8)])
 @pytest.mark.parametrize("value", [True, False])
 def test_gae_tiles(E, T, value):
+    check(E, T, value)
+
+
+@pytest.mark.parametrize("E,T", [(1, 63), (1, 64), (17, 72), (8192, 127), (8192, 128), (8193, 128),
+                                 (14336, 175), (14336, 176), (14352, 176), (163839, 9), (163841, 9),
+                                 (184304, 17), (184320, 17), (393215, 2), (393216, 3)])
+@pytest.mark.parametrize("value", [True, False])
+def test_gae_forms(E, T, value):
+    check(E, T, value)
+
+
+def check(E, T, value):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     import oracle
