@@ -323,8 +323,9 @@ int returns_gae(sim_ctx* ctx, int32_t T, const double* d_r, const float* d_v, do
  * 8 MiB of split-k partial sums is held by the context after the first call (grown if a later
  * call needs more). A stored action out of range latches SIM_ESTATE (reported by sim_sync);
  * that sample then contributes nothing.
- * For the attention policy (policy_kind = SIM_POLICY_ATTN) the forward is fp32 with exact
- * GELU and d_grads holds the fourteen arrays of sim_attn_layout in its order (w_in, b_in,
+ * For the attention policy (policy_kind = SIM_POLICY_ATTN) the forward is fp32 (GELU no further
+ * from its exact value than with erff; sums in another order than sim_policy's, so that the
+ * log-probabilities of the two differ by their rounding) and d_grads holds the fourteen arrays of sim_attn_layout in its order (w_in, b_in,
  * w_qkv, b_qkv, w_o, b_o, wp1, bp1, wp2, bp2, wv1, bv1, wv2, bv2), each [in][out] as in the
  * weights; the gradient terms of 32 samples at a time are summed over the minibatch in a fixed
  * order, in a scratch of 4 P + 24 bytes per 32 samples (P = sim_ppo_grad_count; the limit of

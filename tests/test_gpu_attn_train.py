@@ -10,6 +10,7 @@ times the sum over samples of the magnitudes of the entry's gradient terms (u = 
 the oracle's absolute-value backward gives; the test allows 2^-12 of that sum (16x margin). The
 PPO clip decision is kept away from its boundaries: logp_old = logp_new - d with
 |d - ln(1 +- clip)| >= 0.01. Loss terms: fp32 per sample, fp64 sums: 2^-12 relative."""
+import math
 import sys
 
 import numpy as np
@@ -174,3 +175,39 @@ def test_attention_update_loop_parity(bs, orc, algo):
     scale = np.abs(ref_losses[:, 1:]).sum(axis=1)
     assert np.all(np.abs(gl - ref_losses) <= 2.0 ** -8 * scale[:, None])
     sim.close()
+
+
+@pytest.mark.parametrize("name,over", [("paper", {}), ("L4_H4", VARIANTS["L4_H4"]),
+                                       ("wide_heads", dict(mlp_h1=256, mlp_h2=256))])
+def test_attention_logp_of_gradient_and_policy(bs, orc, name, over):
+    """The gradient's log-probabilities against those stored by the policy: one sample (T = E = 1,
+    advantage 1, no value and entropy terms) at its stored log-probability, so that the policy
+    term is -rho = -exp(the difference). Each logit is Hp rounded products and sums of hidden units
+    that are themselves D of pooled values behind a chain of some 32 operations: off by at most
+    (Hp + 32) u times its magnitudes' sum S in either kernel (u = 2^-24), and a log-probability
+    by twice that: a difference of 4 (Hp + 32) u S. Independent errors of that size would differ
+    by sqrt of the count, so the root mean square is held to 8 sqrt(Hp + 32) u S."""
+    w = attn_preset(**over)
+    sim = bs.Sim(w, n_envs=1)
+    sim.reset(3)
+    one = torch.ones(1, 1, dtype=torch.float64, device="cuda")
+    n, u, share, worst = w["mlp_h1"] + 32, 2.0 ** -24, [], 0.0
+    for i in range(64):
+        W = rand_weights(orc, w, 100 + i)
+        x = seeded_obs(200 + i, 1, w["obs_dim"]).astype(np.float32)
+        wb = sim.upload_weights(W)
+        obs = torch.from_numpy(np.ascontiguousarray(x.reshape(1, -1, 1))).cuda()
+        o = sim.policy(wb, obs[0], i)
+        _, loss, _ = sim.ppo_minibatch_grad(wb, obs, o["actions"].view(1, 1), o["logp"].view(1, 1),
+                                            one, one, 16, 5, CLIP, 0.0, 0.0)
+        p = np.abs(orc_attn.forward(w, W, x.astype(np.float64))["p"][0])
+        T = p @ np.abs(W["wp1"]) + np.abs(W["bp1"])
+        S = (T @ np.abs(W["wp2"]) + np.abs(W["bp2"])).max()
+        d = np.log(-loss.cpu().numpy()[1])
+        worst = max(worst, abs(d) / (4 * n * u * S))
+        share.append(d / (8 * math.sqrt(n) * u * S))
+    sim.sync()
+    sim.close()
+    rms = float(np.sqrt(np.mean(np.square(share))))
+    say(f"  {name}: max {worst:.3g}, rms {rms:.3g} of their bounds")
+    assert worst <= 1.0 and rms <= 1.0
