@@ -5,6 +5,8 @@ second half, for every policy kernel, with the value row, stored observations an
 shadow system beside them, several times with other work on the caller's stream in between (short
 such rollouts are not captured as graphs; long ones of few servers are, run by run); and inside a
 caller's own capture."""
+import concurrent.futures
+
 import pytest
 
 from test_gpu_fused import assert_same, bs, snapshot, weights  # noqa: F401
@@ -99,3 +101,31 @@ def test_replayed_halves_match_one_chain(bs, name, kw, E, T):  # noqa: F811
                     assert_same({k: ref[seed][k] for k in out}, out, f"{name} E={E}, call {i}")
                 for t in (tr.actions, tr.reward, tr.rchk):
                     t.zero_()
+
+
+@pytest.mark.parametrize("T", [17, 130])   # launched, and replayed from graphs from the third call on
+def test_two_contexts_halves_from_two_threads(bs, T):  # noqa: F811
+    """Two contexts, each with its own thread, stream and network, whose rollouts in halves run at the
+    same time: every call's outputs are those of the context alone."""
+    cases = [(preset("C1"), 8192, 0x1A), (preset("C2", value_head=1), 8449, 0x2B)]
+
+    def calls(i, n):
+        w, E, seed = cases[i]
+        st = torch.cuda.Stream()
+        out = []
+        with torch.cuda.stream(st), bs.Sim(w, n_envs=E) as sim:
+            sim.set_fused_rollout(bs.FUSE_OFF)
+            wb, tr = sim.upload_weights(weights(w, 21)), None
+            for _ in range(n):
+                sim.reset(seed)
+                tr = sim.rollout(wb, T, rchk=True, traj=tr)
+                out.append(snapshot(sim, tr))
+                tr.actions.zero_()
+        return out
+
+    alone = [calls(i, 1)[0] for i in range(2)]
+    with concurrent.futures.ThreadPoolExecutor(2) as pool:
+        jobs = [pool.submit(calls, i, 5) for i in range(2)]
+        for i, job in enumerate(jobs):
+            for k, out in enumerate(job.result(timeout=100)):
+                assert_same(alone[i], out, f"context {i}, call {k}")
