@@ -651,8 +651,8 @@ hipError_t launch_step(const SimParams& p, const EnvState& s, uint32_t k,
   // a rollout in two halves takes the next smaller number also where the batch is one wave per SIMD
   // exactly: the halves' ticks then overlap each other's policies as two waves per SIMD (8 servers,
   // us per tick: 32768 environments 48.8 -> 45.0, 65536 60.3 -> 56.9; in one chain the tick alone is
-  // slower for it, 43.7 -> 46.9), if the lanes then hold all servers' rows (16 servers: 32768 63.0 ->
-  // 61.1; 65536, where they would not, 92.0 -> 95.2)
+  // slower for it, 43.7 -> 46.9; 65537, whose waves are full again, 58.4), if the lanes then hold all
+  // servers' rows (16 servers: 32768 63.0 -> 61.1; 65536, where they would not, 92.0 -> 95.2)
   if (part.n < p.E && lpw > 4 && (p.E + lpw - 1) / lpw <= kFillWaves && p.K >= kShareServers &&
       p.K <= kShareChunk * (64 / (lpw / 2)))
     lpw /= 2;
