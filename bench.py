@@ -115,13 +115,13 @@ def static_bytes(w, tot, E, T, ticks_per_launch):
     return 2 * state_rw + 12 * K + ticks_per_launch * per_tick
 
 
-# the source of each kernel class (with the shared device headers)
+# the source of each kernel class (with the device headers but the two that all share)
 KERNEL_SOURCE = {"policy": ["mlp_kernels.hip", "policy_dev.hpp"],
                  "step": ["sim_kernels.hip", "sim_dev.hpp"],
                  "static": ["sim_kernels.hip", "sim_dev.hpp"], "gae": ["gae_kernels.hip"],
-                 "ppo": ["ppo_kernels.hip"],
-                 "rollout": ["rollout_kernels.hip", "policy_dev.hpp", "sim_dev.hpp"]}
-
+                 "ppo": ["ppo_fused.hip", "ppo_kernels.hip", "ppo_dev.hpp", "train_dev.hpp"],
+                 "rollout": ["rollout_kernels.hip", "rollout_wide.hip", "rollout_dev.hpp",
+                             "policy_dev.hpp", "sim_dev.hpp"]}
 
 def kernel_hash(cls=None):
     """Hash of the sources a kernel class is built from (all kernel sources without a class)."""
@@ -148,9 +148,9 @@ def traffic_for(kernel, cfg_name):
     return ent.get("bytes_per_launch")
 
 
-# kernel classes whose HBM traffic is taken from counters (the minibatch gradient, a sequence of
-# library GEMMs and small kernels, has no single kernel to attribute it to)
-KERNEL_OF = {"policy": "policy_", "step": "learned_k", "static": "static_k", "gae": "gae_k"}
+# kernel classes whose HBM traffic is taken from counters, by a part of their kernels' names (the
+# minibatch gradient is a sequence of kernels, none of which to attribute it to)
+KERNEL_OF = {"policy": "policy_", "step": "learned_k", "static": "static_k", "gae": "gae_"}
 
 
 def _pmc_rows(d):

@@ -2,6 +2,7 @@
 library (no fallback path exists), bench.py refuses more than one GPU with a message, and the
 entry points the build and smoke checks call exist."""
 import os
+import re
 import subprocess
 import sys
 
@@ -25,6 +26,27 @@ def test_binding_fails_loudly_without_the_library(tmp_path):
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "not built" in r.stdout
+
+
+def test_bench_kernel_classes_name_their_kernels_and_sources():
+    """The HBM traffic that bench.py reports for a kernel class is counted over the kernels whose
+    names hold the class's pattern and dropped when the class's sources change: every pattern is
+    the start of a kernel's name in those sources, and they hold every device header that they
+    include (all classes share devmath.hpp and params.hpp)."""
+    sys.path.insert(0, ROOT)
+    import bench
+    csrc = os.path.join(ROOT, "paper_2607_05272_amd", "csrc")
+    text = {f: open(os.path.join(csrc, f)).read() for f in os.listdir(csrc)}
+    kernel = re.compile(r"__global__[^;{]*?void\s+(\w+)\(")
+    for cls, files in bench.KERNEL_SOURCE.items():
+        inc = {h for f in files for h in re.findall(r'#include "(\w+\.hpp)"', text[f])}
+        assert inc - {"devmath.hpp", "params.hpp"} <= set(files), cls
+        if cls in bench.KERNEL_OF:
+            names = [n for f in files for n in kernel.findall(text[f])]
+            assert any(n.startswith(bench.KERNEL_OF[cls]) for n in names), (cls, names)
+    # kernels that the runtime times under a class
+    for cls, file in (("rollout", "rollout_wide.hip"), ("ppo", "ppo_fused.hip")):
+        assert file in bench.KERNEL_SOURCE[cls]
 
 
 def test_bench_refuses_several_gpus():
