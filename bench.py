@@ -123,6 +123,7 @@ KERNEL_SOURCE = {"policy": ["mlp_kernels.hip", "policy_dev.hpp"],
                  "rollout": ["rollout_kernels.hip", "rollout_wide.hip", "rollout_dev.hpp",
                              "policy_dev.hpp", "sim_dev.hpp"]}
 
+
 def kernel_hash(cls=None):
     """Hash of the sources a kernel class is built from (all kernel sources without a class)."""
     d = os.path.join(ROOT, "paper_2607_05272_amd", "csrc")
@@ -163,10 +164,13 @@ def _pmc_rows(d):
 
 
 def _per_dispatch(rows, counter, match):
-    """Counter total over the kernels that `match`, per dispatch of them."""
+    """Counter total over the kernels that `match`, per dispatch of them over the whole batch (a
+    rollout in two halves launches half of the grid at a time)."""
     tot, disp = 0.0, set()
+    rows = [r for r in rows if r["Counter_Name"] == counter and match(r["Kernel_Name"])]
+    whole = max((int(r["Grid_Size"]) for r in rows), default=0)
     for r in rows:
-        if r["Counter_Name"] != counter or not match(r["Kernel_Name"]):
+        if int(r["Grid_Size"]) < whole:
             continue
         tot += float(r["Counter_Value"])
         disp.add(r.get("Dispatch_Id") or r.get("Correlation_Id"))

@@ -49,6 +49,16 @@ def test_bench_kernel_classes_name_their_kernels_and_sources():
         assert file in bench.KERNEL_SOURCE[cls]
 
 
+def test_bench_traffic_is_of_whole_batch_launches():
+    """Halves of a batch, which a rollout launches side by side, are not averaged with whole ones."""
+    sys.path.insert(0, ROOT)
+    import bench
+    row = lambda i, grid, v: {"Counter_Name": "FETCH_SIZE", "Kernel_Name": "learned_k<4>",  # noqa: E731
+                              "Dispatch_Id": str(i), "Grid_Size": str(grid), "Counter_Value": str(v)}
+    rows = [row(0, 512, 5.0), row(1, 512, 6.0), row(2, 1024, 10.0), row(3, 1024, 12.0)]
+    assert bench._per_dispatch(rows, "FETCH_SIZE", lambda k: "learned_k" in k) == (11.0, 2)
+
+
 def test_bench_refuses_several_gpus():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
