@@ -195,12 +195,13 @@ __global__ __launch_bounds__(64 + kMovers) void gae_tile_k(int T, int E,
 // those start on cache lines (E a multiple of 16; us with V, tiled against streaming, T = 512):
 // 4096 environments 16.9 / 31.2, 12288 30.1 / 34.1, 14336 35.9 / 36.1, 65536 213 / 171. Where
 // they straddle lines: 5001 23.4 / 34.0, 9999 39.7 / 35.8, 14001 55.0 / 39.2. Trajectories shorter than
-// its chunks of 128 steps leave it nothing to overlap (14336 x 16 6.6 / 5.3, 14336 x 64 8.6 / 6.2, 16 x
-// 64 5.2 / 5.2, 16 x 96 5.2 / 6.3, 4096 x 96 6.0 / 6.8, 8192 x 96 7.3 / 7.4, 8192 x 128 8.5 / 8.9, 12288 x 256 18.2 /
-// 18.6).
+// its chunks of 128 steps leave it little to overlap (with V 14336 x 16 6.6 / 5.3, 14336 x 64 8.6 / 6.2; its
+// time over the streaming form's with V at T = 64, 96, 128: 100 environments 1.02, 0.88, 0.76, 4096 1.04,
+// 0.88, 0.77, 10000 1.19, 1.02, 0.94; without V at 96, 128, 160: 1.08, 0.96, 0.93, 1.04, 0.96, 0.93 and
+// 1.11, 0.95, 0.95).
 constexpr int kTileE = 14336, kTileEOdd = 8192;
-static bool tiled(int T, int E) {
-  return E <= (E % kEnvs ? kTileEOdd : kTileE) && T >= 64 + E / 128;
+static bool tiled(int T, int E, bool has_v) {
+  return E <= (E % kEnvs ? kTileEOdd : kTileE) && T >= (has_v ? 64 + E / 256 : kSteps);
 }
 // From which batches on the streaming form loads one row ahead in place of 8, earlier where the waves'
 // rows straddle cache lines, and none (us with and without V, 8, 1 and none: 163840 x 300 271 and 241,
@@ -216,7 +217,7 @@ static void launch(int T, int E, const double* r, const float* v, double gamma, 
     hipLaunchKernelGGL(kern, dim3((E + envs - 1) / envs), dim3(block), 0, st, T, E, r, v, gamma, gl,
                        adv, ret);
   };
-  if (tiled(T, E)) go(gae_tile_k<HASV>, kEnvs, 64 + kMovers);
+  if (tiled(T, E, HASV)) go(gae_tile_k<HASV>, kEnvs, 64 + kMovers);
   else if (E < (E % kEnvs ? kAhead1EOdd : kAhead1E)) go(gae_stream_k<HASV, 8, 64>, 64, 64);
   else if (E < kRowE) go(gae_stream_k<HASV, 1, 256>, 256, 256);
   else go(gae_row_k, 256, 256);

@@ -20,8 +20,8 @@ def test_gae_tiles(E, T, value):
     check(E, T, value)
 
 
-@pytest.mark.parametrize("E,T", [(1, 63), (1, 64), (17, 72), (8192, 127), (8192, 128), (8193, 128),
-                                 (14336, 175), (14336, 176), (14352, 176), (163839, 9), (163841, 9),
+@pytest.mark.parametrize("E,T", [(1, 63), (1, 64), (17, 72), (8192, 95), (8192, 96), (8193, 128),
+                                 (14336, 119), (14336, 127), (14352, 128), (163839, 9), (163841, 9),
                                  (184304, 17), (184320, 17), (393215, 2), (393216, 3)])
 @pytest.mark.parametrize("value", [True, False])
 def test_gae_forms(E, T, value):
